@@ -48,7 +48,8 @@ def phase_work(name: str, info, nb: int, m: int, steps: int, real_bytes: int, n1
     happs = steps * (m + 1)  # H applications of nb bands in the timed steps
     bands = happs * nb
     if name == "proj" or name == "nl":
-        return 8.0 * npw * nproj * nb * happs, "flop"
+        # real products on pairs (G, -G): the projectors are real functions of position
+        return 4.0 * npw * nproj * nb * happs, "flop"
     if name == "gram":
         # S = Y^H Y (Hermitian: one triangle, 4 N_pw N_b^2) and H_s = Y^H W (8 N_pw N_b^2)
         return 12.0 * npw * nb * nb * steps, "flop"

@@ -38,7 +38,7 @@ static thread_local std::string g_last_error;
 // the library runs on holds its own copy for the life of the process; host code reaches it only
 // through the device address hipGetSymbolAddress returns (kept per device below), never through
 // the array's name.
-constexpr size_t kScratchBytes = 64ull << 20;
+constexpr size_t kScratchBytes = (64ull << 20) + 4096;  // 64 MiB of buffers and their alignment
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
@@ -81,8 +81,12 @@ struct pw_handle_s {
   // PW_PROGRESS=1 in the environment: report each completed filter block of a band-blocked
   // step on stderr (the stream is synchronised at each report).
   bool progress = false;
-  // Block whose bf16 planes the planes buffer holds (split-precision projectors), or null, and
-  // the number of its leading columns they cover.
+  // Block whose pair planes the planes buffer holds (split-precision projectors), or null, and the
+  // number of its columns.
+  const void* fg_src = nullptr;
+  int fg_n = 0;
+  // Block whose bf16 planes the planes buffer holds (Gram product, rotation), or null, and the number
+  // of its leading columns they cover.
   const void* yp_src = nullptr;
   int yp_n = 0;
   // Block whose planes follow those of yp_src (the Gram product's second operand), or null.
@@ -94,7 +98,7 @@ struct pw_handle_s {
   unsigned char* scratch = nullptr;
   unsigned char* ws = nullptr;
   size_t ws_sb = 0, ws_g1 = 0, ws_parts = 0, ws_pt = 0, ws_yp = 0;
-  int ws_cols = 0, ws_fft_batch = 0;
+  int ws_cols = 0, ws_fft_batch = 0, ws_nsplit = 0;
   std::chrono::steady_clock::time_point t_step;
   void report(const char* what, int i, int n) {
     if (!progress) return;
@@ -208,7 +212,7 @@ pw_status fail(pw_handle_s* h, pw_status s, const std::string& m) {
 
 template <typename T>
 struct Engine {
-  enum { PLANES_NONE = 0, PLANES_NEXT = 1, PLANES_GRAM = 2, PLANES_KEEP = 3 };
+  enum { PLANES_NONE = 0, PLANES_NEXT = 1, PLANES_LAST = 2, PLANES_GRAM = 3 };
   pw_handle_s* h;
   const Plan& P;
   explicit Engine(pw_handle_s* hh) : h(hh), P(hh->plan) {}
@@ -219,8 +223,8 @@ struct Engine {
   cplx<T>* zb() const { return h->at<cplx<T>>(P.lay.zb); }
 
   bool flag(unsigned f) const { return (P.flags & f) != 0; }
-  // With split-precision projector products the table is stored as bf16 hi and lo planes of
-  // one (re, im) word per entry, leading dimension ldw words, in the same arena bytes.
+  // With split-precision projector products the table is stored as bf16 hi and lo planes of one
+  // (re, im) word per entry on half of the sphere, nproj32 columns of ldh words.
   bool beta_planes() const { return std::is_same<T, float>::value && flag(PW_FLAG_BF16_KB); }
   bool beta_otf() const { return flag(PW_FLAG_BETA_OTF); }
   BetaGen beta_gen() const {
@@ -259,7 +263,7 @@ struct Engine {
     return d;
   }
   unsigned int* beta_hi() const { return h->at<unsigned int>(P.lay.beta); }
-  unsigned int* beta_lo() const { return beta_hi() + (size_t)P.ldw * P.nproj; }
+  unsigned int* beta_lo() const { return beta_hi() + (size_t)P.ldh * P.nproj32; }
   // Work buffers of an H application: the arena's, or the static work array's during
   // pw_apply_h_noalloc.
   template <typename X>
@@ -271,20 +275,35 @@ struct Engine {
   double2* parts_buf() const { return work<double2>(P.lay.parts, h->ws_parts); }
   int fft_batch() const { return h->ws ? h->ws_fft_batch : P.fft_batch; }
   unsigned int* yp_hi() const { return work<unsigned int>(P.lay.yp, h->ws_yp); }
-  unsigned int* yp_lo() const { return yp_hi() + (size_t)P.ldw * (h->ws ? h->ws_cols : P.yp_cols); }
-  // the unblocked step keeps the planes of W = H Y beside those of Y for the Gram product
+  unsigned int* yp_lo() const { return yp_hi() + (size_t)P.ldy * (h->ws ? h->ws_cols : P.yp_cols); }
+  // the unblocked step keeps the planes of Y and W = H Y for the Gram product
   bool gram_planes() const {
     return std::is_same<T, float>::value && (beta_planes() || P.rspace) && flag(PW_FLAG_BF16_GRAM) &&
            P.yp_cols >= 2 * P.nbb;
   }
+  // offset of the pair planes of nb columns in the planes buffer (gram_planes: the place of W's planes)
+  size_t fg_off(int nb) const { return !h->ws && gram_planes() ? (size_t)P.ldw * nb : 0; }
   // with projector planes, D B^H Y is kept as the nonlocal product's B planes in the bytes of PT
   unsigned int* pt_hi() const { return work<unsigned int>(P.lay.pt, h->ws_pt); }
-  unsigned int* pt_lo() const { return pt_hi() + (size_t)P.nproj * (h->ws ? h->ws_cols : P.nbb); }
+  unsigned int* pt_lo() const { return pt_hi() + (size_t)P.nproj32 * (h->ws ? h->ws_cols : P.nbb); }
+  long ldpt() const { return P.nproj32 / 2; }  // words of two projectors
+  // partials of one band and projector that the work buffer holds
+  long parts_cap(int nb) const {
+    return h->ws ? (long)h->ws_nsplit * h->ws_cols / nb : (long)P.nsplit_proj * P.nbb / nb;
+  }
   bool planes_of(const void* Y, int nb) const { return Y && h->yp_src == Y && nb <= h->yp_n; }
   void set_planes(const void* Y, int nb) {
     h->yp_src = Y;
     h->yp_n = Y ? nb : 0;
     h->wp_src = nullptr;
+  }
+  void set_pairs(const void* Y, int nb) {
+    h->fg_src = Y;
+    h->fg_n = Y ? nb : 0;
+  }
+  void drop_planes() {
+    set_planes(nullptr, 0);
+    set_pairs(nullptr, 0);
   }
   // Rotation coefficients (n x n, leading dimension n) as the nn product's B operand: with
   // split-precision rotation, bf16 planes (hi, then lo) in the bytes of the fp32 table at off;
@@ -433,10 +452,10 @@ struct Engine {
 
   // out = alpha ((kin - c) Y + Zl + B D B^H Y) - beta Yp, where Zl is first filled with the
   // local potential part.  Zl may equal out (apply_h); Yp may equal out (in-place update).
-  // planes_out (split-precision projectors): PLANES_NEXT writes the bf16 planes of out for a
-  // following hop on out; PLANES_GRAM writes them beside those of Y for the Gram product and keeps
-  // Y's; PLANES_KEEP keeps Y's (the caller leaves Y unchanged while it uses them); PLANES_NONE
-  // drops them.
+  // planes_out (split-precision projectors): PLANES_NEXT writes the pair planes of out for a following
+  // hop on out; PLANES_LAST writes its bf16 planes for the Gram product too (gram_planes); PLANES_GRAM
+  // writes those of out beside those of Y, which are made here if no earlier hop wrote them;
+  // PLANES_NONE keeps none.
   pw_status hop(const cplx<T>* Y, long ldy, int nb, cplx<T>* out, long ldo, cplx<T>* Zl, long ldz, double alpha,
                 double c, double beta_c, const cplx<T>* Yp, long ldp, int planes_out = PLANES_NONE) {
     // the local part (FFTs, memory bound) on the second stream, the projection (matrix cores)
@@ -447,7 +466,7 @@ struct Engine {
     const bool overlap = !P.rspace && !h->timing && (double)P.npw * nb >= (double)(1 << 26);
     if (P.rspace) {
       // the forward sticks write the updated block: nothing else to do
-      set_planes(nullptr, 0);
+      drop_planes();
       return local_part_rs(Y, ldy, out, ldo, nb, alpha, c, beta_c, Yp, ldp, h->stream);
     }
     if (overlap) {
@@ -464,26 +483,29 @@ struct Engine {
       double2* parts = parts_buf();
       if constexpr (std::is_same<T, float>::value) {
         if (beta_planes()) {
-          if (!planes_of(Y, nb)) {
-            PW_TIMED(PW_PH_OTHER, launch_split_planes(Y, ldy, P.npw, nb, yp_hi(), yp_lo(), P.ldw, h->stream));
-            set_planes(Y, nb);
+          const int kt = (int)(P.ldh / 16), ns = pairs_proj_splits(P.nproj, nb, kt, parts_cap(nb));
+          if (h->fg_src != static_cast<const void*>(Y) || h->fg_n != nb) {
+            if (fg_off(nb) == 0) set_planes(nullptr, 0);  // the same bytes
+            h->wp_src = nullptr;
+            PW_TIMED(PW_PH_OTHER, launch_pair_planes(Y, ldy, P.npw, nb, yp_hi() + fg_off(nb), yp_lo() + fg_off(nb),
+                                                     P.ldh, h->stream));
           }
-          PW_TIMED(PW_PH_PROJ, launch_gemm_cn_bf16x3_planes(beta_hi(), beta_lo(), P.ldw, yp_hi(), yp_lo(), P.ldw,
-                                                            P.nproj, nb, P.npw, P.nsplit_proj, parts, h->stream));
+          PW_TIMED(PW_PH_PROJ, launch_pairs_proj(beta_hi(), beta_lo(), P.ldh, yp_hi() + fg_off(nb),
+                                                 yp_lo() + fg_off(nb), P.ldh, P.nproj, nb, kt, ns, parts, h->stream));
+          PW_TIMED(PW_PH_PROJ_REDUCE, launch_pair_reduce(parts, ns, P.nproj, nb, h->at<double>(P.lay.dscale), pt_hi(),
+                                                         pt_lo(), ldpt(), h->stream));
         }
       }
-      if (beta_otf())
-        PW_TIMED(PW_PH_PROJ, launch_gemm_cn_beta<T>(beta_gen(), Y, ldy, nb, P.nsplit_proj, parts, h->stream));
-      else if (!beta_planes())
-        PW_TIMED(PW_PH_PROJ, cn(false, beta(), P.ldw, Y, ldy, nullptr, 0, nb, P.nproj, nb, P.npw, P.nsplit_proj, parts));
-      if (beta_planes())
-        PW_TIMED(PW_PH_PROJ_REDUCE, launch_reduce_planes(parts, P.nsplit_proj, P.nproj, nb,
-                                                         h->at<double>(P.lay.dscale), 4, pt_hi(), pt_lo(), P.nproj,
-                                                         h->stream));
-      else
+      if (!beta_planes()) {
+        if (beta_otf())
+          PW_TIMED(PW_PH_PROJ, launch_gemm_cn_beta<T>(beta_gen(), Y, ldy, nb, P.nsplit_proj, parts, h->stream));
+        else
+          PW_TIMED(PW_PH_PROJ,
+                   cn(false, beta(), P.ldw, Y, ldy, nullptr, 0, nb, P.nproj, nb, P.npw, P.nsplit_proj, parts));
         PW_TIMED(PW_PH_PROJ_REDUCE, launch_reduce_parts<T>(parts, P.nsplit_proj, P.nproj, nb,
                                                            h->at<double>(P.lay.dscale), 4, nullptr, 0, PT, P.nproj,
                                                            h->stream));
+      }
     }
     if (overlap) PW_HIP(hipStreamWaitEvent(h->stream, h->ev_join, 0));
     EpiH e;
@@ -498,27 +520,34 @@ struct Engine {
     e.ldz = ldz;
     e.Yp = Yp;
     e.ldp = ldp;
-    e.ph = e.pl = nullptr;
-    e.ldpl = 0;
+    e.ph = e.pl = e.ch = e.cl = nullptr;
+    e.ldpl = e.ldcl = 0;
     e.vec4 = 0;
-    const bool keep_y = (planes_out == PLANES_GRAM || planes_out == PLANES_KEEP) && planes_of(Y, nb) &&
-                        static_cast<const void*>(out) != static_cast<const void*>(Y) &&
-                        static_cast<const void*>(Zl) != static_cast<const void*>(Y);
-    const void* ysrc = h->yp_src;
-    set_planes(keep_y ? ysrc : nullptr, keep_y ? nb : 0);
     if constexpr (std::is_same<T, float>::value) {
       if (beta_planes()) {
-        const bool w_gram = planes_out == PLANES_GRAM && keep_y && gram_planes();
-        if (planes_out == PLANES_NEXT || w_gram) {
-          const size_t pc = w_gram ? (size_t)P.ldw * nb : 0;  // W's columns follow Y's
-          e.ph = yp_hi() + pc;
-          e.pl = yp_lo() + pc;
-          e.ldpl = P.ldw;
+        const bool w_gram = planes_out == PLANES_GRAM && gram_planes();
+        if (w_gram && !planes_of(Y, nb)) {
+          PW_TIMED(PW_PH_OTHER, launch_split_planes(Y, ldy, P.npw, nb, yp_hi(), yp_lo(), P.ldw, h->stream));
+          set_planes(Y, nb);
         }
-        PW_TIMED(PW_PH_NL, launch_gemm_nn_bf16x3_planes(beta_hi(), beta_lo(), P.ldw, pt_hi(), pt_lo(), P.nproj,
-                                                        P.npw, nb, P.nproj, out, ldo, e, h->stream));
-        if (planes_out == PLANES_NEXT) set_planes(out, nb);
+        if (!w_gram) set_planes(nullptr, 0);
+        set_pairs(nullptr, 0);
+        if (planes_out == PLANES_NEXT || planes_out == PLANES_LAST) {
+          e.ph = yp_hi() + fg_off(nb);
+          e.pl = yp_lo() + fg_off(nb);
+          e.ldpl = P.ldh;
+        }
+        if (w_gram || (planes_out == PLANES_LAST && gram_planes())) {
+          const size_t pc = w_gram ? (size_t)P.ldw * nb : 0;  // W's columns follow Y's
+          e.ch = yp_hi() + pc;
+          e.cl = yp_lo() + pc;
+          e.ldcl = P.ldw;
+        }
+        PW_TIMED(PW_PH_NL, launch_pairs_nl(beta_hi(), beta_lo(), P.ldh, pt_hi(), pt_lo(), ldpt(), P.npw, nb,
+                                           P.nproj32 / 32, out, ldo, e, h->stream));
+        if (e.ph) set_pairs(out, nb);
         if (w_gram) h->wp_src = out;
+        else if (e.ch) set_planes(out, nb);
         return PW_OK;
       }
     }
@@ -589,7 +618,7 @@ struct Engine {
   // HX = H X in column groups of `step` bands (the filter block, or what the static work array
   // holds during pw_apply_h_noalloc).
   pw_status apply_h(const cplx<T>* X, cplx<T>* HX, int nb, int ld, int step) {
-    set_planes(nullptr, 0);
+    drop_planes();
     for (int c0 = 0; c0 < nb; c0 += step) {
       const int w = std::min(step, nb - c0);
       pw_status s = hop(X + (long)c0 * ld, ld, w, HX + (long)c0 * ld, ld, HX + (long)c0 * ld, ld, 1.0, 0.0, 0.0,
@@ -624,7 +653,7 @@ struct Engine {
       sg = sn;
     }
     PW_TIMED(PW_PH_OTHER, launch_copy_cols<T>(cur, ldw, Y0, ld0, P.npw, w, h->stream));
-    if (h->yp_src == static_cast<const void*>(cur)) h->yp_src = Y0;  // same values, same columns
+    if (h->fg_src == static_cast<const void*>(cur)) h->fg_src = Y0;  // same values, same columns
     return PW_OK;
   }
 
@@ -672,7 +701,7 @@ struct Engine {
     // X' = X C into W's storage, then back into X
     PW_TIMED(PW_PH_ROTATE, rot(X, ld, C, nb, 0, nb, W, ldw, st));
     PW_TIMED(PW_PH_OTHER, launch_copy_cols<T>(W, ldw, X, ld, P.npw, nb, h->stream));
-    set_planes(nullptr, 0);
+    drop_planes();
     return finish(nb, eig_host, resid_host, bounds_out, prm.b);
   }
 
@@ -687,7 +716,7 @@ struct Engine {
 
   pw_status eig_step(cplx<T>* X, cplx<T>* HX, int nb, int ld, const pw_step_params& prm, double* eig_host,
                      double* resid_host, double* bounds_out) {
-    set_planes(nullptr, 0);
+    drop_planes();
     if (P.nbb < P.nbands) return eig_step_blocked(X, HX, nb, ld, prm, eig_host, resid_host, bounds_out);
     const int m = prm.degree;
     double bmax = prm.b;
@@ -699,7 +728,7 @@ struct Engine {
     if (m >= 1) {
       const double e = 0.5 * (prm.b - prm.a), c = 0.5 * (prm.b + prm.a);
       const double s1 = e / (prm.a_lo - c), tau = 2.0 / s1;
-      s = hop(X, ld, nb, u1(), ldw, zb(), ldw, s1 / e, c, 0.0, nullptr, 0, PLANES_NEXT);
+      s = hop(X, ld, nb, u1(), ldw, zb(), ldw, s1 / e, c, 0.0, nullptr, 0, m == 1 ? PLANES_LAST : PLANES_NEXT);
       if (s != PW_OK) return s;
       const cplx<T>* prev = X;
       long ldprev = ld;
@@ -708,7 +737,8 @@ struct Engine {
       for (int k = 1; k < m; ++k) {
         const double sn = 1.0 / (tau - sg);
         cplx<T>* dst = (prev == X) ? u0() : const_cast<cplx<T>*>(prev);
-        s = hop(cur, ldw, nb, dst, ldw, zb(), ldw, 2.0 * sn / e, c, sg * sn, prev, ldprev, PLANES_NEXT);
+        s = hop(cur, ldw, nb, dst, ldw, zb(), ldw, 2.0 * sn / e, c, sg * sn, prev, ldprev,
+                k == m - 1 ? PLANES_LAST : PLANES_NEXT);
         if (s != PW_OK) return s;
         prev = cur;
         ldprev = ldw;
@@ -721,7 +751,7 @@ struct Engine {
     }
     // W = H Y
     cplx<T>* W = dead;
-    s = hop(Y, ldy, nb, W, ldw, zb(), ldw, 1.0, 0.0, 0.0, nullptr, 0, gram_planes() ? PLANES_GRAM : PLANES_KEEP);
+    s = hop(Y, ldy, nb, W, ldw, zb(), ldw, 1.0, 0.0, 0.0, nullptr, 0, PLANES_GRAM);
     if (s != PW_OK) return s;
     s = project_solve(Y, ldy, W, ldw, nb);
     if (s != PW_OK) return s;
@@ -743,7 +773,7 @@ struct Engine {
     if (s != PW_OK) return s;
     double* resid_d = h->at<double>(P.lay.resid);
     PW_TIMED(PW_PH_RESID, launch_resid<T>(Wr, ldwr, X, ld, eig_d, P.npw, nb, resid_d, h->stream));
-    set_planes(nullptr, 0);
+    drop_planes();
     return finish(nb, eig_host, resid_host, bounds_out, bmax);
   }
 
@@ -752,9 +782,12 @@ struct Engine {
     double2* parts = h->at<double2>(P.lay.parts);
     double2* SH = h->at<double2>(P.lay.sh);
     if (gram_planes() && planes_of(Y, nb) && h->wp_src == static_cast<const void*>(W)) {
+      // the words past the last plane wave are read too; the pair planes were in the same bytes
+      if (beta_planes())
+        PW_TIMED(PW_PH_OTHER, launch_zero_plane_rows(yp_hi(), yp_lo(), P.ldw, P.npw, 2 * nb, h->stream));
       // S = Y^H Y is Hermitian: its tiles below the diagonal are skipped and mirrored afterwards
       PW_TIMED(PW_PH_GRAM, launch_gemm_cn_bf16x3_planes(yp_hi(), yp_lo(), P.ldw, yp_hi(), yp_lo(), P.ldw, nb, 2 * nb,
-                                                        P.npw, P.nsplit_gram, parts, h->stream, 4, nb));
+                                                        P.npw, P.nsplit_gram, parts, h->stream, nb));
       return dense_solve(nb, P.nsplit_gram, 0.0, true);
     }
     if constexpr (std::is_same<T, float>::value) {
@@ -766,7 +799,7 @@ struct Engine {
         set_planes(Y, nb);
         h->wp_src = W;
         PW_TIMED(PW_PH_GRAM, launch_gemm_cn_bf16x3_planes(yp_hi(), yp_lo(), P.ldw, yp_hi(), yp_lo(), P.ldw, nb,
-                                                          2 * nb, P.npw, P.nsplit_gram, parts, h->stream, 4, nb));
+                                                          2 * nb, P.npw, P.nsplit_gram, parts, h->stream, nb));
         return dense_solve(nb, P.nsplit_gram, 0.0, true);
       }
     }
@@ -923,7 +956,7 @@ struct Engine {
   // Rayleigh-Ritz on span Z, X' = Z C_1 into X, P' = [R P] C_1(R and P rows) into Pd.
   pw_status lobpcg_step(cplx<T>* X, cplx<T>* Pd, int nb, long ld, bool have_p, double* eig_host,
                         double* resid_host, int* kept) {
-    set_planes(nullptr, 0);
+    drop_planes();
     const long ldw = P.ldw;
     cplx<T>* Z = h->at<cplx<T>>(P.lay.lz);
     cplx<T>* HZ = Z + (size_t)3 * P.nbands * ldw;
@@ -983,7 +1016,7 @@ struct Engine {
   // vectors, W = T R, [W P] <- [W P] - X (X^H [W P]), H W and H P, then per column the Ritz vector
   // of span{x_j, w_j, p_j}: X <- a X + b W + g P, P <- b W + g P.
   pw_status ppcg_step(cplx<T>* X, cplx<T>* Pd, int nb, long ld, bool have_p, double* eig_host, double* resid_host) {
-    set_planes(nullptr, 0);
+    drop_planes();
     const long ldw = P.ldw;
     cplx<T>* Z = h->at<cplx<T>>(P.lay.lz);
     cplx<T>* HZ = Z + (size_t)3 * P.nbands * ldw;
@@ -1256,8 +1289,8 @@ struct Engine {
       PW_HIP(launch_beta_gen_tables(beta_gen(), h->at<double>(p.lay.frac), p.L, p.beta_sigma,
                                     h->at<double>(p.lay.brad), h->at<double2>(p.lay.bph), st));
     else if (p.nproj && beta_planes())
-      PW_HIP(launch_beta_planes(h->at<int>(p.lay.miller), p.npw, h->at<double>(p.lay.frac), p.natoms, p.L,
-                                p.beta_sigma, p.proj_form, beta_hi(), beta_lo(), p.ldw, st));
+      PW_HIP(launch_beta_planes(h->at<int>(p.lay.miller), p.nh, h->at<double>(p.lay.frac), p.natoms, p.nproj32, p.L,
+                                p.beta_sigma, p.proj_form, beta_hi(), beta_lo(), p.ldh, st));
     else if (p.nproj && !p.rspace)
       PW_HIP(launch_beta_table<T>(h->at<int>(p.lay.miller), p.npw, h->at<double>(p.lay.frac), p.natoms, p.L,
                                   p.beta_sigma, p.proj_form, beta(), p.ldw, st));
@@ -1273,8 +1306,9 @@ struct Engine {
       PW_HIP(up(p.lay.rsao, p.rs_aoff.data(), sizeof(int) * p.rs_aoff.size()));
       PW_HIP(up(p.lay.rsae, p.rs_aent.data(), sizeof(int) * p.rs_aent.size()));
     }
-    // the block planes' words past the last plane wave stay zero from here on (the cn products read them)
-    if (p.yp_cols > 0) PW_HIP(launch_zero_plane_rows(yp_hi(), yp_lo(), p.ldw, p.npw, p.yp_cols, st));
+    // real-space projectors: the block planes' words past the last plane wave stay zero from here on (the
+    // Gram product reads them)
+    if (p.rspace && p.yp_cols > 0) PW_HIP(launch_zero_plane_rows(yp_hi(), yp_lo(), p.ldw, p.npw, p.yp_cols, st));
     PW_HIP(hipStreamSynchronize(st));
     return PW_OK;
   }
@@ -1535,11 +1569,16 @@ static int noalloc_layout(pw_handle* h, int nb) {
   const size_t sb1 = (size_t)P.nst * g.n3 * cb;
   const size_t g11 = P.fl.fused ? 0 : (size_t)g.n3 * g.n2 * g.n1a * cb;
   const bool planes = P.real_bytes == 4 && (P.flags & PW_FLAG_BF16_KB) && P.nproj > 0;
-  const size_t per_col = sb1 + g11 + (P.nproj ? 16 * (size_t)P.nsplit_proj * P.nproj + cb * P.nproj : 0) +
-                         (planes ? 8 * (size_t)P.ldw : 0);
+  const size_t npt = planes ? P.nproj32 : P.nproj;
+  // the projection on pairs takes fewer K splits where one column would not fit otherwise
+  int ns = P.nsplit_proj;
+  auto per_column = [&]() {
+    return sb1 + g11 + (P.nproj ? 16 * (size_t)ns * P.nproj + cb * npt : 0) + (planes ? 8 * (size_t)P.ldy : 0);
+  };
   const size_t slack = 5 * kArenaAlign;
   if (kScratchBytes <= slack) return 0;
-  long w = (long)((kScratchBytes - slack) / per_col);
+  if (planes && per_column() > kScratchBytes - slack) ns = 1;
+  long w = (long)((kScratchBytes - slack) / per_column());
   w = std::min<long>(w, std::min(nb, P.nbb));
   if (w < 1) return 0;
   auto al = [](size_t x) { return (x + kArenaAlign - 1) / kArenaAlign * kArenaAlign; };
@@ -1550,14 +1589,15 @@ static int noalloc_layout(pw_handle* h, int nb) {
   h->ws_g1 = off;
   off = al(off + g11 * fb);
   h->ws_parts = off;
-  off = al(off + (P.nproj ? 16 * (size_t)P.nsplit_proj * P.nproj * w : 0));
+  off = al(off + (P.nproj ? 16 * (size_t)ns * P.nproj * w : 0));
   h->ws_pt = off;
-  off = al(off + (P.nproj ? cb * P.nproj * w : 0));
+  off = al(off + (P.nproj ? cb * npt * w : 0));
   h->ws_yp = off;
-  off = al(off + (planes ? 8 * (size_t)P.ldw * w : 0));
+  off = al(off + (planes ? 8 * (size_t)P.ldy * w : 0));
   if (off > kScratchBytes) return 0;
   h->ws_cols = (int)w;
   h->ws_fft_batch = (int)fb;
+  h->ws_nsplit = ns;
   return (int)w;
 }
 
@@ -1582,17 +1622,6 @@ pw_status pw_apply_h_noalloc(pw_handle* h, const void* X, void* HX, int nb, int 
   const bool timing = h->timing;
   h->timing = false;
   h->ws = h->scratch;
-  // the bf16 planes of the block live in the shared array: clear the words past the last plane
-  // wave, which the projection reads as zeros
-  if (h->plan.real_bytes == 4 && (h->plan.flags & PW_FLAG_BF16_KB) && h->plan.nproj > 0) {
-    unsigned int* yh = reinterpret_cast<unsigned int*>(h->ws + h->ws_yp);
-    if (launch_zero_plane_rows(yh, yh + (size_t)h->plan.ldw * w, h->plan.ldw, h->plan.npw, w, h->stream) !=
-        hipSuccess) {
-      h->ws = nullptr;
-      h->timing = timing;
-      return fail(h, PW_EDEVICE, "clearing the work array failed");
-    }
-  }
   if (h->plan.prec == PW_FP64)
     s = Engine<double>(h).apply_h(static_cast<const double2*>(X), static_cast<double2*>(HX), nb, ld, w);
   else
@@ -1600,9 +1629,8 @@ pw_status pw_apply_h_noalloc(pw_handle* h, const void* X, void* HX, int nb, int 
   // the planes bookkeeping refers to the work array only during this call
   h->ws = nullptr;
   h->timing = timing;
-  h->yp_src = nullptr;
-  h->yp_n = 0;
-  h->wp_src = nullptr;
+  h->fg_src = h->yp_src = h->wp_src = nullptr;
+  h->fg_n = h->yp_n = 0;
   return s;
 }
 

@@ -28,30 +28,13 @@
 
 #include <type_traits>
 
-#include "bf16split.hpp"
+#include "bf16mma.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
-#include "pipe_addr.hpp"
 
 namespace pw {
 
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef float v4f16 __attribute__((ext_vector_type(4)));
-
-constexpr int hBK = 16;       // complex K per tile = 32 real k' = one MFMA slab
-constexpr int hFlush = 256;   // K tiles (4096 complex K) per fp32 MFMA accumulation before fp64
-constexpr int hXcd = 8;
 constexpr int hTM = 128, hTN = 128;  // workgroup tile
-
-__device__ __forceinline__ int chunk_of(int row, int slot) {
-  return (((row >> 4) << 2) + slot) * 16 + ((row & 15) ^ slot);
-}
-
-__device__ __forceinline__ int xcd_tile16(int w, int total) {
-  const int per = total / hXcd, rem = total % hXcd;
-  const int x = w % hXcd, i = w / hXcd;
-  return x < rem ? x * (per + 1) + i : rem * (per + 1) + (x - rem) * per + i;
-}
 
 // (re, im) words -> (im, -re): B'' from B' (cn)
 __device__ __forceinline__ v8bf swapneg_hi(v8bf v) {
@@ -70,16 +53,6 @@ __device__ __forceinline__ v8bf swapneg_lo(v8bf v) {
   u.z = ((u.z >> 16) | (u.z << 16)) ^ 0x00008000u;
   u.w = ((u.w >> 16) | (u.w << 16)) ^ 0x00008000u;
   return __builtin_bit_cast(v8bf, u);
-}
-
-__device__ __forceinline__ v4f16 mma16(v8bf a, v8bf b, v4f16 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// Fragment of rows row0..row0+15 (row0 a multiple of 16): lane l reads chunk (row0 + l % 16, l / 16).
-__device__ __forceinline__ v8bf frag(const uint4* plane, int row0, int lane) {
-  const int slot = lane >> 4, i = lane & 15;
-  return __builtin_bit_cast(v8bf, plane[((row0 >> 4) << 6) + slot * 16 + (i ^ slot)]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -523,35 +496,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 }
 
 // Epilogue of the nn products for a wave's AT x BT blocks of 16 x 16 (accumulator layout of the
-// 16 x 16 MFMA: lane l holds rows 4 (l / 16) + r, column l % 16): out = update(acc) as EpiH says,
-// plus the bf16 planes of out when e.ph is set.
+// 16 x 16 MFMA: lane l holds rows 4 (l / 16) + r, column l % 16): out = acc, plus Zl in mode 2.
 template <int AT, int BT>
 __device__ __forceinline__ void epi_tile(const v4f16 (&cr)[AT][BT], const v4f16 (&ci)[AT][BT], int row_base,
                                          int col_base, int lane, int M, int N, float2* out, long ldo,
                                          const EpiH& e) {
-  const float* kin = static_cast<const float*>(e.kin);
-  const float2* Y = static_cast<const float2*>(e.Y);
   const float2* Zl = static_cast<const float2*>(e.Zl);
-  const float2* Yp = static_cast<const float2*>(e.Yp);
-  const float alpha = (float)e.alpha, cc = (float)e.c, beta = (float)e.beta;
-  const float2 zero2 = make_float2(0.f, 0.f);
-  // one entry: v = accumulator, kr = kin[row], y, z, p = Y, Zl, Yp at (row, col)
-  auto update = [&](float2 v, float kr, float2 y, float2 z, float2 p) {
-    if (e.mode == 1) {
-      const float kc = kr - cc;
-      v.x = alpha * (kc * y.x + z.x + v.x);
-      v.y = alpha * (kc * y.y + z.y + v.y);
-      if (Yp) {
-        v.x -= beta * p.x;
-        v.y -= beta * p.y;
-      }
-    }
-    if (e.mode == 2) {
-      v.x += z.x;
-      v.y += z.y;
-    }
-    return v;
-  };
 #pragma unroll
   for (int a = 0; a < AT; ++a)
 #pragma unroll
@@ -560,73 +510,36 @@ __device__ __forceinline__ void epi_tile(const v4f16 (&cr)[AT][BT], const v4f16 
       __builtin_amdgcn_sched_barrier(0);
       const int col = col_base + b * 16 + (lane & 15);
       const int row0 = row_base + a * 16 + 4 * (lane >> 4);
+      float2 v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = make_float2(cr[a][b][r], ci[a][b][r]);
       if (e.vec4 && col < N && row0 + 4 <= M) {
         // the lane's four consecutive rows of one column: 16-byte accesses
-        float2 v[4], y[4], z[4], q[4];
-        float kr[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) y[r] = z[r] = q[r] = zero2;
-        if (e.mode == 1) {
-          const float4 k4 = *reinterpret_cast<const float4*>(kin + row0);
-          kr[0] = k4.x;
-          kr[1] = k4.y;
-          kr[2] = k4.z;
-          kr[3] = k4.w;
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const float4 yy = reinterpret_cast<const float4*>(Y + (long)col * e.ldy + row0)[h];
-            y[2 * h] = make_float2(yy.x, yy.y);
-            y[2 * h + 1] = make_float2(yy.z, yy.w);
-            if (Yp) {
-              const float4 pp = reinterpret_cast<const float4*>(Yp + (long)col * e.ldp + row0)[h];
-              q[2 * h] = make_float2(pp.x, pp.y);
-              q[2 * h + 1] = make_float2(pp.z, pp.w);
-            }
-          }
-        }
-        if (e.mode >= 1) {
+        if (e.mode == 2) {
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             const float4 zz = reinterpret_cast<const float4*>(Zl + (long)col * e.ldz + row0)[h];
-            z[2 * h] = make_float2(zz.x, zz.y);
-            z[2 * h + 1] = make_float2(zz.z, zz.w);
+            v[2 * h].x += zz.x;
+            v[2 * h].y += zz.y;
+            v[2 * h + 1].x += zz.z;
+            v[2 * h + 1].y += zz.w;
           }
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = update(make_float2(cr[a][b][r], ci[a][b][r]), kr[r], y[r], z[r], q[r]);
         float4* oq = reinterpret_cast<float4*>(out + (long)col * ldo + row0);
         oq[0] = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
         oq[1] = make_float4(v[2].x, v[2].y, v[3].x, v[3].y);
-        if (e.ph) {
-          unsigned int wh[4], wl[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const Split2 sr = split(v[r].x), si = split(v[r].y);
-            wh[r] = pack(sr.h, si.h);
-            wl[r] = pack(sr.l, si.l);
-          }
-          const long o = (long)col * e.ldpl + row0;
-          *reinterpret_cast<uint4*>(static_cast<unsigned int*>(e.ph) + o) = uint4{wh[0], wh[1], wh[2], wh[3]};
-          *reinterpret_cast<uint4*>(static_cast<unsigned int*>(e.pl) + o) = uint4{wl[0], wl[1], wl[2], wl[3]};
-        }
         continue;
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = row0 + r;
         if (row < M && col < N) {
-          const bool m1 = e.mode == 1;
-          const float2 y = m1 ? Y[(long)col * e.ldy + row] : zero2;
-          const float2 z = e.mode >= 1 ? Zl[(long)col * e.ldz + row] : zero2;
-          const float2 q = m1 && Yp ? Yp[(long)col * e.ldp + row] : zero2;
-          const float2 v = update(make_float2(cr[a][b][r], ci[a][b][r]), m1 ? kin[row] : 0.f, y, z, q);
-          out[(long)col * ldo + row] = v;
-          if (e.ph) {
-            const Split2 sr = split(v.x), si = split(v.y);
-            const long o = (long)col * e.ldpl + row;
-            static_cast<unsigned int*>(e.ph)[o] = pack(sr.h, si.h);
-            static_cast<unsigned int*>(e.pl)[o] = pack(sr.l, si.l);
+          if (e.mode == 2) {
+            const float2 z = Zl[(long)col * e.ldz + row];
+            v[r].x += z.x;
+            v[r].y += z.y;
           }
+          out[(long)col * ldo + row] = v[r];
         }
       }
     }
@@ -751,22 +664,6 @@ constexpr int pApitch = 260;                       // words per (plane, k) row o
 constexpr int pAbytes = 2 * hBK * pApitch * 4;     // 33,280 B
 constexpr int pBbytes = 2 * pTN * hBK * 4;         // 16,384 B
 constexpr int pStage = pAbytes + pBbytes;
-
-__device__ __forceinline__ void dma16(const unsigned int* g, void* l) {
-  __builtin_amdgcn_global_load_lds(g, l, 16, 0, 0);
-}
-// s_waitcnt vmcnt(N) alone (expcnt and lgkmcnt left at their maxima)
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }  // lgkmcnt(0)
-
-// Address of the 16 bytes a lane loads: a wave-uniform base plus a per-lane 32-bit byte offset.
-__device__ __forceinline__ const unsigned int* at_off(const unsigned int* base, unsigned int byte_off) {
-  return reinterpret_cast<const unsigned int*>(reinterpret_cast<const unsigned char*>(base) + byte_off);
-}
 
 // K-contiguous tile: NC columns x 16 k, hi and lo planes, 2 NC / 16 loads of 1 KB (16 columns
 // each), this wave issuing those with index wave, wave + NW, ...  (the B tile, and the A tile of
@@ -968,7 +865,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 // herm > 0: the first herm columns of B are A itself (a Gram matrix A^H A in them); tiles of those
 // columns that lie wholly below the diagonal are not computed (their partials are left as they
 // are: the caller takes that block from its upper triangle).
-template <int NTERM>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_cn_pipe(
     const unsigned int* __restrict__ Ah, const unsigned int* __restrict__ Al, long lda,
     const unsigned int* __restrict__ Bh, const unsigned int* __restrict__ Bl, long ldb, int M, int N, int K,
@@ -1018,7 +914,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       if (it + 2 < ntiles) issue(it + 2);
       TileFrags<AT, true> f;
       f.read(smem + (it % pST) * SB, ra0, cb0, lane);
-      f.template mfma<NTERM>(cr, ci);
+      f.template mfma<4>(cr, ci);
     }
 #pragma unroll
     for (int a = 0; a < AT; ++a)
@@ -1085,40 +981,6 @@ hipError_t launch_split_planes(const float2* X, long ldx, int rows, int cols, un
   return hipGetLastError();
 }
 
-// Sum of the split-K partials, scaled per row by dscale[i % dper], rounded to fp32 and stored as the
-// nn B operand's planes: words (re, -im) of bf16(x) and of bf16(x - hi), k = row contiguous.
-__global__ void k_reduce_planes(const double2* __restrict__ part, int nsplit, int M, int N,
-                                const double* __restrict__ dscale, int dper, unsigned int* __restrict__ H,
-                                unsigned int* __restrict__ L, long ldp) {
-  PW_GRID_STRIDE(idx, (long)M * N) {
-    const int j = (int)(idx / M), i = (int)(idx - (long)j * M);
-    double2 s = part[idx];
-    for (int p = 1; p < nsplit; ++p) {
-      const double2 v = part[(long)p * M * N + idx];
-      s.x += v.x;
-      s.y += v.y;
-    }
-    if (dscale) {
-      const double d = dscale[i % dper];
-      s.x *= d;
-      s.y *= d;
-    }
-    const float re = (float)s.x, im = (float)s.y;
-    const Split2 sr = split(re), si = split(-im);
-    H[(long)j * ldp + i] = pack(sr.h, si.h);
-    L[(long)j * ldp + i] = pack(sr.l, si.l);
-  }
-}
-
-hipError_t launch_reduce_planes(const double2* part, int nsplit, int M, int N, const double* dscale, int dper,
-                                unsigned int* H, unsigned int* L, long ldp, hipStream_t s) {
-  const long n = (long)M * N;
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reduce_planes, dim3(stride_blocks(n)), dim3(256), 0, s, part, nsplit, M, N, dscale,
-                     dper > 0 ? dper : 1, H, L, ldp);
-  return hipGetLastError();
-}
-
 // n x n FP64 coefficients (columns optionally scaled by sc * lam[j]) as the nn B planes: rounded to
 // fp32, then words (re, -im) of bf16(x) and bf16(x - hi).
 __global__ void k_coef_planes(const double2* __restrict__ C, long ldc, int n, const double* __restrict__ lam,
@@ -1143,13 +1005,11 @@ hipError_t launch_coef_planes(const double2* C, long ldc, int n, const double* l
 }
 
 // Whether every array of the nn epilogue allows 16-byte accesses of a lane's four rows (row0 a
-// multiple of 4): 16-byte aligned bases, even complex leading dimensions, planes' a multiple of 4.
+// multiple of 4): 16-byte aligned bases, even complex leading dimensions.
 static EpiH epi_vec4(const EpiH& e, const void* out, long ldo) {
   auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   bool ok = al(out) && ldo % 2 == 0;
-  if (e.mode >= 1) ok = ok && al(e.Zl) && e.ldz % 2 == 0;
-  if (e.mode == 1) ok = ok && al(e.kin) && al(e.Y) && e.ldy % 2 == 0 && (!e.Yp || (al(e.Yp) && e.ldp % 2 == 0));
-  if (e.ph) ok = ok && al(e.ph) && al(e.pl) && e.ldpl % 4 == 0;
+  if (e.mode == 2) ok = ok && al(e.Zl) && e.ldz % 2 == 0;
   EpiH r = e;
   r.vec4 = ok ? 1 : 0;
   return r;
@@ -1195,11 +1055,10 @@ hipError_t launch_gemm_cn_bf16x3(const float2* A, long lda, const float2* B, lon
   return hipGetLastError();
 }
 
-// The projection with pre-split planes uses a 256-row tile with 8 waves when M is large: the block
-// is then re-read by half as many workgroups.  (The nonlocal product, whose K is short, keeps two
-// 128 x 128 workgroups per CU, which overlap one's epilogue with the other's MFMAs.)
+// The Gram product with pre-split planes uses a 256-row tile with 8 waves when M is large: the block
+// is then re-read by half as many workgroups.
 constexpr int hWM = 256, hWT = 512;
-// wave tile rows of the nonlocal product on planes
+// wave tile rows of the rotation on planes
 constexpr int hNnWR = 128;
 static bool planes_wide(int M) { return M >= 512; }
 
@@ -1218,19 +1077,14 @@ static bool use_pipe(const void* a, const void* a2, long lda, const void* b, con
 
 hipError_t launch_gemm_cn_bf16x3_planes(const unsigned int* Ahi, const unsigned int* Alo, long lda,
                                         const unsigned int* Bhi, const unsigned int* Blo, long ldb, int M, int N, int K,
-                                        int nsplit, double2* part, hipStream_t s, int nterm, int herm_cols) {
+                                        int nsplit, double2* part, hipStream_t s, int herm_cols) {
   if (M <= 0 || N <= 0) return hipSuccess;
   const int kchunk = cn_chunk(K, nsplit);
   const long kpad = (long)ceil_div(K, hBK) * hBK;  // the last tile reads the zero words up to here
   if (kpad <= lda && kpad <= ldb && use_pipe(Ahi, Alo, lda, Bhi, Blo, ldb, M, N)) {
     const int tm = ceil_div(M, pTM), tn = ceil_div(N, pTN);
-    dim3 grid(tm * tn * nsplit);
-    if (nterm == 4)
-      hipLaunchKernelGGL(k_gemm_cn_pipe<4>, grid, dim3(512), 0, s, Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, kchunk, tm,
-                         tn, part, herm_cols);
-    else
-      hipLaunchKernelGGL(k_gemm_cn_pipe<3>, grid, dim3(512), 0, s, Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, kchunk, tm,
-                         tn, part, herm_cols);
+    hipLaunchKernelGGL(k_gemm_cn_pipe, dim3(tm * tn * nsplit), dim3(512), 0, s, Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K,
+                       kchunk, tm, tn, part, herm_cols);
     return hipGetLastError();
   }
   const bool vec = ok_planes(Ahi, Alo, lda) && ok_planes(Bhi, Blo, ldb);
@@ -1239,25 +1093,15 @@ hipError_t launch_gemm_cn_bf16x3_planes(const unsigned int* Ahi, const unsigned 
   const void* b0 = Bhi;
   const void* b1 = Blo;
   const void* nul = nullptr;
-#define PW_CNP(NTERM, V, TM, NT)                                                                                  \
-  hipLaunchKernelGGL((k_gemm_cn_bf16x3<NTERM, CnAPlanes<TM, V, NT>, CnBPlanes<hTN, V, NT>, TM, NT>), grid, dim3(NT), \
-                     0, s, a0, a1, lda, b0, b1, ldb, nul, 0L, N, M, N, K, kchunk, tm, tn, part)
+#define PW_CNP(V, TM, NT)                                                                                         \
+  hipLaunchKernelGGL((k_gemm_cn_bf16x3<4, CnAPlanes<TM, V, NT>, CnBPlanes<hTN, V, NT>, TM, NT>), grid, dim3(NT), 0, s, \
+                     a0, a1, lda, b0, b1, ldb, nul, 0L, N, M, N, K, kchunk, tm, tn, part)
+  const int tm = ceil_div(M, planes_wide(M) ? hWM : hTM), tn = ceil_div(N, hTN);
+  const dim3 grid(tm * tn * nsplit);
   if (planes_wide(M)) {
-    const int tm = ceil_div(M, hWM), tn = ceil_div(N, hTN);
-    dim3 grid(tm * tn * nsplit);
-    if (nterm == 4) {
-      if (vec) PW_CNP(4, true, hWM, hWT); else PW_CNP(4, false, hWM, hWT);
-    } else {
-      if (vec) PW_CNP(3, true, hWM, hWT); else PW_CNP(3, false, hWM, hWT);
-    }
-    return hipGetLastError();
-  }
-  const int tm = ceil_div(M, hTM), tn = ceil_div(N, hTN);
-  dim3 grid(tm * tn * nsplit);
-  if (nterm == 4) {
-    if (vec) PW_CNP(4, true, hTM, 256); else PW_CNP(4, false, hTM, 256);
+    if (vec) PW_CNP(true, hWM, hWT); else PW_CNP(false, hWM, hWT);
   } else {
-    if (vec) PW_CNP(3, true, hTM, 256); else PW_CNP(3, false, hTM, 256);
+    if (vec) PW_CNP(true, hTM, 256); else PW_CNP(false, hTM, 256);
   }
 #undef PW_CNP
   return hipGetLastError();

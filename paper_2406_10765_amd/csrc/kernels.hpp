@@ -114,12 +114,16 @@ struct EpiH {
   long ldz;
   const void* Yp;  // may be null when beta == 0
   long ldp;
-  // split-precision nn only, optional: bf16 hi/lo planes of out (one (re, im) word per entry,
-  // leading dimension ldpl), for the next projector product
+  // split-precision products on pairs only, optional: pair planes of out for the next projection
+  // (leading dimension ldpl, columns as launch_pair_planes writes them), and bf16 hi/lo planes of
+  // out (one (re, im) word per entry, leading dimension ldcl) for the Gram product and the rotation
   void* ph;
   void* pl;
   long ldpl;
-  // split-precision nn: set by the launcher when every epilogue array allows 16-byte accesses
+  void* ch;
+  void* cl;
+  long ldcl;
+  // split-precision products: set by the launcher when every epilogue array allows 16-byte accesses
   int vec4;
 };
 
@@ -154,14 +158,14 @@ hipError_t launch_gemm_nn(const cplx<T>* A, long lda, const cplx<T>* B, long ldb
 
 // Split-precision (bf16x3) forms of the two GEMM shapes, fp32 data.
 int gemm_cn_bf16_tiles(int M, int N);
-// tiles of the projection product with pre-split planes (launch_gemm_cn_bf16x3_planes)
+// tiles of the Gram product with pre-split planes (launch_gemm_cn_bf16x3_planes)
 int gemm_cn_bf16_planes_tiles(int M, int N);
 // nterm = 3: hi*hi' + hi*lo' + lo*hi'; nterm = 4 adds lo*lo'.
 hipError_t launch_gemm_cn_bf16x3(const float2* A, long lda, const float2* B, long ldb, const float2* B2, long ldb2,
                                  int ncol1, int M, int N, int K, int nsplit, double2* part, int nterm, hipStream_t s);
 hipError_t launch_gemm_nn_bf16x3(const float2* A, long lda, const float2* B, long ldb, int M, int N, int K,
                                  float2* out, long ldo, const EpiH& e, hipStream_t s);
-// The same products with pre-split bf16 planes (launch_beta_planes layout): cn with A and B given
+// The same products with pre-split bf16 planes (one (re, im) word per entry): cn with A and B given
 // as planes of M and N columns of length K, nn with A = planes of K columns of length M.  Leading
 // dimensions of planes count 32-bit words.
 // herm_cols > 0: B's first herm_cols columns are A itself; the pipelined form may then skip the
@@ -169,17 +173,15 @@ hipError_t launch_gemm_nn_bf16x3(const float2* A, long lda, const float2* B, lon
 // the caller must take the block's lower triangle from its upper one (launch_mirror_upper).
 hipError_t launch_gemm_cn_bf16x3_planes(const unsigned int* Ahi, const unsigned int* Alo, long lda,
                                         const unsigned int* Bhi, const unsigned int* Blo, long ldb, int M, int N, int K,
-                                        int nsplit, double2* part, hipStream_t s, int nterm = 3, int herm_cols = 0);
+                                        int nsplit, double2* part, hipStream_t s, int herm_cols = 0);
 // The cn form on planes reads the words of each column from K up to the next multiple of 16 when
-// both leading dimensions reach that far: those words must be zero.  The projector planes are
-// written with zeros there; the block planes are cleared once (at set-up, or by
-// launch_zero_plane_rows for planes in other memory) and never written there afterwards.
+// both leading dimensions reach that far: those words must be zero (launch_zero_plane_rows).
 hipError_t launch_zero_plane_rows(unsigned int* H, unsigned int* L, long ld, int r0, int cols, hipStream_t s);
 // hi/lo planes (one (re, im) word per entry, leading dimension ldp) of rows x cols fp32 complex.
 hipError_t launch_split_planes(const float2* X, long ldx, int rows, int cols, unsigned int* H, unsigned int* L,
                                long ldp, hipStream_t s);
 // nn with A = planes of K columns of length M and B = planes of N columns of length K holding
-// (re, -im) words (launch_reduce_planes).
+// (re, -im) words (launch_coef_planes).
 hipError_t launch_gemm_nn_bf16x3_planes(const unsigned int* Ahi, const unsigned int* Alo, long lda,
                                         const unsigned int* Bhi, const unsigned int* Blo, long ldb, int M, int N, int K,
                                         float2* out, long ldo, const EpiH& e, hipStream_t s);
@@ -190,11 +192,27 @@ hipError_t launch_gemm_nn_bf16x3_bplanes(const float2* A, long lda, const unsign
 // n x n FP64 matrix C (ldc), column j scaled by sc * lam[j] when lam is given, as nn B planes (ldp).
 hipError_t launch_coef_planes(const double2* C, long ldc, int n, const double* lam, double sc, unsigned int* H,
                               unsigned int* L, long ldp, hipStream_t s);
-// launch_reduce_parts into the nn B planes: the M x N sum over nsplit partials, row i scaled by
-// dscale[i % dper], rounded to fp32 and split into words (re, -im) of hi and lo (leading dimension
-// ldp, a multiple of 4 words).
-hipError_t launch_reduce_planes(const double2* part, int nsplit, int M, int N, const double* dscale, int dper,
-                                unsigned int* H, unsigned int* L, long ldp, hipStream_t s);
+// Projector products on pairs (G, -G) with bf16 planes (gemm_pairs.hip): half of the sphere's rows
+// (nh = (npw + 1) / 2), leading dimension ldh words, zero from nh to ldh, ldh a multiple of 16.
+// Pair planes of nb fp32 columns: columns 0 .. nb - 1 hold F, nb .. 2 nb - 1 hold G.
+hipError_t launch_pair_planes(const float2* X, long ldx, int npw, int nb, unsigned int* H, unsigned int* L, long ldp,
+                              hipStream_t s);
+// K splits of the projection of nb bands on M projectors over ktiles tiles of 16 half rows, at most cap.
+int pairs_proj_splits(int M, int nb, int ktiles, long cap);
+// part[s][band][projector] = (p_f, p_g) over the s-th K chunk; A = M projector columns, B = pair planes.
+hipError_t launch_pairs_proj(const unsigned int* Ah, const unsigned int* Al, long lda, const unsigned int* Bh,
+                             const unsigned int* Bl, long ldb, int M, int nb, int ktiles, int nsplit, double2* part,
+                             hipStream_t s);
+// q = d p summed over the splits as the nonlocal product's B planes: words of two consecutive
+// projectors, 2 nb columns (f, then g) of ldp words, zero past the M projectors.  d: 4 values, by
+// projector index modulo 4.
+hipError_t launch_pair_reduce(const double2* part, int nsplit, int M, int nb, const double* dscale, unsigned int* H,
+                              unsigned int* L, long ldp, hipStream_t s);
+// out = EpiH(mode 1) with V_NL psi from the projector planes (32 ktiles columns) and the planes of q
+// (16 ktiles words per column).
+hipError_t launch_pairs_nl(const unsigned int* Ah, const unsigned int* Al, long lda, const unsigned int* Bh,
+                           const unsigned int* Bl, long ldb, int npw, int nb, int ktiles, float2* out, long ldo,
+                           const EpiH& e, hipStream_t s);
 
 // --------------------------------------------------------------- misc ------
 // LOBPCG pieces: per-column Rayleigh quotients theta_j = Re(x_j^H w_j) / |x_j|^2 (FP64), and the
@@ -247,9 +265,10 @@ hipError_t launch_vg_sphere(const int* miller, int npw, const double* frac, cons
 template <typename T>
 hipError_t launch_beta_table(const int* miller, int npw, const double* frac, int natoms, const double* L,
                              double sigma, int form, cplx<T>* beta, long ld, hipStream_t s);
-// Projector table as bf16 hi/lo planes (one 32-bit (re, im) word per entry, column-major, leading
-// dimension ld; rows npw..ld-1 zero), for the split-precision projector GEMMs.
-hipError_t launch_beta_planes(const int* miller, int npw, const double* frac, int natoms, const double* L,
+// Projector table on half the sphere as bf16 hi/lo planes (one 32-bit (re, im) word per entry,
+// column-major, leading dimension ld; rows nh..ld-1 and columns 4 natoms..cols-1 zero), for the
+// projector products on pairs.
+hipError_t launch_beta_planes(const int* miller, int nh, const double* frac, int natoms, int cols, const double* L,
                               double sigma, int form, unsigned int* hi, unsigned int* lo, long ld, hipStream_t s);
 template <typename T>
 hipError_t launch_convert_c64_to(const double2* in, long ldi, cplx<T>* out, long ldo, int rows, int cols,

@@ -78,6 +78,8 @@ __global__ void k_vg_sphere(const int* __restrict__ miller, int npw, const doubl
 // beta[g, 4a+m] = (c/sqrt(Omega)) e^{-sigma^2 |G|^2/2} Y_m(G) e^{-i G.tau_a},
 // c = sqrt(32 pi^{5/2} sigma^3); Y_0 = 1/(2 sqrt(pi)), Y_{1x,y,z} = sqrt(3/(4 pi)) G_{x,y,z}/|G| (0 at G=0).
 // form PW_PROJ_LOCALIZED: Y_{1m} = -i sigma G_m / sqrt(2 pi) (the transform of a Gaussian times r_m).
+// The l = 1 columns of the other form are stored times i: V_NL does not see the factor, and every column
+// then is the transform of a real function, beta(-G) = conj beta(G).
 __device__ __forceinline__ void beta_values(const int* __restrict__ miller, int g, const double* __restrict__ frac,
                                             int a, double L0, double L1, double L2, double sigma, int form,
                                             double2 out[4]) {
@@ -104,10 +106,11 @@ __device__ __forceinline__ void beta_values(const int* __restrict__ miller, int 
     return;
   }
   const double ym[4] = {y0, gx * inv, gy * inv, gz * inv};
+  out[0] = make_double2(radial * y0 * e.x, radial * y0 * e.y);
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
+  for (int m = 1; m < 4; ++m) {
     const double sc = radial * ym[m];
-    out[m] = make_double2(sc * e.x, sc * e.y);
+    out[m] = make_double2(-sc * e.y, sc * e.x);  // i (e.x + i e.y)
   }
 }
 
@@ -123,16 +126,16 @@ __global__ void k_beta_table(const int* __restrict__ miller, int npw, const doub
   for (int m = 0; m < 4; ++m) beta[(long)(4 * a + m) * ld + g] = mk<T>((T)v[m].x, (T)v[m].y);
 }
 
-// The fp32 table stored as two bf16 planes: word (re, im) of hi = bf16(x) and of lo = bf16(x - hi),
-// x the fp32 value; rows npw..ld-1 of every column are zero.
-__global__ void k_beta_planes(const int* __restrict__ miller, int npw, const double* __restrict__ frac, double L0,
-                              double L1, double L2, double sigma, int form, unsigned int* __restrict__ hi,
+// The fp32 table of half the sphere stored as two bf16 planes: word (re, im) of hi = bf16(x) and of
+// lo = bf16(x - hi), x the fp32 value; rows nh..ld-1 and the columns past the last atom's are zero.
+__global__ void k_beta_planes(const int* __restrict__ miller, int nh, const double* __restrict__ frac, int natoms,
+                              double L0, double L1, double L2, double sigma, int form, unsigned int* __restrict__ hi,
                               unsigned int* __restrict__ lo, long ld) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   const int a = blockIdx.y;
   if (g >= ld) return;
   double2 v[4] = {};
-  if (g < npw) beta_values(miller, g, frac, a, L0, L1, L2, sigma, form, v);
+  if (g < nh && a < natoms) beta_values(miller, g, frac, a, L0, L1, L2, sigma, form, v);
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
     const Split2 re = split((float)v[m].x), im = split((float)v[m].y);
@@ -402,11 +405,11 @@ hipError_t launch_beta_table(const int* miller, int npw, const double* frac, int
   return hipGetLastError();
 }
 
-hipError_t launch_beta_planes(const int* miller, int npw, const double* frac, int natoms, const double* L,
+hipError_t launch_beta_planes(const int* miller, int nh, const double* frac, int natoms, int cols, const double* L,
                               double sigma, int form, unsigned int* hi, unsigned int* lo, long ld, hipStream_t s) {
   if (natoms <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_beta_planes, dim3(ceil_div(ld, 256), natoms), dim3(256), 0, s, miller, npw, frac, L[0], L[1],
-                     L[2], sigma, form, hi, lo, ld);
+  hipLaunchKernelGGL(k_beta_planes, dim3(ceil_div(ld, 256), cols / 4), dim3(256), 0, s, miller, nh, frac, natoms, L[0],
+                     L[1], L[2], sigma, form, hi, lo, ld);
   return hipGetLastError();
 }
 

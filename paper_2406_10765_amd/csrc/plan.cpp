@@ -265,6 +265,10 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   if (P.nbands > P.npw) { *err = "nbands exceeds the number of plane waves"; return PW_EINVAL; }
   P.nproj = have_proj ? 4 * P.natoms : 0;
   P.ldw = (P.npw + 15) / 16 * 16;
+  P.nh = (P.npw + 1) / 2;
+  P.ldh = (P.nh + 15) / 16 * 16;
+  P.ldy = std::max(P.ldw, 2 * P.ldh);
+  P.nproj32 = (P.nproj + 31) / 32 * 32;
 
   // --- grid ----------------------------------------------------------------------
   const bool user_grid = d->fft_n[0] || d->fft_n[1] || d->fft_n[2];
@@ -340,8 +344,8 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   if (fb > P.nbb) fb = P.nbb;
   P.fft_batch = fb;
   // K splits: enough workgroups to fill the chip several times over (the pipelined split-bf16
-  // forms run one workgroup per CU, and more, shorter chunks balance their tail: measured at
-  // Si512, 57 splits of the projection and 49 of the Gram take 1.0 and 2 ms less than 29 and 25)
+  // Gram product runs one workgroup per CU, and more, shorter chunks balance its tail: measured at
+  // Si512, 49 splits take 2 ms less than 25); the projection on pairs has its own rule
   auto pick_split = [](int tiles, int K, int target = 2048) {
     int s = (target + tiles - 1) / tiles;
     int kmax = K / 512;
@@ -352,7 +356,7 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   };
   const bool f64 = P.prec == PW_FP64;
   const bool bkb = (P.flags & PW_FLAG_BF16_KB) != 0, bgr = (P.flags & PW_FLAG_BF16_GRAM) != 0;
-  P.nsplit_proj = P.nproj ? (bkb ? pick_split(gemm_cn_bf16_planes_tiles(P.nproj, P.nbb), P.npw, 4096)
+  P.nsplit_proj = P.nproj ? (bkb ? pairs_proj_splits(P.nproj, P.nbb, (int)(P.ldh / 16), 64)
                                   : pick_split(gemm_cn_tiles(P.nproj, P.nbb, f64), P.npw))
                           : 1;
   // planes of Y and W for the Gram product: written by the nonlocal product's epilogue with
@@ -404,7 +408,7 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   for (int gi = 0; gi < P.npw; ++gi)
     for (int i = 0; i < 3; ++i) P.hmax[i] = std::max(P.hmax[i], std::abs(P.miller[3 * gi + i]));
   P.bwidth = (2 * P.hmax[0] + 1) + (2 * P.hmax[1] + 1) + (2 * P.hmax[2] + 1);
-  L.beta = take(otf || P.rspace ? 0 : cb * P.ldw * P.nproj);
+  L.beta = take(otf || P.rspace ? 0 : bkb ? cb * P.ldh * P.nproj32 : cb * P.ldw * P.nproj);
   L.brad = take(otf ? sizeof(double) * 4 * P.npw : 0);
   L.bph = take(otf ? 16 * (size_t)P.natoms * P.bwidth : 0);
   const bool blocked = P.nbb < P.nbands;
@@ -414,9 +418,9 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   L.wf = take(blocked ? cb * P.ldw * nb : 0);
   L.sb = take(per_band_sb * P.fft_batch);
   L.g1 = take(per_band_g1 * P.fft_batch);
-  L.pt = take(cb * std::max(1, P.nproj) * P.nbb);
+  L.pt = take(cb * std::max(1, bkb ? P.nproj32 : P.nproj) * P.nbb);
   // bf16 hi/lo planes of the block entering the projector product (split-precision projectors)
-  L.yp = take(8 * (size_t)P.ldw * P.yp_cols);
+  L.yp = take(8 * (size_t)P.ldy * P.yp_cols);
   const size_t parts = std::max({(size_t)P.nsplit_proj * P.nproj * P.nbb, (size_t)P.nsplit_gram * nb * 2 * nb,
                                   (size_t)P.nsplit_lob * kb * 2 * kb});
   L.parts = take(16 * parts);

@@ -41,6 +41,11 @@ struct Plan {
   int n[3];
   int npw, nst, nproj;
   long ldw;  // internal leading dimension (npw rounded up to 16)
+  // half of the sphere, rows 0 .. nh - 1 (row npw - 1 - g is -G of row g; row nh - 1 is G = 0), and
+  // its leading dimension (a multiple of 16)
+  int nh;
+  long ldh;
+  int nproj32;  // projector columns of the split-precision table (nproj rounded up to 32)
   std::vector<int> miller;     // 3 * npw, stick order
   std::vector<Stick> sticks;   // nst
   std::vector<int> colstart;   // n1a + 1: first stick of each active x column
@@ -51,9 +56,12 @@ struct Plan {
   int nbb;                     // bands per filter block (== nbands: unblocked step)
   int nsplit_proj, nsplit_gram;
   int nsplit_lob;  // K splits of the LOBPCG basis Gram product (PW_FLAG_LOBPCG), else 0
-  // bf16 plane columns held per plane: nbb, or 2 nbb when the unblocked step also keeps the
-  // planes of H Y beside those of Y (split-precision projectors and Gram product)
+  // bf16 plane columns held per plane, of ldy words: nbb (the pair planes of the block entering the
+  // projection, 2 nb columns of ldh words), or 2 nbb when the unblocked step also keeps the planes of
+  // Y and H Y for the Gram product: Y's in the first nb columns, and in the nb columns after them the
+  // pair planes until the projection of H Y has read them, then the planes of H Y
   int yp_cols;
+  long ldy;  // max(ldw, 2 ldh)
   int hmax[3];                 // max |n_d| over the sphere (projector generator tables)
   int bwidth;                  // per-atom axis-factor table length
   int proj_form;               // PW_PROJ_GSPACE or PW_PROJ_LOCALIZED

@@ -1,0 +1,84 @@
+"""Split-bf16 projector products on pairs (G, -G): every tile shape of the projection and the
+nonlocal product with remainders in bands, plane waves and projectors, the scalar epilogue of
+unaligned blocks, and the planes buffer shared by blocks of different widths.
+
+Tolerance of H X: 5e-5 of max|HX|, as for the split-bf16 products elsewhere (each product's split
+residual is at most 2^-16, with random signs).  The reference is the FP64 oracle on the same
+FP32-rounded input."""
+import numpy as np
+import pytest
+
+from oracle import pw_oracle as O
+from paper_2406_10765_amd import pw, synth
+
+pytestmark = pytest.mark.gpu
+
+TOL = 5e-5
+
+
+def cell_with_atoms(n, L=(9.0, 10.26, 11.5), ecut=9.0, nbands=40):
+    rng = np.random.Generator(np.random.PCG64(7))
+    return synth.Cell(L=L, tau=rng.uniform(0, 1, (n, 3)) * np.array(L), ecut=ecut, nbands=nbands)
+
+
+def check(cell, nbs, ld_extra=None, cols=None):
+    m = O.model_from_cell(cell)
+    h = pw.Handle(cell, pw.PW_MIXED, flags=pw.PW_FLAG_BF16_ALL)
+    perm = pw.permutation_to(m.miller, h.gvectors())
+    for nb in nbs:
+        X = synth.random_block(h.npw, nb, 11 + nb).astype(np.complex64)
+        ld = None if ld_extra is None else h.npw + ld_extra
+        Xd = h.to_device(X, ld)
+        got = h.to_host(h.apply_h(Xd))
+        use = range(nb) if cols is None else sorted({0, nb // 2, nb - 1})
+        inv = np.argsort(perm)
+        ref = O.apply_h(m, X[inv][:, list(use)].astype(np.complex128))[perm]
+        err = float(np.abs(got[:, list(use)] - ref).max() / np.abs(ref).max())
+        print("pairs npw", h.npw, "nproj", h.info.nproj, "nb", nb, "ld_extra", ld_extra, "err", err, flush=True)
+        assert err <= TOL
+    h.close()
+
+
+@pytest.mark.parametrize("natoms", [0, 1, 3, 8, 9])
+def test_projector_and_row_remainders(natoms):
+    check(cell_with_atoms(natoms), (1, 16, 17, 33, 40))
+
+
+@pytest.mark.parametrize("ecut", [6.0, 8.0])
+def test_projection_tile_shapes(ecut):
+    # 256 projectors: the narrow shape (<= 16 bands), 64 x 32 (17 .. 47) and 128 x 64 (from 48)
+    check(synth.silicon_cell((2, 2, 2), ecut, nbands=129, disp_seed=5), (1, 15, 16, 17, 47, 48, 63, 65, 129), cols=3)
+
+
+def test_largest_tiles_with_remainders():
+    # 864 projectors x 153 bands: 256 x 128 projection tiles; 131 bands x 257 row tiles: 128 x 128 nonlocal tiles
+    check(synth.silicon_cell((3, 3, 3), 6.0, nbands=153, disp_seed=5), (152, 153), cols=3)
+    check(synth.silicon_cell((3, 3, 4), 11.5, nbands=131, disp_seed=6), (129, 131), cols=3)
+
+
+@pytest.mark.parametrize("ld_extra", [0, 1, 2, 3])
+def test_block_alignments(ld_extra):
+    check(synth.silicon_cell((1, 1, 2), 9.0, nbands=19, disp_seed=5), (3, 19), ld_extra=ld_extra)
+
+
+@pytest.mark.parametrize("degree", [0, 1, 2, 5])
+def test_steps_of_different_widths_share_the_planes(degree):
+    """A step on a handle that has just processed a wider or narrower block gives bitwise what a new handle gives:
+    nothing of the earlier block's planes is read."""
+    cell = synth.silicon_cell((1, 1, 2), 10.0, nbands=40, disp_seed=3)
+    flags = pw.PW_FLAG_BF16_ALL
+
+    def step(h, nb):
+        X = h.random_block(nb, 9)
+        e, r, _ = h.eig_step(X, degree, -0.8, 1.0, 17.0)
+        return e, r, h.to_host(X)
+
+    h = pw.Handle(cell, pw.PW_MIXED, flags=flags)
+    for nb in (40, 23, 36, 40):
+        got = step(h, nb)
+        new = pw.Handle(cell, pw.PW_MIXED, flags=flags)
+        ref = step(new, nb)
+        new.close()
+        for a, b in zip(got, ref):
+            assert np.array_equal(a, b), (degree, nb)
+    h.close()
