@@ -239,6 +239,7 @@ struct Engine {
     bg.o3 = bg.o2 + 2 * P.hmax[1] + 1;
     bg.w = P.bwidth;
     bg.npw = P.npw;
+    bg.nh = P.nh;
     bg.natoms = P.natoms;
     return bg;
   }
@@ -497,14 +498,12 @@ struct Engine {
         }
       }
       if (!beta_planes()) {
-        if (beta_otf())
-          PW_TIMED(PW_PH_PROJ, launch_gemm_cn_beta<T>(beta_gen(), Y, ldy, nb, P.nsplit_proj, parts, h->stream));
-        else
-          PW_TIMED(PW_PH_PROJ,
-                   cn(false, beta(), P.ldw, Y, ldy, nullptr, 0, nb, P.nproj, nb, P.npw, P.nsplit_proj, parts));
-        PW_TIMED(PW_PH_PROJ_REDUCE, launch_reduce_parts<T>(parts, P.nsplit_proj, P.nproj, nb,
-                                                           h->at<double>(P.lay.dscale), 4, nullptr, 0, PT, P.nproj,
-                                                           h->stream));
+        const BetaGen bg = beta_gen();
+        const PairsCn pc = pairs_cn_plan(P.nproj, nb, P.nh, sizeof(T) == 8, parts_cap(nb));
+        PW_TIMED(PW_PH_PROJ, launch_pairs_cn<T>(beta(), P.ldh, beta_otf() ? &bg : nullptr, Y, ldy, P.nproj, nb, P.npw,
+                                                pc, parts, h->stream));
+        PW_TIMED(PW_PH_PROJ_REDUCE, launch_reduce_parts<T>(parts, pc.splits, P.nproj, nb, h->at<double>(P.lay.dscale), 4,
+                                                           nullptr, 0, PT, P.nproj, h->stream));
       }
     }
     if (overlap) PW_HIP(hipStreamWaitEvent(h->stream, h->ev_join, 0));
@@ -551,11 +550,9 @@ struct Engine {
         return PW_OK;
       }
     }
-    if (beta_otf()) {
-      PW_TIMED(PW_PH_NL, launch_gemm_nn_beta<T>(beta_gen(), PT, P.nproj, nb, out, ldo, e, h->stream));
-      return PW_OK;
-    }
-    PW_TIMED(PW_PH_NL, nn(false, beta(), P.ldw, PT, P.nproj, P.npw, nb, P.nproj, out, ldo, e));
+    const BetaGen bg = beta_gen();
+    PW_TIMED(PW_PH_NL, launch_pairs_nn<T>(beta(), P.ldh, beta_otf() ? &bg : nullptr, PT, P.nproj, P.npw, nb, P.nproj,
+                                          out, ldo, e, h->stream));
     return PW_OK;
   }
 
@@ -1292,8 +1289,8 @@ struct Engine {
       PW_HIP(launch_beta_planes(h->at<int>(p.lay.miller), p.nh, h->at<double>(p.lay.frac), p.natoms, p.nproj32, p.L,
                                 p.beta_sigma, p.proj_form, beta_hi(), beta_lo(), p.ldh, st));
     else if (p.nproj && !p.rspace)
-      PW_HIP(launch_beta_table<T>(h->at<int>(p.lay.miller), p.npw, h->at<double>(p.lay.frac), p.natoms, p.L,
-                                  p.beta_sigma, p.proj_form, beta(), p.ldw, st));
+      PW_HIP(launch_beta_table<T>(h->at<int>(p.lay.miller), p.nh, h->at<double>(p.lay.frac), p.natoms, p.L,
+                                  p.beta_sigma, p.proj_form, beta(), p.ldh, st));
     if (p.rspace) {
       auto up = [&](size_t off, const void* src, size_t bytes) -> hipError_t {
         return bytes ? hipMemcpyAsync(h->at<char>(off), src, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
@@ -1570,14 +1567,14 @@ static int noalloc_layout(pw_handle* h, int nb) {
   const size_t g11 = P.fl.fused ? 0 : (size_t)g.n3 * g.n2 * g.n1a * cb;
   const bool planes = P.real_bytes == 4 && (P.flags & PW_FLAG_BF16_KB) && P.nproj > 0;
   const size_t npt = planes ? P.nproj32 : P.nproj;
-  // the projection on pairs takes fewer K splits where one column would not fit otherwise
+  // the projection takes fewer K splits where one column would not fit otherwise
   int ns = P.nsplit_proj;
   auto per_column = [&]() {
     return sb1 + g11 + (P.nproj ? 16 * (size_t)ns * P.nproj + cb * npt : 0) + (planes ? 8 * (size_t)P.ldy : 0);
   };
   const size_t slack = 5 * kArenaAlign;
   if (kScratchBytes <= slack) return 0;
-  if (planes && per_column() > kScratchBytes - slack) ns = 1;
+  if (per_column() > kScratchBytes - slack) ns = 1;
   long w = (long)((kScratchBytes - slack) / per_column());
   w = std::min<long>(w, std::min(nb, P.nbb));
   if (w < 1) return 0;

@@ -105,7 +105,7 @@ hipError_t launch_reduce_parts(const double2* part, int nsplit, int M, int N, co
 //   out = alpha * ((kin_i - c) Y + Zl + acc) - beta * Yp      (EPI_H)
 //   out = acc                                                  (EPI_STORE)
 struct EpiH {
-  int mode;  // 0 = store, 1 = H / Chebyshev update, 2 = out = acc + Zl
+  int mode;  // 0 = store, 1 = H / Chebyshev update (the products on pairs), 2 = out = acc + Zl
   double alpha, c, beta;
   const void* kin;  // T[M]
   const void* Y;
@@ -130,7 +130,8 @@ struct EpiH {
 // Generator of the projector matrix inside the GEMM loaders, for cells whose table would not
 // fit:  beta[g, 4a+m] = rad[4g+m] * ph_a(n1) ph_a(n2) ph_a(n3), where rad holds
 // (c/sqrt(Omega)) e^{-sigma^2|G|^2/2} Y_m(G) per plane wave and ph_a the per-atom factors
-// e^{-2 pi i n f_d(a)} of each axis d (f = fractional position), n from -h_d to h_d.
+// e^{-2 pi i n f_d(a)} of each axis d (f = fractional position), n from -h_d to h_d; the l = 1 columns
+// (m > 0) are generated times i, as the table stores them.
 struct BetaGen {
   const int* miller;    // 3 * npw
   const double* rad;    // 4 * npw
@@ -138,16 +139,21 @@ struct BetaGen {
   int h1, h2, h3;       // offsets of n = 0 in the three axis tables
   int o2, o3;           // start of the axis-2 and axis-3 tables within one atom's row
   int w;                // (2 h1 + 1) + (2 h2 + 1) + (2 h3 + 1)
-  int npw, natoms;
+  int npw, nh, natoms;  // nh = (npw + 1) / 2 half rows
 };
-// part[s] = beta^H B over K chunk s with beta generated on the fly (M = 4 natoms columns).
+// Projector products on pairs (G, -G) in the compute precision (gemm.hip): A = table of M (K) columns of the
+// nh = (npw + 1) / 2 half rows, or generated (bg).  part[s][band][projector] = (p_f, p_g).
+struct PairsCn {
+  int width, splits;  // bands per tile, K splits
+};
+PairsCn pairs_cn_plan(int M, int nb, int nh, bool fp64, long cap);  // at most cap splits
 template <typename T>
-hipError_t launch_gemm_cn_beta(const BetaGen& bg, const cplx<T>* B, long ldb, int N, int nsplit, double2* part,
-                               hipStream_t s);
-// out = epilogue(beta B) with beta generated on the fly (K = 4 natoms).
+hipError_t launch_pairs_cn(const cplx<T>* A, long lda, const BetaGen* bg, const cplx<T>* Y, long ldy, int M, int nb,
+                           int npw, const PairsCn& c, double2* part, hipStream_t s);
+// out = EpiH(mode 1) with V_NL psi = beta Q, Q: K x nb, entries (q_f, q_g).
 template <typename T>
-hipError_t launch_gemm_nn_beta(const BetaGen& bg, const cplx<T>* B, long ldb, int N, cplx<T>* out, long ldo,
-                               const EpiH& e, hipStream_t s);
+hipError_t launch_pairs_nn(const cplx<T>* A, long lda, const BetaGen* bg, const cplx<T>* Q, long ldq, int npw, int nb,
+                           int K, cplx<T>* out, long ldo, const EpiH& e, hipStream_t s);
 // Tables of BetaGen: rad (npw x 4) and the per-atom axis factors (natoms x w).
 hipError_t launch_beta_gen_tables(const BetaGen& bg, const double* frac, const double* L, double sigma,
                                   double* rad, double2* ph, hipStream_t s);
@@ -261,9 +267,9 @@ struct PotParams {
 hipError_t launch_vg_sphere(const int* miller, int npw, const double* frac, const int* mode_miller,
                             const double* mode_amp, const double* mode_phase, PotParams p, double2* vg,
                             hipStream_t s);
-// beta[g, 4a+m] table (column-major, ld)
+// beta[g, 4a+m] table of the nh half rows (column-major, ld)
 template <typename T>
-hipError_t launch_beta_table(const int* miller, int npw, const double* frac, int natoms, const double* L,
+hipError_t launch_beta_table(const int* miller, int nh, const double* frac, int natoms, const double* L,
                              double sigma, int form, cplx<T>* beta, long ld, hipStream_t s);
 // Projector table on half the sphere as bf16 hi/lo planes (one 32-bit (re, im) word per entry,
 // column-major, leading dimension ld; rows nh..ld-1 and columns 4 natoms..cols-1 zero), for the

@@ -115,11 +115,11 @@ __device__ __forceinline__ void beta_values(const int* __restrict__ miller, int 
 }
 
 template <typename T>
-__global__ void k_beta_table(const int* __restrict__ miller, int npw, const double* __restrict__ frac, double L0,
+__global__ void k_beta_table(const int* __restrict__ miller, int nh, const double* __restrict__ frac, double L0,
                              double L1, double L2, double sigma, int form, cplx<T>* __restrict__ beta, long ld) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   const int a = blockIdx.y;
-  if (g >= npw) return;
+  if (g >= nh) return;
   double2 v[4];
   beta_values(miller, g, frac, a, L0, L1, L2, sigma, form, v);
 #pragma unroll
@@ -397,10 +397,10 @@ hipError_t launch_vg_sphere(const int* miller, int npw, const double* frac, cons
 }
 
 template <typename T>
-hipError_t launch_beta_table(const int* miller, int npw, const double* frac, int natoms, const double* L,
+hipError_t launch_beta_table(const int* miller, int nh, const double* frac, int natoms, const double* L,
                              double sigma, int form, cplx<T>* beta, long ld, hipStream_t s) {
   if (natoms <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_beta_table<T>, dim3(ceil_div(npw, 256), natoms), dim3(256), 0, s, miller, npw, frac, L[0], L[1],
+  hipLaunchKernelGGL(k_beta_table<T>, dim3(ceil_div(nh, 256), natoms), dim3(256), 0, s, miller, nh, frac, L[0], L[1],
                      L[2], sigma, form, beta, ld);
   return hipGetLastError();
 }

@@ -357,7 +357,7 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   const bool f64 = P.prec == PW_FP64;
   const bool bkb = (P.flags & PW_FLAG_BF16_KB) != 0, bgr = (P.flags & PW_FLAG_BF16_GRAM) != 0;
   P.nsplit_proj = P.nproj ? (bkb ? pairs_proj_splits(P.nproj, P.nbb, (int)(P.ldh / 16), 64)
-                                  : pick_split(gemm_cn_tiles(P.nproj, P.nbb, f64), P.npw))
+                                  : pairs_cn_plan(P.nproj, P.nbb, P.nh, f64, 64).splits)
                           : 1;
   // planes of Y and W for the Gram product: written by the nonlocal product's epilogue with
   // split-precision projectors, split from Y and W before the Gram product with real-space ones
@@ -408,7 +408,7 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   for (int gi = 0; gi < P.npw; ++gi)
     for (int i = 0; i < 3; ++i) P.hmax[i] = std::max(P.hmax[i], std::abs(P.miller[3 * gi + i]));
   P.bwidth = (2 * P.hmax[0] + 1) + (2 * P.hmax[1] + 1) + (2 * P.hmax[2] + 1);
-  L.beta = take(otf || P.rspace ? 0 : bkb ? cb * P.ldh * P.nproj32 : cb * P.ldw * P.nproj);
+  L.beta = take(otf || P.rspace ? 0 : cb * P.ldh * (bkb ? P.nproj32 : P.nproj));
   L.brad = take(otf ? sizeof(double) * 4 * P.npw : 0);
   L.bph = take(otf ? 16 * (size_t)P.natoms * P.bwidth : 0);
   const bool blocked = P.nbb < P.nbands;

@@ -1,10 +1,11 @@
-"""Split-bf16 projector products on pairs (G, -G): every tile shape of the projection and the
-nonlocal product with remainders in bands, plane waves and projectors, the scalar epilogue of
-unaligned blocks, and the planes buffer shared by blocks of different widths.
+"""Projector products on pairs (G, -G): every tile shape of the projection and the nonlocal product
+with remainders in bands, plane waves and projectors, in split-bf16, FP32 and FP64, with the table
+stored or generated and both projector families; the scalar epilogue of unaligned blocks, and the
+planes buffer shared by blocks of different widths.
 
-Tolerance of H X: 5e-5 of max|HX|, as for the split-bf16 products elsewhere (each product's split
-residual is at most 2^-16, with random signs).  The reference is the FP64 oracle on the same
-FP32-rounded input."""
+Tolerances of H X relative to max|HX|, as for the same arithmetic elsewhere: 5e-5 with split-bf16
+products (each product's split residual is at most 2^-16, with random signs), 2e-5 in FP32, 1e-12 in
+FP64.  The reference is the FP64 oracle on the same (FP32-rounded) input."""
 import numpy as np
 import pytest
 
@@ -13,20 +14,20 @@ from paper_2406_10765_amd import pw, synth
 
 pytestmark = pytest.mark.gpu
 
-TOL = 5e-5
-
 
 def cell_with_atoms(n, L=(9.0, 10.26, 11.5), ecut=9.0, nbands=40):
     rng = np.random.Generator(np.random.PCG64(7))
     return synth.Cell(L=L, tau=rng.uniform(0, 1, (n, 3)) * np.array(L), ecut=ecut, nbands=nbands)
 
 
-def check(cell, nbs, ld_extra=None, cols=None):
-    m = O.model_from_cell(cell)
-    h = pw.Handle(cell, pw.PW_MIXED, flags=pw.PW_FLAG_BF16_ALL)
+def check(cell, nbs, ld_extra=None, cols=None, prec=pw.PW_MIXED, flags=pw.PW_FLAG_BF16_ALL, form=pw.PW_PROJ_GSPACE):
+    tol = 1e-12 if prec == pw.PW_FP64 else 5e-5 if flags & pw.PW_FLAG_BF16_KB else 2e-5
+    m = O.model_from_cell(cell, proj_form=O.PROJ_LOCALIZED) if form else O.model_from_cell(cell)
+    h = pw.Handle(cell, prec, flags=flags, proj_form=form)
     perm = pw.permutation_to(m.miller, h.gvectors())
     for nb in nbs:
-        X = synth.random_block(h.npw, nb, 11 + nb).astype(np.complex64)
+        X = synth.random_block(h.npw, nb, 11 + nb)
+        X = X if prec == pw.PW_FP64 else X.astype(np.complex64)
         ld = None if ld_extra is None else h.npw + ld_extra
         Xd = h.to_device(X, ld)
         got = h.to_host(h.apply_h(Xd))
@@ -35,13 +36,24 @@ def check(cell, nbs, ld_extra=None, cols=None):
         ref = O.apply_h(m, X[inv][:, list(use)].astype(np.complex128))[perm]
         err = float(np.abs(got[:, list(use)] - ref).max() / np.abs(ref).max())
         print("pairs npw", h.npw, "nproj", h.info.nproj, "nb", nb, "ld_extra", ld_extra, "err", err, flush=True)
-        assert err <= TOL
+        assert err <= tol
     h.close()
 
 
 @pytest.mark.parametrize("natoms", [0, 1, 3, 8, 9])
 def test_projector_and_row_remainders(natoms):
     check(cell_with_atoms(natoms), (1, 16, 17, 33, 40))
+
+
+@pytest.mark.parametrize("prec,flags,form", [(pw.PW_FP64, 0, 0), (pw.PW_FP64, pw.PW_FLAG_BETA_OTF, 0), (pw.PW_FP64, 0, 1),
+                                             (pw.PW_MIXED, 0, 0), (pw.PW_MIXED, pw.PW_FLAG_BETA_OTF, 0),
+                                             (pw.PW_MIXED, pw.PW_FLAG_BF16_KB, 1)])
+@pytest.mark.parametrize("natoms", [0, 3, 17])
+def test_precisions_tables_and_families(prec, flags, form, natoms):
+    # 68 projectors: 128-row tiles with a remainder; 12: 64-row tiles; widths 16, 32, 48 and 64
+    check(cell_with_atoms(natoms), (1, 17, 40) if natoms else (17,), prec=prec, flags=flags, form=form)
+    if natoms == 17:
+        check(cell_with_atoms(natoms, nbands=101), (48, 64, 101), prec=prec, flags=flags, form=form, cols=3)
 
 
 @pytest.mark.parametrize("ecut", [6.0, 8.0])
