@@ -99,6 +99,7 @@ struct pw_handle_s {
   unsigned char* ws = nullptr;
   size_t ws_sb = 0, ws_g1 = 0, ws_parts = 0, ws_pt = 0, ws_yp = 0;
   int ws_cols = 0, ws_fft_batch = 0, ws_nsplit = 0;
+  int ws_pitch = 0;  // row pitch of its pencil intermediate, 0: none (the plane is transformed inside LDS)
   std::chrono::steady_clock::time_point t_step;
   void report(const char* what, int i, int n) {
     if (!progress) return;
@@ -275,6 +276,8 @@ struct Engine {
   cplx<T>* g1_buf() const { return work<cplx<T>>(P.lay.g1, h->ws_g1); }
   double2* parts_buf() const { return work<double2>(P.lay.parts, h->ws_parts); }
   int fft_batch() const { return h->ws ? h->ws_fft_batch : P.fft_batch; }
+  // row pitch of the sized pencil form, 0 where it is not used
+  int pencil_pitch() const { return !P.fl.pencil_n ? 0 : h->ws ? h->ws_pitch : P.fl.pitch; }
   unsigned int* yp_hi() const { return work<unsigned int>(P.lay.yp, h->ws_yp); }
   unsigned int* yp_lo() const { return yp_hi() + (size_t)P.ldy * (h->ws ? h->ws_cols : P.yp_cols); }
   // the unblocked step keeps the planes of Y and W = H Y for the Gram product
@@ -388,6 +391,10 @@ struct Engine {
                   launch_sticks_inv<T>(Y + (long)b0 * ldy, ldy, SB, nbt, st, g, tw3, P.fl, sm));
       if (P.fl.sized) {
         PW_TIMED_ON(PW_PH_PLANE, sm, launch_plane_n<T>(SB, V, nbt, st, cs, g, tw1, scale, sm));
+      } else if (const int pitch = pencil_pitch()) {
+        PW_TIMED_ON(PW_PH_PENCIL_YINV, sm, launch_pencil_yinv_n<T>(SB, G1, nbt, cs, g, pitch, tw2, sm));
+        PW_TIMED_ON(PW_PH_PENCIL_X, sm, launch_pencil_x_n<T>(G1, V, nbt, g, pitch, tw1, sm));
+        PW_TIMED_ON(PW_PH_PENCIL_YFWD, sm, launch_pencil_yfwd_n<T>(SB, G1, nbt, cs, g, pitch, tw2, scale, sm));
       } else if (P.fl.fused) {
         PW_TIMED_ON(PW_PH_PLANE, sm,
                     launch_plane_fused<T>(SB, V, nbt, st, g, tw1, tw2, scale, 0, (T*)nullptr, P.fl, sm));
@@ -590,6 +597,30 @@ struct Engine {
                    launch_sticks_inv<T>(X + (long)b0 * ld, ld, SB, nbt, st, g, tw3, P.fl, h->stream));
           PW_TIMED(PW_PH_PLANE, launch_density128(SB, cs, g, tw1, occ + b0, nbt, ngroups, part, rho, b0 == 0,
                                                   h->stream));
+        }
+        return PW_OK;
+      }
+    }
+    if (pencil_n_supported(g.n1) && pencil_n_supported(g.n2)) {
+      // pencil form in the three work blocks (u0, u1, zb): one FP64 grid per band group, enough groups for
+      // two waves of 8 rows per SIMD, then the pencil intermediate of as many bands as fit
+      unsigned char* w0 = h->at<unsigned char>(P.lay.u0);
+      const size_t room = P.lay.zb - P.lay.u0 + sizeof(cplx<T>) * P.ldw * P.nbb;
+      const size_t grid_bytes = sizeof(double) * nr, g1_bytes = (size_t)g.n3 * g.n2 * P.fl.pitch * sizeof(cplx<T>);
+      int ngroups = (int)std::min<long>(16, std::max<long>(1, 32768 / ((long)g.n3 * g.n2)));
+      while (ngroups > 1 && 2 * ngroups * grid_bytes > room) --ngroups;
+      const size_t parts_bytes = (ngroups * grid_bytes + kArenaAlign - 1) / kArenaAlign * kArenaAlign;
+      const int bands = room > parts_bytes ? (int)std::min<size_t>(P.fft_batch, (room - parts_bytes) / g1_bytes) : 0;
+      if (bands >= 1) {
+        double* part = reinterpret_cast<double*>(w0);
+        cplx<T>* GP = reinterpret_cast<cplx<T>*>(w0 + parts_bytes);
+        for (int b0 = 0; b0 < nb; b0 += bands) {
+          const int nbt = std::min(bands, nb - b0), ng = std::min(ngroups, nbt);
+          PW_TIMED(PW_PH_STICKS_INV, launch_sticks_inv<T>(X + (long)b0 * ld, ld, SB, nbt, st, g, tw3, P.fl, h->stream));
+          PW_TIMED(PW_PH_PENCIL_YINV, launch_pencil_yinv_n<T>(SB, GP, nbt, cs, g, P.fl.pitch, tw2, h->stream));
+          PW_TIMED(PW_PH_PENCIL_X,
+                   launch_pencil_density_n<T>(GP, nbt, g, P.fl.pitch, tw1, occ + b0, ng, part, h->stream));
+          PW_TIMED(PW_PH_OTHER, launch_density_groups(part, ng, nr, rho, b0 == 0, h->stream));
         }
         return PW_OK;
       }
@@ -1564,7 +1595,10 @@ static int noalloc_layout(pw_handle* h, int nb) {
   const GridDesc& g = P.g;
   const size_t cb = 2 * (size_t)P.real_bytes;
   const size_t sb1 = (size_t)P.nst * g.n3 * cb;
-  const size_t g11 = P.fl.fused ? 0 : (size_t)g.n3 * g.n2 * g.n1a * cb;
+  // the sized pencil form, unless one column only fits without it (planes in LDS) or without the
+  // padding of its rows
+  int pitch = P.fl.pencil_n ? P.fl.pitch : 0;
+  size_t g11 = pitch || !P.fl.fused ? (size_t)g.n3 * g.n2 * (pitch ? pitch : g.n1a) * cb : 0;
   const bool planes = P.real_bytes == 4 && (P.flags & PW_FLAG_BF16_KB) && P.nproj > 0;
   const size_t npt = planes ? P.nproj32 : P.nproj;
   // the projection takes fewer K splits where one column would not fit otherwise
@@ -1575,6 +1609,10 @@ static int noalloc_layout(pw_handle* h, int nb) {
   const size_t slack = 5 * kArenaAlign;
   if (kScratchBytes <= slack) return 0;
   if (per_column() > kScratchBytes - slack) ns = 1;
+  if (pitch && per_column() > kScratchBytes - slack) {
+    pitch = P.fl.fused ? 0 : g.n1a;
+    g11 = (size_t)g.n3 * g.n2 * pitch * cb;
+  }
   long w = (long)((kScratchBytes - slack) / per_column());
   w = std::min<long>(w, std::min(nb, P.nbb));
   if (w < 1) return 0;
@@ -1595,6 +1633,7 @@ static int noalloc_layout(pw_handle* h, int nb) {
   h->ws_cols = (int)w;
   h->ws_fft_batch = (int)fb;
   h->ws_nsplit = ns;
+  h->ws_pitch = pitch;
   return (int)w;
 }
 

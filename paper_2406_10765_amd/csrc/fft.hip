@@ -467,6 +467,9 @@ bool fft_plan_launch(const GridDesc& g, int real_bytes, size_t max_lds, FftLaunc
   }
   L->sized = L->fused && plane_n_supported(g.n1, g.n2, real_bytes, max_lds) && std::getenv("PW_GENERIC_PLANE") == nullptr;
   L->sized_sticks = sticks_n_supported(g.n3) && std::getenv("PW_GENERIC_STICKS") == nullptr;
+  L->pencil_n = !L->sized && pencil_n_supported(g.n1) && pencil_n_supported(g.n2);
+  const int line = 128 / cb;
+  L->pitch = (g.n1a + line - 1) / line * line;
   L->cx = 16;
   while (L->cx > 1 && L->cx * g.n2 > 4096) L->cx /= 2;
   L->cy = 16;

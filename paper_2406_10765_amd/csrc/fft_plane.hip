@@ -17,96 +17,10 @@
 #include <utility>
 
 #include "common.hpp"
+#include "fft_small.hpp"
 #include "kernels.hpp"
 
 namespace pw {
-
-// static loop: f(std::integral_constant<int, i>) for i in [0, N)
-template <typename F, int... I>
-__device__ __forceinline__ void sfor_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void sfor(F&& f) {
-  sfor_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// ---- compile-time trigonometry (twiddles of the small DFTs) ------------------------------
-constexpr double kPiC = 3.14159265358979323846264338327950288;
-constexpr double csin(double x) {
-  // reduce to [-pi, pi]
-  while (x > kPiC) x -= 2 * kPiC;
-  while (x < -kPiC) x += 2 * kPiC;
-  double term = x, sum = x;
-  for (int n = 1; n < 30; ++n) {
-    term *= -x * x / ((2 * n) * (2 * n + 1));
-    sum += term;
-  }
-  return sum;
-}
-constexpr double ccos(double x) { return csin(x + kPiC / 2); }
-
-// In-register DFT of compile-time size S with sign SG (+1 inverse, -1 forward), natural order.
-template <typename T, int S, int SG>
-struct SmallDft {
-  static __device__ __forceinline__ void run(cplx<T>* v) {
-    if constexpr (S == 1) {
-      return;
-    } else if constexpr (S == 2) {
-      const cplx<T> a = v[0], b = v[1];
-      v[0] = cadd<T>(a, b);
-      v[1] = csub<T>(a, b);
-    } else if constexpr (S == 3) {
-      const T h = (T)0.86602540378443864676;
-      const cplx<T> t1 = cadd<T>(v[1], v[2]), t2 = csub<T>(v[1], v[2]);
-      const cplx<T> m = mk<T>(v[0].x - (T)0.5 * t1.x, v[0].y - (T)0.5 * t1.y);
-      const cplx<T> r = cmuli<T>(cscale<T>(t2, h), SG);
-      v[0] = cadd<T>(v[0], t1);
-      v[1] = cadd<T>(m, r);
-      v[2] = csub<T>(m, r);
-    } else if constexpr (S == 4) {
-      const cplx<T> s02 = cadd<T>(v[0], v[2]), d02 = csub<T>(v[0], v[2]);
-      const cplx<T> s13 = cadd<T>(v[1], v[3]);
-      const cplx<T> d13 = cmuli<T>(csub<T>(v[1], v[3]), SG);
-      v[0] = cadd<T>(s02, s13);
-      v[2] = csub<T>(s02, s13);
-      v[1] = cadd<T>(d02, d13);
-      v[3] = csub<T>(d02, d13);
-    } else {
-      // S = F * G with F the first radix (4, 2 or 3): n = G f + g, k = kf + F kg
-      constexpr int F = (S % 4 == 0) ? 4 : (S % 2 == 0) ? 2 : 3;
-      constexpr int G = S / F;
-      cplx<T> t[G][F];
-      sfor<G>([&](auto gi) {
-        constexpr int g = decltype(gi)::value;
-        cplx<T> u[F];
-#pragma unroll
-        for (int f = 0; f < F; ++f) u[f] = v[G * f + g];
-        SmallDft<T, F, SG>::run(u);
-        sfor<F>([&](auto ki) {
-          constexpr int kf = decltype(ki)::value;
-          if constexpr (g * kf != 0) {
-            constexpr double ang = SG * 2.0 * kPiC * (double)(g * kf) / (double)S;
-            constexpr T wc = (T)ccos(ang), ws = (T)csin(ang);
-            u[kf] = cmul<T>(u[kf], mk<T>(wc, ws));
-          }
-          t[g][kf] = u[kf];
-        });
-      });
-#pragma unroll
-      for (int kf = 0; kf < F; ++kf) {
-        cplx<T> w[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) w[g] = t[g][kf];
-        SmallDft<T, G, SG>::run(w);
-#pragma unroll
-        for (int kg = 0; kg < G; ++kg) v[kf + F * kg] = w[kg];
-      }
-    }
-  }
-};
-
-constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
 
 // One line FFT of length N = A B held in LDS (element e at base + e * es), T threads per line.
 // In: natural order; out: natural order.  Barriers are executed by every thread of the block
@@ -459,11 +373,6 @@ __device__ __forceinline__ void rs_add_regs(float2 (&r)[16], const RsDesc& rd, i
 //   16 k1 + (n2 ^ k1 ^ 8 (y & 1)), word (m1, q2) of the forward at (8 q2 + (m1 ^ (q2 & 7))) ^ 8 (y & 1).
 // Each swizzle spreads the 64 lanes of a wave (8 lines x 8 threads) over all 16 eight-byte bank
 // slots in every access of the three passes.  Three workgroup barriers per plane.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 __device__ __forceinline__ int p128_col(int row, int xa) { return xa ^ ((((row >> 4) ^ row) & 1) << 3); }
 
 // NL: the real-space projectors' D P term is added to V psi between the x passes (rs_add_regs).
@@ -812,6 +721,11 @@ __global__ void k_density_groups(const double* __restrict__ part, int ngroups, l
     for (int q = 0; q < ngroups; ++q) s += part[(long)q * nr + r];
     rho[r] = s;
   }
+}
+
+hipError_t launch_density_groups(const double* part, int ngroups, long nr, double* rho, bool first, hipStream_t s) {
+  hipLaunchKernelGGL(k_density_groups, dim3(stride_blocks(nr)), dim3(256), 0, s, part, ngroups, nr, rho, first ? 1 : 0);
+  return hipGetLastError();
 }
 
 bool density128_supported(const GridDesc& g, int real_bytes) {

@@ -1,0 +1,112 @@
+// In-register DFTs of compile-time size with compile-time twiddles, shared by the sized FFT kernels
+// (fft_plane.hip, fft_pencil.hpp).
+#pragma once
+
+#include <type_traits>
+#include <utility>
+
+#include "common.hpp"
+
+namespace pw {
+
+// static loop: f(std::integral_constant<int, i>) for i in [0, N)
+template <typename F, int... I>
+__device__ __forceinline__ void sfor_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void sfor(F&& f) {
+  sfor_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// ---- compile-time trigonometry (twiddles of the small DFTs) ------------------------------
+constexpr double kPiC = 3.14159265358979323846264338327950288;
+// sin(x + q pi / 2) for |x| <= pi / 4 by the power series of sin or cos
+constexpr double csin_q(double x, int q) {
+  double term = q % 2 ? 1.0 : x, sum = term;
+  for (int n = 1; n < 14; ++n) {
+    const int k = q % 2 ? 2 * n - 1 : 2 * n;
+    term *= -x * x / (k * (k + 1));
+    sum += term;
+  }
+  return q >= 2 ? -sum : sum;
+}
+// x reduced to the nearest multiple of pi / 2, so that no series term exceeds the result's order
+constexpr double csin_from(double x, int q) {
+  const int k = (int)(x / (kPiC / 2) + (x < 0 ? -0.5 : 0.5));
+  return csin_q(x - k * (kPiC / 2), (((k + q) % 4) + 4) % 4);
+}
+constexpr double csin(double x) { return csin_from(x, 0); }
+constexpr double ccos(double x) { return csin_from(x, 1); }
+
+// In-register DFT of compile-time size S with sign SG (+1 inverse, -1 forward), natural order.
+template <typename T, int S, int SG>
+struct SmallDft {
+  static __device__ __forceinline__ void run(cplx<T>* v) {
+    if constexpr (S == 1) {
+      return;
+    } else if constexpr (S == 2) {
+      const cplx<T> a = v[0], b = v[1];
+      v[0] = cadd<T>(a, b);
+      v[1] = csub<T>(a, b);
+    } else if constexpr (S == 3) {
+      const T h = (T)0.86602540378443864676;
+      const cplx<T> t1 = cadd<T>(v[1], v[2]), t2 = csub<T>(v[1], v[2]);
+      const cplx<T> m = mk<T>(v[0].x - (T)0.5 * t1.x, v[0].y - (T)0.5 * t1.y);
+      const cplx<T> r = cmuli<T>(cscale<T>(t2, h), SG);
+      v[0] = cadd<T>(v[0], t1);
+      v[1] = cadd<T>(m, r);
+      v[2] = csub<T>(m, r);
+    } else if constexpr (S == 4) {
+      const cplx<T> s02 = cadd<T>(v[0], v[2]), d02 = csub<T>(v[0], v[2]);
+      const cplx<T> s13 = cadd<T>(v[1], v[3]);
+      const cplx<T> d13 = cmuli<T>(csub<T>(v[1], v[3]), SG);
+      v[0] = cadd<T>(s02, s13);
+      v[2] = csub<T>(s02, s13);
+      v[1] = cadd<T>(d02, d13);
+      v[3] = csub<T>(d02, d13);
+    } else {
+      // S = F * G with F the first radix (4, 2 or 3): n = G f + g, k = kf + F kg
+      constexpr int F = (S % 4 == 0) ? 4 : (S % 2 == 0) ? 2 : 3;
+      constexpr int G = S / F;
+      cplx<T> t[G][F];
+      sfor<G>([&](auto gi) {
+        constexpr int g = decltype(gi)::value;
+        cplx<T> u[F];
+#pragma unroll
+        for (int f = 0; f < F; ++f) u[f] = v[G * f + g];
+        SmallDft<T, F, SG>::run(u);
+        sfor<F>([&](auto ki) {
+          constexpr int kf = decltype(ki)::value;
+          if constexpr (g * kf != 0) {
+            constexpr int turn = 2 * g * kf > S ? g * kf - S : g * kf;  // angle within [-pi, pi]
+            constexpr double ang = SG * 2.0 * kPiC * (double)turn / (double)S;
+            constexpr T wc = (T)ccos(ang), ws = (T)csin(ang);
+            u[kf] = cmul<T>(u[kf], mk<T>(wc, ws));
+          }
+          t[g][kf] = u[kf];
+        });
+      });
+#pragma unroll
+      for (int kf = 0; kf < F; ++kf) {
+        cplx<T> w[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) w[g] = t[g][kf];
+        SmallDft<T, G, SG>::run(w);
+#pragma unroll
+        for (int kg = 0; kg < G; ++kg) v[kf + F * kg] = w[kg];
+      }
+    }
+  }
+};
+
+constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
+
+// Orders a wave's LDS accesses before and after it (lines whose threads sit in one wave exchange through
+// LDS without a workgroup barrier).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+}  // namespace pw

@@ -12,6 +12,11 @@ struct FftLaunch {
   bool fused;     // whole plane in LDS
   bool sized;     // fused plane with a compile-time size kernel (register FFT stages)
   bool sized_sticks;  // z transforms with a compile-time size kernel
+  // pencil form with compile-time line lengths: planes that do not fit in LDS, and the others without a
+  // sized fused kernel (unequal sides).  A sized fused plane moves a quarter of the bytes and stays ahead
+  // (64^2, 144 bands, FP32: 126 against 236 us; 96^2, 128 bands, FP64: 1,314 against 1,341 us)
+  bool pencil_n;
+  int pitch;          // its row pitch of G1: n1a rounded up to whole 128-byte lines
   int plane_thr;
   int cx, cy;     // columns / rows per workgroup in the pencil form
   int col_thr, row_thr;
@@ -83,6 +88,25 @@ hipError_t launch_pencil_x(cplx<T>* G1, const T* V, int nbatch, const GridDesc& 
 template <typename T>
 hipError_t launch_pencil_yfwd(cplx<T>* SB, const cplx<T>* G1, int nbatch, const Stick* st, const int* colstart,
                               const GridDesc& g, const cplx<T>* tw2, T scale, const FftLaunch& L, hipStream_t s);
+
+// Pencil form with compile-time line lengths (fft_pencil.hpp): G1[band][z][y][xa] with rows of `pitch`
+// elements.  launch_pencil_density_n sums occ |psi|^2 over each of ngroups consecutive groups of the
+// bands into part[group][z][y][x]; launch_density_groups adds the groups in order:
+// rho = (first ? 0 : rho) + part[0] + part[1] + ...
+bool pencil_n_supported(int n);
+template <typename T>
+hipError_t launch_pencil_yinv_n(const cplx<T>* SB, cplx<T>* G1, int nbatch, const int* colstart, const GridDesc& g,
+                                int pitch, const cplx<T>* tw2, hipStream_t s);
+template <typename T>
+hipError_t launch_pencil_x_n(cplx<T>* G1, const T* V, int nbatch, const GridDesc& g, int pitch, const cplx<T>* tw1,
+                             hipStream_t s);
+template <typename T>
+hipError_t launch_pencil_yfwd_n(cplx<T>* SB, const cplx<T>* G1, int nbatch, const int* colstart, const GridDesc& g,
+                                int pitch, const cplx<T>* tw2, T scale, hipStream_t s);
+template <typename T>
+hipError_t launch_pencil_density_n(const cplx<T>* G1, int nbatch, const GridDesc& g, int pitch, const cplx<T>* tw1,
+                                   const double* occ, int ngroups, double* part, hipStream_t s);
+hipError_t launch_density_groups(const double* part, int ngroups, long nr, double* rho, bool first, hipStream_t s);
 
 // --------------------------------------------------------------- GEMM ------
 // C_part[s] = A^H B over the s-th K chunk.  A: K x M, B: K x N (column-major; columns of B

@@ -336,7 +336,8 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   // --- batching ------------------------------------------------------------------
   const size_t cb = 2 * (size_t)P.real_bytes;
   const size_t per_band_sb = (size_t)P.nst * g.n3 * cb;
-  const size_t per_band_g1 = P.fl.fused ? 0 : (size_t)g.n3 * g.n2 * g.n1a * cb;
+  const size_t per_band_g1 = P.fl.pencil_n ? (size_t)g.n3 * g.n2 * P.fl.pitch * cb
+                             : P.fl.fused ? 0 : (size_t)g.n3 * g.n2 * g.n1a * cb;
   size_t budget = 192ull << 20;  // keep the stick/pencil intermediates of one batch cache-sized
   if (const char* e = std::getenv("PW_FFT_BATCH_MB")) budget = (size_t)std::atol(e) << 20;
   int fb = (int)(budget / (per_band_sb + per_band_g1));

@@ -1,0 +1,85 @@
+"""Sized pencil form of the plane stage (planes with unequal sides, FP64 planes beyond LDS) against the
+oracle: H X and the charge density with every compiled line length along x and along y, several bands
+per wave, and the allocation-free entry point where the pencil intermediate does and does not fit its
+work array.  Tolerances as elsewhere: H X 1e-12 (FP64) and 2e-5 (FP32) of max|HX|, density 1e-12 and
+1e-5 of its maximum."""
+import numpy as np
+import pytest
+
+from oracle import pw_oracle as O
+from paper_2406_10765_amd import pw, synth
+
+pytestmark = pytest.mark.gpu
+
+# every length once along x and once along y, never equal
+GRIDS = [(24, 27, 32), (27, 32, 24), (32, 36, 27), (36, 48, 24), (48, 54, 27), (54, 64, 24), (64, 72, 24), (72, 81, 27),
+         (81, 96, 24), (96, 108, 24), (108, 128, 24), (128, 144, 24), (144, 162, 24), (162, 192, 24), (192, 24, 27)]
+
+
+def model_and_handle(cell, prec, nb, grid):
+    # the density keeps its grids in the work blocks: room for one grid of the largest size
+    m = O.model_from_cell(cell, grid=grid)
+    h = pw.Handle(cell, prec, nbands=max(nb, 300), fft_n=grid)
+    assert tuple(h.info.fft_n) == grid
+    return m, h, pw.permutation_to(m.miller, h.gvectors())
+
+
+@pytest.mark.parametrize("grid", GRIDS)
+@pytest.mark.parametrize("prec", [pw.PW_FP64, pw.PW_MIXED])
+def test_line_lengths(grid, prec):
+    nb = 3
+    m, h, p = model_and_handle(synth.make_cell("si8", modes=True), prec, nb, grid)
+    X = synth.random_block(m.npw, nb, 5 + grid[0])
+    if prec == pw.PW_MIXED:
+        X = X.astype(np.complex64).astype(np.complex128)
+    Xd = h.to_device(X[p])
+    ref = O.apply_h(m, X)[p]
+    err = float(np.abs(h.to_host(h.apply_h(Xd)) - ref).max() / np.abs(ref).max())
+    occ = np.array([2.0, 0.0, 0.7])
+    rho = O.density(X, occ, m.miller, m.grid).transpose(2, 1, 0)
+    got = h.density(Xd, occ).cpu().numpy()
+    derr = float(np.abs(got - rho).max() / rho.max())
+    print("pencil grid", grid, "prec", prec, "H X", err, "density", derr, flush=True)
+    assert err < (1e-12 if prec == pw.PW_FP64 else 2e-5)
+    assert derr < (1e-12 if prec == pw.PW_FP64 else 1e-5)
+    h.close()
+
+
+@pytest.mark.parametrize("prec,nb", [(pw.PW_FP64, 33), (pw.PW_MIXED, 50)])
+def test_several_bands_per_wave_and_groups(prec, nb):
+    # 64 x 72 x 54: 36,288 .. waves of one band, so the x pass takes several bands per wave (nb is no multiple)
+    cell = synth.silicon_cell((2, 2, 2), 8.0, nbands=nb, disp_seed=4)
+    m, h, p = model_and_handle(cell, prec, nb, (64, 72, 54))
+    X = synth.random_block(m.npw, nb, 8)
+    if prec == pw.PW_MIXED:
+        X = X.astype(np.complex64).astype(np.complex128)
+    Xd = h.to_device(X[p])
+    use = [0, 1, nb // 2, nb - 2, nb - 1]
+    ref = O.apply_h(m, X[:, use])[p]
+    err = float(np.abs(h.to_host(h.apply_h(Xd))[:, use] - ref).max() / np.abs(ref).max())
+    occ = np.linspace(2.0, 0.1, nb)
+    rho = O.density(X, occ, m.miller, m.grid).transpose(2, 1, 0)
+    derr = float(np.abs(h.density(Xd, occ).cpu().numpy() - rho).max() / rho.max())
+    print("pencil bands", nb, "prec", prec, "H X", err, "density", derr, flush=True)
+    assert err < (1e-12 if prec == pw.PW_FP64 else 2e-5)
+    assert derr < (1e-12 if prec == pw.PW_FP64 else 1e-5)
+    h.close()
+
+
+@pytest.mark.parametrize("ncells,ecut,grid,prec", [
+    ((1, 2, 2), 10.0, (0, 0, 0), pw.PW_FP64),      # the intermediate fits
+    ((4, 3, 1), 12.5, (108, 81, 512), pw.PW_FP64)])  # 46 MiB a band beside the sticks: the planes stay in LDS
+def test_noalloc(ncells, ecut, grid, prec):
+    nb = 5
+    cell = synth.silicon_cell(ncells, ecut, nbands=nb, disp_seed=4)
+    h = pw.Handle(cell, prec, nbands=nb, fft_n=grid)
+    X = h.random_block(nb, 3)
+    ref = h.to_host(h.apply_h(X))
+    out = h.empty_block(nb)
+    out.fill_(float("nan"))
+    h.apply_h_noalloc(X, out)
+    got = h.to_host(out)
+    err = float(np.abs(got - ref).max() / np.abs(ref).max())
+    print("pencil noalloc", ncells, grid, err, flush=True)
+    assert err < (1e-12 if prec == pw.PW_FP64 else 2e-5)
+    h.close()
