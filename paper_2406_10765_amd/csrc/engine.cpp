@@ -390,7 +390,7 @@ struct Engine {
       PW_TIMED_ON(PW_PH_STICKS_INV, sm,
                   launch_sticks_inv<T>(Y + (long)b0 * ldy, ldy, SB, nbt, st, g, tw3, P.fl, sm));
       if (P.fl.sized) {
-        PW_TIMED_ON(PW_PH_PLANE, sm, launch_plane_n<T>(SB, V, nbt, st, cs, g, tw1, scale, sm));
+        PW_TIMED_ON(PW_PH_PLANE, sm, launch_plane_n<T>(SB, V, nbt, cs, g, tw1, scale, sm));
       } else if (const int pitch = pencil_pitch()) {
         PW_TIMED_ON(PW_PH_PENCIL_YINV, sm, launch_pencil_yinv_n<T>(SB, G1, nbt, cs, g, pitch, tw2, sm));
         PW_TIMED_ON(PW_PH_PENCIL_X, sm, launch_pencil_x_n<T>(G1, V, nbt, g, pitch, tw1, sm));

@@ -13,8 +13,8 @@
 //   F[B q1 + q2] = sum_m1 Z[m1][q2] W_A^{-m1 q1}                                       (after one exchange)
 // The small DFTs are fully unrolled with compile-time twiddles.
 
+#include <algorithm>
 #include <type_traits>
-#include <utility>
 
 #include "common.hpp"
 #include "fft_small.hpp"
@@ -22,198 +22,238 @@
 
 namespace pw {
 
-// One line FFT of length N = A B held in LDS (element e at base + e * es), T threads per line.
-// In: natural order; out: natural order.  Barriers are executed by every thread of the block
-// (active = false threads take part in the barriers only).
-template <typename T, int A, int B, int SG>
-__device__ __forceinline__ void line_fft(cplx<T>* buf, int base, int es, int t, bool active, const cplx<T>* twN) {
-  constexpr int N = A * B, TT = cgcd(A, B), I1 = B / TT, J2 = A / TT;
-  cplx<T> r1[I1][A];
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < I1; ++i)
-#pragma unroll
-      for (int n1 = 0; n1 < A; ++n1) r1[i][n1] = buf[base + (B * n1 + t + TT * i) * es];
-  }
-  __syncthreads();
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < I1; ++i) {
-      const int n2 = t + TT * i;
-      SmallDft<T, A, SG>::run(r1[i]);
-#pragma unroll
-      for (int k1 = 1; k1 < A; ++k1) {
-        cplx<T> w = twN[(n2 * k1) % N];
-        if (SG > 0) w.y = -w.y;
-        r1[i][k1] = cmul<T>(r1[i][k1], w);
-      }
-#pragma unroll
-      for (int k1 = 0; k1 < A; ++k1) buf[base + (k1 * B + n2) * es] = r1[i][k1];
-    }
-  }
-  __syncthreads();
-  cplx<T> r2[J2][B];
-  if (active) {
-#pragma unroll
-    for (int j = 0; j < J2; ++j) {
-      const int k1 = t + TT * j;
-#pragma unroll
-      for (int n2 = 0; n2 < B; ++n2) r2[j][n2] = buf[base + (k1 * B + n2) * es];
-      SmallDft<T, B, SG>::run(r2[j]);
-    }
-  }
-  __syncthreads();
-  if (active) {
-#pragma unroll
-    for (int j = 0; j < J2; ++j) {
-      const int k1 = t + TT * j;
-#pragma unroll
-      for (int k2 = 0; k2 < B; ++k2) buf[base + (k1 + A * k2) * es] = r2[j][k2];
-    }
-  }
-  __syncthreads();
-}
 
-// Row pass: inverse FFT, * V, forward FFT, in place on a row held in LDS (element stride 1).
-// vr[j][k2] = V at x = k1 + A k2 with k1 = t + gcd(A, B) j (loaded by the caller ahead of time).
+
+// ---- N x N planes in LDS with wave-local lines -----------------------------------------------------
+// The TT = gcd(A, B) threads of a line sit in one wave, which orders the exchange between the two
+// register stages by itself; three workgroup barriers per plane:
+//   y inverse   lines = active columns xa = n1 + n1max, read straight from the sticks (zeros off a stick's
+//               n2 range), exchanged in place in the plane's columns
+//   x           every wave keeps one group of LPW rows: inverse, * V, forward, exchanged in place in the row
+//   y forward   back into the sticks
+// The plane holds the active columns only, with row pitch R; BX and AX are the pitches of the in-row
+// exchange words (k1 BX + n2 and q2 AX + m1).  TT threads share a line (gcd(A, B), or 8 for 96, whose
+// 24 elements per thread would leave one wave per SIMD).  R, BX and AX are those with the fewest LDS bank
+// conflicts over the passes' accesses, by enumeration; 64 in FP32 (R = 64) swizzles columns and exchange
+// words instead and has none.  WPE: waves per SIMD the compiler must reach, set where the natural register
+// count would cost a workgroup per CU.  LOOP: a workgroup takes one z plane of several bands in turn, so that
+// its rows of V stay in the first cache.  V is read where it is used: held in registers across the plane
+// it cost a wave per SIMD.
+// Bound by the issue of the butterflies and LDS accesses; sticks and barriers of one workgroup wait under
+// the others of the compute unit.  Per band of H X (us), before with a workgroup barrier per exchange and
+// zeroing, scatter and gather of the whole plane, and now:
+//   FP32  54^2 0.83 -> 0.64 (144 bands), 64^2 0.88 -> 0.76, 81^2 2.20 -> 1.63, 96^2 4.14 -> 3.98 (440 bands),
+//         108^2 7.76 (pencil form) -> 6.87
+//   FP64  54^2 1.40 -> 1.15, 64^2 1.65 -> 1.20, 81^2 5.28 -> 3.17 (128 bands), 96^2 10.3 -> 8.54
+template <typename T, int N> struct PlanePitch;
+template <> struct PlanePitch<float, 24> { static constexpr int TT = 2, R = 30, BX = 7, AX = 5, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<float, 27> { static constexpr int TT = 3, R = 27, BX = 9, AX = 3, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<float, 32> { static constexpr int TT = 4, R = 37, BX = 8, AX = 4, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<float, 48> { static constexpr int TT = 4, R = 60, BX = 13, AX = 5, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<float, 54> { static constexpr int TT = 3, R = 54, BX = 9, AX = 6, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<float, 64> { static constexpr int TT = 8, R = 64, BX = 8, AX = 8, WPE = 4, LOOP = 1; };
+template <> struct PlanePitch<float, 81> { static constexpr int TT = 9, R = 81, BX = 9, AX = 9, WPE = 6, LOOP = 0; };
+template <> struct PlanePitch<float, 96> { static constexpr int TT = 8, R = 101, BX = 12, AX = 8, WPE = 1, LOOP = 1; };
+template <> struct PlanePitch<float, 108> { static constexpr int TT = 6, R = 133, BX = 19, AX = 7, WPE = 1, LOOP = 1; };
+template <> struct PlanePitch<double, 24> { static constexpr int TT = 2, R = 30, BX = 7, AX = 5, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<double, 27> { static constexpr int TT = 3, R = 27, BX = 9, AX = 3, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<double, 32> { static constexpr int TT = 4, R = 44, BX = 9, AX = 5, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<double, 48> { static constexpr int TT = 4, R = 60, BX = 13, AX = 5, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<double, 54> { static constexpr int TT = 3, R = 59, BX = 9, AX = 6, WPE = 1, LOOP = 0; };
+template <> struct PlanePitch<double, 64> { static constexpr int TT = 8, R = 73, BX = 9, AX = 9, WPE = 4, LOOP = 0; };
+template <> struct PlanePitch<double, 81> { static constexpr int TT = 9, R = 89, BX = 9, AX = 9, WPE = 1, LOOP = 1; };
+template <> struct PlanePitch<double, 96> { static constexpr int TT = 4, R = 99, BX = 12, AX = 8, WPE = 1, LOOP = 0; };
+
 template <typename T, int A, int B>
-__device__ __forceinline__ void row_ivf(cplx<T>* buf, int base, int t, bool active, const cplx<T>* twN,
-                                        const T (&vr)[A / cgcd(A, B)][B]) {
-  constexpr int N = A * B, TT = cgcd(A, B), I1 = B / TT, J2 = A / TT;
-  // inverse stage 1
-  cplx<T> r1[I1][A];
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < I1; ++i)
-#pragma unroll
-      for (int n1 = 0; n1 < A; ++n1) r1[i][n1] = buf[base + B * n1 + t + TT * i];
+struct PlaneShape : PlanePitch<T, A * B> {
+  using P = PlanePitch<T, A * B>;
+  static constexpr int N = A * B, TT = P::TT, I1 = (B + TT - 1) / TT, J2 = (A + TT - 1) / TT;
+  static constexpr int LPW = 64 / TT, NW = (N + LPW - 1) / LPW;  // lines per wave; one group of rows per wave
+  static constexpr size_t LDS = (size_t)(N * P::R + N) * sizeof(cplx<T>);
+  static constexpr bool SWZ = P::R == 64;
+  // whether thread t's transform i of stage 1 (j of stage 2) exists: all do where TT divides B (A)
+  static __device__ __forceinline__ bool has1(int t, int i) { return B % TT == 0 || t + TT * i < B; }
+  static __device__ __forceinline__ bool has2(int t, int j) { return A % TT == 0 || t + TT * j < A; }
+  // plane word of (row, xa); in-row words of the exchanges of row y
+  static __device__ __forceinline__ int at(int row, int xa) {
+    return row * P::R + (SWZ ? xa ^ (4 * ((row ^ (row >> 3)) & 7)) : xa);
   }
-  __syncthreads();
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < I1; ++i) {
-      const int n2 = t + TT * i;
-      SmallDft<T, A, +1>::run(r1[i]);
-#pragma unroll
-      for (int k1 = 1; k1 < A; ++k1) {
-        cplx<T> w = twN[(n2 * k1) % N];
-        w.y = -w.y;
-        r1[i][k1] = cmul<T>(r1[i][k1], w);
-      }
-#pragma unroll
-      for (int k1 = 0; k1 < A; ++k1) buf[base + k1 * B + n2] = r1[i][k1];
-    }
+  static __device__ __forceinline__ int inv_word(int y, int k1, int n2) {
+    return SWZ ? (8 * k1 + (n2 ^ k1)) ^ (8 * (y & 3)) : k1 * P::BX + n2;
   }
-  __syncthreads();
-  // inverse stage 2, * V, forward stage 1 (all in registers)
-  cplx<T> r2[J2][B];
-  if (active) {
-#pragma unroll
-    for (int j = 0; j < J2; ++j) {
-      const int k1 = t + TT * j;
-#pragma unroll
-      for (int n2 = 0; n2 < B; ++n2) r2[j][n2] = buf[base + k1 * B + n2];
-      SmallDft<T, B, +1>::run(r2[j]);
-#pragma unroll
-      for (int k2 = 0; k2 < B; ++k2) r2[j][k2] = cscale<T>(r2[j][k2], vr[j][k2]);
-      SmallDft<T, B, -1>::run(r2[j]);  // over m2 = k2, output q2
-#pragma unroll
-      for (int q2 = 1; q2 < B; ++q2) r2[j][q2] = cmul<T>(r2[j][q2], twN[(k1 * q2) % N]);
-    }
+  static __device__ __forceinline__ int fwd_word(int y, int q2, int m1) {
+    return SWZ ? (8 * q2 + (m1 ^ q2)) ^ (8 * (y & 3)) : q2 * P::AX + m1;
   }
-  __syncthreads();
-  if (active) {
-#pragma unroll
-    for (int j = 0; j < J2; ++j) {
-      const int m1 = t + TT * j;
-#pragma unroll
-      for (int q2 = 0; q2 < B; ++q2) buf[base + q2 * A + m1] = r2[j][q2];
-    }
-  }
-  __syncthreads();
-  // forward stage 2: for each q2 of this thread, A-point DFT over m1
-  cplx<T> r3[I1][A];
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < I1; ++i) {
-      const int q2 = t + TT * i;
-#pragma unroll
-      for (int m1 = 0; m1 < A; ++m1) r3[i][m1] = buf[base + q2 * A + m1];
-      SmallDft<T, A, -1>::run(r3[i]);
-    }
-  }
-  __syncthreads();
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < I1; ++i) {
-      const int q2 = t + TT * i;
-#pragma unroll
-      for (int q1 = 0; q1 < A; ++q1) buf[base + B * q1 + q2] = r3[i][q1];
-    }
-  }
-  __syncthreads();
-}
+};
 
-__device__ __forceinline__ int wrapn(int n, int N) { return n < 0 ? n + N : n; }
-
-// Plane kernel for an N x N plane, N = A B.  Grid (n3, nbatch), NT threads.
-// LDS: plane [y][x] with row stride N + 1, then the twiddle table W_N (forward sign).
-template <typename T, int A, int B, int NT>
-__global__ __launch_bounds__(NT) void k_plane_n(cplx<T>* __restrict__ SB, const T* __restrict__ V,
-                                                const Stick* __restrict__ st, GridDesc g,
-                                                const cplx<T>* __restrict__ twg, T scale) {
-  constexpr int N = A * B, TT = cgcd(A, B), R = N + 1, J2 = A / TT;
-  static_assert(NT / TT >= N, "one row per thread group");
+// Grid (n3, band groups), 64 NW threads; bands blockIdx.y, blockIdx.y + gridDim.y, ...
+template <typename T, int A, int B>
+__global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
+    __attribute__((amdgpu_waves_per_eu(PlaneShape<T, A, B>::WPE))) void k_plane_w(
+        cplx<T>* __restrict__ SB, const T* __restrict__ V, const int* __restrict__ colstart, GridDesc g,
+        const cplx<T>* __restrict__ twg, T scale, int nbatch) {
+  using S = PlaneShape<T, A, B>;
+  constexpr int N = S::N, TT = S::TT, I1 = S::I1, J2 = S::J2, LPW = S::LPW, NW = S::NW;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cplx<T>* plane = reinterpret_cast<cplx<T>*>(smem_raw);
-  cplx<T>* tw = plane + N * R;
-  const int tid = threadIdx.x;
-  const int z = blockIdx.x, b = blockIdx.y;
-  // V(r) of this thread's row, fetched first so that its latency hides behind the y pass
-  const int yrow = tid % (NT / TT), trow = min(tid / (NT / TT), TT);
-  const bool row_act = yrow < N && trow < TT;
-  T vr[J2][B];
-  {
-    const T* vz = V + ((long)z * N + (row_act ? yrow : 0)) * N;
-#pragma unroll
-    for (int j = 0; j < J2; ++j)
-#pragma unroll
-      for (int k2 = 0; k2 < B; ++k2) vr[j][k2] = row_act ? vz[(trow + TT * j) + A * k2] : (T)0;
-  }
-  for (int i = tid; i < N * R; i += NT) plane[i] = mk<T>(0, 0);
-  for (int i = tid; i < N; i += NT) tw[i] = twg[i];
+  cplx<T>* tw = plane + N * S::R;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int l = min(lane / TT, LPW - 1), t = lane % TT;
+  const bool on = lane < LPW * TT;
+  const int z = blockIdx.x, n1max = g.n1max, n1a = g.n1a;
+  for (int i = tid; i < N; i += 64 * NW) tw[i] = twg[i];
+  const bool row_on = on && wv * LPW + l < N;  // this thread's row
+  const int y = min(wv * LPW + l, N - 1);
+  const T* vz = V + ((long)z * N + y) * N;
   __syncthreads();
-  cplx<T>* sb = SB + ((long)b * g.n3 + z) * g.nst;
-  for (int s = tid; s < g.nst; s += NT) {
-    const Stick t = st[s];
-    plane[wrapn(t.n2, N) * R + wrapn(t.n1, N)] = sb[s];
-  }
-  __syncthreads();
-  // inverse along y on the active columns (lines = x, element stride R)
-  {
-    const int L = g.n1a;
-    for (int l0 = 0; l0 < L; l0 += NT / TT) {
-      const int l = l0 + tid % (NT / TT), t = min(tid / (NT / TT), TT);
-      const bool act = l < L && t < TT;
-      const int x = act ? (l <= g.n1max ? l : l + N - g.n1a) : 0;
-      line_fft<T, A, B, +1>(plane, x, R, t, act, tw);
+  const cplx<T> zero = mk<T>(0, 0);
+  // W_N^{n2 k1} of stage 1 (n2 = t + TT i), conjugated for the inverse
+  auto twiddle1 = [&](cplx<T>(&r)[I1][A], bool inverse) {
+#pragma unroll
+    for (int i = 0; i < I1; ++i)
+#pragma unroll
+      for (int k1 = 1; k1 < A; ++k1) {
+        cplx<T> w = tw[((t + TT * i) * k1) % N];
+        if (inverse) w.y = -w.y;
+        r[i][k1] = cmul<T>(r[i][k1], w);
+      }
+  };
+  // rows e = B k1 + n2 of a column <- stage 1; rows B k1 + n2 of it -> stage 2
+  auto col_exchange = [&](cplx<T>(&r1)[I1][A], cplx<T>(&r2)[J2][B], int xa, bool act) {
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < I1; ++i)
+      if (act && S::has1(t, i))
+#pragma unroll
+        for (int k1 = 0; k1 < A; ++k1) plane[S::at(B * k1 + t + TT * i, xa)] = r1[i][k1];
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < J2; ++j) {
+      const int k1 = S::has2(t, j) ? t + TT * j : 0;
+#pragma unroll
+      for (int n2 = 0; n2 < B; ++n2) r2[j][n2] = plane[S::at(B * k1 + n2, xa)];
     }
-  }
-  // along x: inverse, * V, forward (lines = y rows, one per thread group)
-  row_ivf<T, A, B>(plane, (row_act ? yrow : 0) * R, trow, row_act, tw, vr);
-  // forward along y on the active columns
-  {
-    const int L = g.n1a;
-    for (int l0 = 0; l0 < L; l0 += NT / TT) {
-      const int l = l0 + tid % (NT / TT), t = min(tid / (NT / TT), TT);
-      const bool act = l < L && t < TT;
-      const int x = act ? (l <= g.n1max ? l : l + N - g.n1a) : 0;
-      line_fft<T, A, B, -1>(plane, x, R, t, act, tw);
+  };
+  auto one_band = [&](int b) {
+    cplx<T>* sb = SB + ((long)b * g.n3 + z) * g.nst;
+    // ---- inverse along y, active columns ----
+    for (int c0 = wv * LPW; c0 < n1a; c0 += NW * LPW) {
+      const int xa = min(c0 + l, n1a - 1);
+      const bool act = on && c0 + l < n1a;
+      const int cs = colstart[xa], m = act ? (colstart[xa + 1] - cs - 1) >> 1 : -1;
+      cplx<T> r1[I1][A], r2[J2][B];
+#pragma unroll
+      for (int i = 0; i < I1; ++i)
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) {
+          const int e = B * n1 + t + TT * i;
+          const int n2 = 2 * e < N ? e : e - N;
+          r1[i][n1] = (n2 <= m && -n2 <= m && S::has1(t, i)) ? sb[cs + n2 + m] : zero;
+        }
+#pragma unroll
+      for (int i = 0; i < I1; ++i) SmallDft<T, A, +1>::run(r1[i]);
+      twiddle1(r1, true);
+      col_exchange(r1, r2, xa, act);
+#pragma unroll
+      for (int j = 0; j < J2; ++j) SmallDft<T, B, +1>::run(r2[j]);
+      wave_sync();
+#pragma unroll
+      for (int j = 0; j < J2; ++j)
+        if (act && S::has2(t, j))
+#pragma unroll
+          for (int k2 = 0; k2 < B; ++k2) plane[S::at(t + TT * j + A * k2, xa)] = r2[j][k2];
     }
-  }
-  for (int s = tid; s < g.nst; s += NT) {
-    const Stick t = st[s];
-    sb[s] = cscale<T>(plane[wrapn(t.n2, N) * R + wrapn(t.n1, N)], scale);
+    __syncthreads();
+    // ---- along x: inverse, * V, forward ----
+    {
+      cplx<T>* row = plane + y * S::R;
+      cplx<T> r1[I1][A], r2[J2][B];
+#pragma unroll
+      for (int i = 0; i < I1; ++i)
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) {
+          const int x = B * n1 + t + TT * i;
+          const int k = 2 * x < N ? x : x - N;
+          r1[i][n1] = (k <= n1max && -k <= n1max && S::has1(t, i)) ? plane[S::at(y, k + n1max)] : zero;
+        }
+#pragma unroll
+      for (int i = 0; i < I1; ++i) SmallDft<T, A, +1>::run(r1[i]);
+      twiddle1(r1, true);
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < I1; ++i)
+        if (row_on && S::has1(t, i))
+#pragma unroll
+          for (int k1 = 0; k1 < A; ++k1) row[S::inv_word(y, k1, t + TT * i)] = r1[i][k1];
+      wave_sync();
+#pragma unroll
+      for (int j = 0; j < J2; ++j) {
+        const int k1 = S::has2(t, j) ? t + TT * j : 0;
+#pragma unroll
+        for (int n2 = 0; n2 < B; ++n2) r2[j][n2] = row[S::inv_word(y, k1, n2)];
+        SmallDft<T, B, +1>::run(r2[j]);
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) r2[j][k2] = cscale<T>(r2[j][k2], vz[k1 + A * k2]);
+        SmallDft<T, B, -1>::run(r2[j]);  // over m2 = k2, output q2
+#pragma unroll
+        for (int q2 = 1; q2 < B; ++q2) r2[j][q2] = cmul<T>(r2[j][q2], tw[(k1 * q2) % N]);
+      }
+      wave_sync();
+#pragma unroll
+      for (int j = 0; j < J2; ++j)
+        if (row_on && S::has2(t, j))
+#pragma unroll
+          for (int q2 = 0; q2 < B; ++q2) row[S::fwd_word(y, q2, t + TT * j)] = r2[j][q2];
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < I1; ++i) {
+        const int q2 = S::has1(t, i) ? t + TT * i : 0;
+#pragma unroll
+        for (int m1 = 0; m1 < A; ++m1) r1[i][m1] = row[S::fwd_word(y, q2, m1)];
+        SmallDft<T, A, -1>::run(r1[i]);  // r1[i][q1] = F[B q1 + q2]
+      }
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < I1; ++i)
+#pragma unroll
+        for (int q1 = 0; q1 < A; ++q1) {
+          const int x = B * q1 + t + TT * i;
+          const int k = 2 * x < N ? x : x - N;
+          if (row_on && S::has1(t, i) && k <= n1max && -k <= n1max) plane[S::at(y, k + n1max)] = r1[i][q1];
+        }
+    }
+    __syncthreads();
+    // ---- forward along y, active columns, into the sticks (the next band's columns are this wave's own) ----
+    for (int c0 = wv * LPW; c0 < n1a; c0 += NW * LPW) {
+      const int xa = min(c0 + l, n1a - 1);
+      const bool act = on && c0 + l < n1a;
+      cplx<T> r1[I1][A], r2[J2][B];
+#pragma unroll
+      for (int i = 0; i < I1; ++i) {
+        const int n2 = S::has1(t, i) ? t + TT * i : 0;
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) r1[i][n1] = plane[S::at(B * n1 + n2, xa)];
+        SmallDft<T, A, -1>::run(r1[i]);
+      }
+      twiddle1(r1, false);
+      col_exchange(r1, r2, xa, act);
+      const int cs = colstart[xa], m = act ? (colstart[xa + 1] - cs - 1) >> 1 : -1;
+#pragma unroll
+      for (int j = 0; j < J2; ++j) {
+        SmallDft<T, B, -1>::run(r2[j]);
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) {
+          const int e = t + TT * j + A * k2;
+          const int n2 = 2 * e < N ? e : e - N;
+          if (n2 <= m && -n2 <= m && S::has2(t, j)) sb[cs + n2 + m] = cscale<T>(r2[j][k2], scale);
+        }
+      }
+    }
+  };
+  if constexpr (S::LOOP) {
+    for (int b = blockIdx.y; b < nbatch; b += gridDim.y) one_band(b);
+  } else {
+    one_band(blockIdx.y);
   }
 }
 
@@ -361,7 +401,7 @@ __device__ __forceinline__ void rs_add_regs(float2 (&r)[16], const RsDesc& rd, i
 }
 
 // ---- 128 x 128 FP32 planes with wave-local lines ---------------------------------------------
-// The same transform as k_plane_n (inverse along y on the active columns, inverse along x, * V,
+// The same transform as k_plane_w (inverse along y on the active columns, inverse along x, * V,
 // forward along x, forward along y on the active columns), arranged so that the 8 threads of a
 // line sit in one wave: the exchange between the two stages of a line is ordered by the wave
 // itself and needs no workgroup barrier, and the plane needs no zero fill, scatter or gather:
@@ -1197,78 +1237,79 @@ template hipError_t launch_sticks_fwd_n<float>(const cplx<float>*, cplx<float>*,
 template hipError_t launch_sticks_fwd_n<double>(const cplx<double>*, cplx<double>*, long, int, const Stick*,
                                                 const GridDesc&, const cplx<double>*, hipStream_t);
 
-// Sizes with a compile-time plane kernel: N = A B and threads per block.
-template <typename T>
-static bool launch_plane_n_sized(int N, cplx<T>* SB, const T* V, int nbatch, const Stick* st, const GridDesc& g,
-                                 const cplx<T>* tw, T scale, hipStream_t s, hipError_t* err) {
-  dim3 grid(g.n3, nbatch);
-  const size_t lds = (size_t)(N * (N + 1) + N) * sizeof(cplx<T>);
-#define PW_PLANE_CASE(NN, AA, BB, NTT)                                                                   \
-  case NN:                                                                                               \
-    hipLaunchKernelGGL((k_plane_n<T, AA, BB, NTT>), grid, dim3(NTT), lds, s, SB, V, st, g, tw, scale); \
-    *err = hipGetLastError();                                                                            \
-    return true;
-  switch (N) {
-    PW_PLANE_CASE(24, 4, 6, 256)
-    PW_PLANE_CASE(27, 3, 9, 256)
-    PW_PLANE_CASE(32, 4, 8, 256)
-    PW_PLANE_CASE(48, 4, 12, 256)
-    PW_PLANE_CASE(54, 6, 9, 256)
-    PW_PLANE_CASE(64, 8, 8, 512)
-    PW_PLANE_CASE(81, 9, 9, 768)
-    PW_PLANE_CASE(96, 8, 12, 512)
-    PW_PLANE_CASE(128, 8, 16, 1024)
-    default:
-      return false;
-  }
-#undef PW_PLANE_CASE
+// Sizes with a compile-time plane kernel, N = A B; 108 in FP32 only (its FP64 plane exceeds LDS).
+#define PW_PLANE_SIZES(X) \
+  X(24, 4, 6) X(27, 3, 9) X(32, 4, 8) X(48, 4, 12) X(54, 6, 9) X(64, 8, 8) X(81, 9, 9) X(96, 8, 12)
+
+template <typename T, int A, int B>
+static hipError_t launch_plane_w(cplx<T>* SB, const T* V, int nbatch, const int* colstart, const GridDesc& g,
+                                 const cplx<T>* tw, T scale, hipStream_t s) {
+  using S = PlaneShape<T, A, B>;
+  // LOOP: two rounds of the workgroups a device holds (16 waves per CU at these register counts)
+  const int per_cu = std::max(1, std::min((int)(160 * 1024 / S::LDS), 16 / S::NW));
+  const int groups = S::LOOP ? std::max(1, std::min(nbatch, 2 * 256 * per_cu / g.n3)) : nbatch;
+  hipLaunchKernelGGL((k_plane_w<T, A, B>), dim3(g.n3, groups), dim3(64 * S::NW), S::LDS, s, SB, V, colstart, g, tw,
+                     scale, nbatch);
+  return hipGetLastError();
 }
 
 bool plane_n_supported(int n1, int n2, int real_bytes, size_t max_lds) {
   if (n1 != n2) return false;
+  size_t lds = 0;
   switch (n1) {
-    case 24: case 27: case 32: case 48: case 54: case 64: case 81: case 96: case 128:
+#define PW_CASE(NN, AA, BB)                                                                     \
+  case NN:                                                                                      \
+    lds = real_bytes == 4 ? PlaneShape<float, AA, BB>::LDS : PlaneShape<double, AA, BB>::LDS;   \
+    break;
+    PW_PLANE_SIZES(PW_CASE)
+#undef PW_CASE
+    case 108:
+      if (real_bytes != 4) return false;
+      lds = PlaneShape<float, 6, 18>::LDS;
+      break;
+    case 128:
+      lds = (size_t)(128 * 128 + 128) * 2 * real_bytes;
       break;
     default:
       return false;
   }
-  const size_t lds = (size_t)(n1 * (n1 + 1) + n1) * 2 * real_bytes;
   return lds <= max_lds;
 }
 
 template <typename T>
-hipError_t launch_plane_n(cplx<T>* SB, const T* V, int nbatch, const Stick* st, const int* colstart,
-                          const GridDesc& g, const cplx<T>* tw, T scale, hipStream_t s) {
+hipError_t launch_plane_n(cplx<T>* SB, const T* V, int nbatch, const int* colstart, const GridDesc& g,
+                          const cplx<T>* tw, T scale, hipStream_t s) {
   if constexpr (std::is_same<T, float>::value) {
-    if (g.n1 == 128 && g.n2 == 128 && g.n1a <= 128) {
+    if (g.n1 == 128) {
       const size_t lds = (size_t)(128 * 128 + 128) * sizeof(float2);
       hipLaunchKernelGGL(k_plane128<false>, dim3(g.n3, nbatch), dim3(1024), lds, s, SB, V, colstart, g, tw, scale,
                          RsDesc{}, (const float2*)nullptr, 0);
       return hipGetLastError();
     }
+    if (g.n1 == 108) return launch_plane_w<T, 6, 18>(SB, V, nbatch, colstart, g, tw, scale, s);
   }
-  hipError_t e = hipErrorInvalidValue;
-  if (!launch_plane_n_sized<T>(g.n1, SB, V, nbatch, st, g, tw, scale, s, &e)) return hipErrorInvalidValue;
-  return e;
+  switch (g.n1) {
+#define PW_CASE(NN, AA, BB) \
+  case NN:                  \
+    return launch_plane_w<T, AA, BB>(SB, V, nbatch, colstart, g, tw, scale, s);
+    PW_PLANE_SIZES(PW_CASE)
+#undef PW_CASE
+    default:
+      return hipErrorInvalidValue;
+  }
 }
 
 void pw_allow_large_lds_plane_n() {
   const int bytes = (int)(160 * 1024);
-#define PW_ALLOW(AA, BB, NTT)                                                                                    \
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane_n<float, AA, BB, NTT>),                      \
+#define PW_ALLOW(NN, AA, BB)                                                                                     \
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane_w<float, AA, BB>),                           \
                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);                                 \
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane_n<double, AA, BB, NTT>),                     \
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane_w<double, AA, BB>),                          \
                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  PW_ALLOW(4, 6, 256)
-  PW_ALLOW(3, 9, 256)
-  PW_ALLOW(4, 8, 256)
-  PW_ALLOW(4, 12, 256)
-  PW_ALLOW(6, 9, 256)
-  PW_ALLOW(8, 8, 512)
-  PW_ALLOW(9, 9, 768)
-  PW_ALLOW(8, 12, 512)
-  PW_ALLOW(8, 16, 1024)
+  PW_PLANE_SIZES(PW_ALLOW)
 #undef PW_ALLOW
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane_w<float, 6, 18>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane128<false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane128<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1279,9 +1320,9 @@ void pw_allow_large_lds_plane_n() {
                             bytes);
 }
 
-template hipError_t launch_plane_n<float>(cplx<float>*, const float*, int, const Stick*, const int*,
-                                          const GridDesc&, const cplx<float>*, float, hipStream_t);
-template hipError_t launch_plane_n<double>(cplx<double>*, const double*, int, const Stick*, const int*,
-                                           const GridDesc&, const cplx<double>*, double, hipStream_t);
+template hipError_t launch_plane_n<float>(cplx<float>*, const float*, int, const int*, const GridDesc&,
+                                          const cplx<float>*, float, hipStream_t);
+template hipError_t launch_plane_n<double>(cplx<double>*, const double*, int, const int*, const GridDesc&,
+                                           const cplx<double>*, double, hipStream_t);
 
 }  // namespace pw

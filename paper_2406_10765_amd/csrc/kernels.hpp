@@ -14,7 +14,7 @@ struct FftLaunch {
   bool sized_sticks;  // z transforms with a compile-time size kernel
   // pencil form with compile-time line lengths: planes that do not fit in LDS, and the others without a
   // sized fused kernel (unequal sides).  A sized fused plane moves a quarter of the bytes and stays ahead
-  // (64^2, 144 bands, FP32: 126 against 236 us; 96^2, 128 bands, FP64: 1,314 against 1,341 us)
+  // (64^2, 144 bands, FP32: 109 against 236 us; 96^2, 128 bands, FP64: 1,093 against 1,341 us)
   bool pencil_n;
   int pitch;          // its row pitch of G1: n1a rounded up to whole 128-byte lines
   int plane_thr;
@@ -48,8 +48,8 @@ bool plane_n_supported(int n1, int n2, int real_bytes, size_t max_lds);
 // colstart: first stick of each active column xa = n1 + n1max (n1a + 1 entries; a column's sticks
 // run over n2 = -m .. m in order).
 template <typename T>
-hipError_t launch_plane_n(cplx<T>* SB, const T* V, int nbatch, const Stick* st, const int* colstart,
-                          const GridDesc& g, const cplx<T>* tw, T scale, hipStream_t s);
+hipError_t launch_plane_n(cplx<T>* SB, const T* V, int nbatch, const int* colstart, const GridDesc& g,
+                          const cplx<T>* tw, T scale, hipStream_t s);
 void pw_allow_large_lds_plane_n();
 // Real-space projectors on 128 x 128 FP32 planes (sticks in SB as for the plane pass).
 // Inverse pass: the projections of nbatch bands, one partial of 4 complex sums per band and

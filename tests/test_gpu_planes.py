@@ -1,5 +1,5 @@
-"""Sized pencil form of the plane stage (planes with unequal sides, FP64 planes beyond LDS) against the
-oracle: H X and the charge density with every compiled line length along x and along y, several bands
+"""Plane stage of the 3D FFTs: the sized pencil form (planes with unequal sides, FP64 planes beyond
+LDS) and square planes inside LDS against the oracle: H X and the charge density with every compiled line length along x and along y, several bands
 per wave, and the allocation-free entry point where the pencil intermediate does and does not fit its
 work array.  Tolerances as elsewhere: H X 1e-12 (FP64) and 2e-5 (FP32) of max|HX|, density 1e-12 and
 1e-5 of its maximum."""
@@ -63,6 +63,22 @@ def test_several_bands_per_wave_and_groups(prec, nb):
     print("pencil bands", nb, "prec", prec, "H X", err, "density", derr, flush=True)
     assert err < (1e-12 if prec == pw.PW_FP64 else 2e-5)
     assert derr < (1e-12 if prec == pw.PW_FP64 else 1e-5)
+    h.close()
+
+
+@pytest.mark.parametrize("n,prec,nb", [(24, pw.PW_MIXED, 5), (27, pw.PW_FP64, 5), (64, pw.PW_MIXED, 37), (81, pw.PW_FP64, 13),
+                                       (96, pw.PW_MIXED, 11), (96, pw.PW_FP64, 3), (108, pw.PW_MIXED, 5)])
+def test_square_planes_of_several_bands(n, prec, nb):
+    # planes inside LDS; 64, 96, 108 (FP32) and 81, 96 (FP64) take the bands of a plane in groups
+    m, h, p = model_and_handle(synth.make_cell("si8", modes=True), prec, nb, (n, n, 24))
+    assert h.info.fused_planes == 1
+    X = synth.random_block(m.npw, nb, n)
+    if prec == pw.PW_MIXED:
+        X = X.astype(np.complex64).astype(np.complex128)
+    ref = O.apply_h(m, X)[p]
+    err = float(np.abs(h.to_host(h.apply_h(h.to_device(X[p]))) - ref).max() / np.abs(ref).max())
+    print("square plane", n, "prec", prec, "nb", nb, "H X", err, flush=True)
+    assert err < (1e-12 if prec == pw.PW_FP64 else 2e-5)
     h.close()
 
 
