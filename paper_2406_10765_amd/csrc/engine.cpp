@@ -357,12 +357,12 @@ struct Engine {
   }
 
   hipError_t cn(bool split16, const cplx<T>* A, long lda, const cplx<T>* B, long ldb, const cplx<T>* B2, long ldb2,
-                int ncol1, int M, int N, int K, int nsplit, double2* part, int nterm = 3) {
+                int ncol1, int M, int N, int K, int nsplit, double2* part, int nterm = 3, int herm_cols = 0) {
     if constexpr (std::is_same<T, float>::value) {
       if (split16)
         return launch_gemm_cn_bf16x3(A, lda, B, ldb, B2, ldb2, ncol1, M, N, K, nsplit, part, nterm, h->stream);
     }
-    return launch_gemm_cn<T>(A, lda, B, ldb, B2, ldb2, ncol1, M, N, K, nsplit, part, h->stream);
+    return launch_gemm_cn<T>(A, lda, B, ldb, B2, ldb2, ncol1, M, N, K, nsplit, part, h->stream, herm_cols);
   }
   hipError_t nn(bool split16, const cplx<T>* A, long lda, const cplx<T>* B, long ldb, int M, int N, int K,
                 cplx<T>* out, long ldo, const EpiH& e) {
@@ -831,9 +831,10 @@ struct Engine {
         return dense_solve(nb, P.nsplit_gram, 0.0, true);
       }
     }
-    PW_TIMED(PW_PH_GRAM, cn(flag(PW_FLAG_BF16_GRAM), Y, ldy, Y, ldy, W, ldw, nb, nb, 2 * nb, P.npw, P.nsplit_gram,
-                            parts, 4));
-    return dense_solve(nb, P.nsplit_gram);
+    const bool g16 = flag(PW_FLAG_BF16_GRAM), upper = !g16 && nb > 48;  // one tile row has no tile below the diagonal
+    PW_TIMED(PW_PH_GRAM, cn(g16, Y, ldy, Y, ldy, W, ldw, nb, nb, 2 * nb, P.npw, P.nsplit_gram, parts, 4,
+                            upper ? nb : 0));
+    return dense_solve(nb, P.nsplit_gram, 0.0, upper);
   }
 
   // Sum the split-K partials of [S | H_s] (n x 2n), take Hermitian parts, and solve

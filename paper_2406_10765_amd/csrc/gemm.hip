@@ -21,12 +21,13 @@
 // of lane l holds C[4 (l / 16) + r][l % 16] for f32 but C[l / 16 + 4 r][l % 16]
 // for f64 (measured with one-hot operands on gfx950).
 //
-// Structure of one workgroup (4 waves in a 2 x 2 arrangement): global loads of
-// the next K tile go to registers (16-byte loads where the leading dimension
-// allows) while the MFMAs run on the current tile; the tiles live in two LDS
-// buffers, so each K tile costs one barrier.  Tiles are handed out XCD by XCD:
-// consecutive tiles, which share operand panels, run on the same L2.
+// The complex products read their operands from global memory straight into the lanes' MFMA layout,
+// a wave per tile, with no LDS and no barrier between waves (below); the products on pairs go
+// through two LDS buffers, so each K tile costs one barrier, with the next one's global loads in
+// registers meanwhile.  Tiles are handed out XCD by XCD: consecutive tiles, which share operand
+// panels, run on the same L2.
 
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -53,20 +54,8 @@ template <> struct MF<float> {
   static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
 };
 
-constexpr int kBK = 16;     // K per tile (complex elements)
-constexpr int kFlush = 16;  // fp32 cn: K tiles per move into fp64 registers
-constexpr int kXcd = 8;     // XCDs per MI355X
-
-// 16 bytes = U complex elements (U = 2 for fp32, 1 for fp64)
-template <typename T> struct Vec16;
-template <> struct Vec16<float> {
-  using type = float4;
-  static constexpr int U = 2;
-};
-template <> struct Vec16<double> {
-  using type = double2;
-  static constexpr int U = 1;
-};
+constexpr int kBK = 16;  // projectors per K tile of the nonlocal product on pairs
+constexpr int kXcd = 8;  // XCDs per MI355X
 
 // Tile index -> (tm, tn, split) with the tiles of one XCD contiguous.  Launch order
 // sends workgroup w to XCD w % 8.
@@ -77,232 +66,150 @@ __device__ __forceinline__ int xcd_tile(int w, int total) {
   return x < rem ? x * (per + 1) + i : rem * (per + 1) + (x - rem) * per + i;
 }
 
-// Loader of a K-contiguous operand panel: kBK values of NC columns starting at (k0, c0).
-// Element (k, c) goes to S[k * LDS_LD + c].
-template <typename T, int NC, bool VEC>
-struct KcLoader {
-  static constexpr int U = VEC ? Vec16<T>::U : 1;
-  static constexpr int UNITS = kBK / U * NC;  // loads per tile
-  static constexpr int PER = (UNITS + 255) / 256;
-  cplx<T> r[PER][U];
-  __device__ __forceinline__ void load(const cplx<T>* __restrict__ P, long ld, const cplx<T>* __restrict__ P2, long ld2,
-                                       int ncol1, int ncols, int c0, int k0, int kend, int tid) {
+// K value u of lane group q (0..3) among the eight of a step: whole 64-byte pieces of a column per load in
+// fp64, 16-byte loads in fp32
+template <typename T>
+__device__ __forceinline__ constexpr int koff(int q, int u) { return std::is_same<T, double>::value ? 4 * u + q : 2 * q + u; }
+// ------------------------------------------------------------------------------------------
+// Complex products, one wave per tile of 16 WA x 16 WB: each lane loads its own operands of eight K values
+// (two of each column or row, so 128-byte lines in fp64) from global memory and the next eight are in flight
+// under the products of the present ones.  Bound by the matrix cores (64 cycles per fp64 instruction, two
+// waves on a SIMD): no barrier stops a wave, narrow tiles leave little padding and fill the last round, and
+// the loads (13 bytes a cycle and compute unit at 2 x 3 blocks) stay far below what the caches give.
+// ------------------------------------------------------------------------------------------
+template <typename T, int WA, int WB, bool CONJ>
+__device__ __forceinline__ void mma_step(const cplx<T> (&av)[WA][2], const cplx<T> (&bv)[WB][2],
+                                         typename MF<T>::acc (&cr)[WA][WB], typename MF<T>::acc (&ci)[WA][WB]) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int idx = tid + q * 256;
-      const int ku = idx % (kBK / U), c = idx / (kBK / U);
-      const int gc = c0 + c, gk = k0 + ku * U;
+  for (int u = 0; u < 2; ++u) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) r[q][u] = mk<T>(0, 0);
-      if (idx < UNITS && gc < ncols) {
-        const cplx<T>* col = gc < ncol1 ? P + (long)gc * ld : P2 + (long)(gc - ncol1) * ld2;
-        if (VEC && gk + U <= kend) {
-          const typename Vec16<T>::type v = *reinterpret_cast<const typename Vec16<T>::type*>(col + gk);
-          if constexpr (std::is_same<T, float>::value) {
-            r[q][0] = mk<T>(v.x, v.y);
-            r[q][U - 1] = mk<T>(v.z, v.w);
-          } else {
-            r[q][0] = mk<T>(v.x, v.y);
-          }
-        } else {
+    for (int a = 0; a < WA; ++a)
 #pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (gk + u < kend) r[q][u] = col[gk + u];
-        }
+      for (int b = 0; b < WB; ++b) {
+        cr[a][b] = MF<T>::mma(av[a][u].x, bv[b][u].x, cr[a][b]);
+        ci[a][b] = MF<T>::mma(av[a][u].x, bv[b][u].y, ci[a][b]);
       }
-    }
-  }
-  template <int LDS_LD>
-  __device__ __forceinline__ void store(cplx<T>* S, int tid) const {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int idx = tid + q * 256;
-      if (idx < UNITS) {
-        const int ku = idx % (kBK / U), c = idx / (kBK / U);
+    for (int a = 0; a < WA; ++a) {
+      const T y = CONJ ? av[a][u].y : -av[a][u].y;
 #pragma unroll
-        for (int u = 0; u < U; ++u) S[(ku * U + u) * LDS_LD + c] = r[q][u];
+      for (int b = 0; b < WB; ++b) {
+        cr[a][b] = MF<T>::mma(y, bv[b][u].y, cr[a][b]);
+        ci[a][b] = MF<T>::mma(-y, bv[b][u].x, ci[a][b]);
       }
-    }
-  }
-};
-
-// Loader of an M-contiguous operand panel (nn A): NR rows x kBK columns of a column-major matrix.
-template <typename T, int NR, bool VEC>
-struct McLoader {
-  static constexpr int U = VEC ? Vec16<T>::U : 1;
-  static constexpr int UNITS = NR / U * kBK;
-  static constexpr int PER = (UNITS + 255) / 256;
-  cplx<T> r[PER][U];
-  __device__ __forceinline__ void load(const cplx<T>* __restrict__ P, long ld, int nrows, int r0, int k0, int kend,
-                                       int tid) {
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int idx = tid + q * 256;
-      const int mu = idx % (NR / U), k = idx / (NR / U);
-      const int gm = r0 + mu * U, gk = k0 + k;
-#pragma unroll
-      for (int u = 0; u < U; ++u) r[q][u] = mk<T>(0, 0);
-      if (idx < UNITS && gk < kend) {
-        const cplx<T>* col = P + (long)gk * ld;
-        if (VEC && gm + U <= nrows) {
-          const typename Vec16<T>::type v = *reinterpret_cast<const typename Vec16<T>::type*>(col + gm);
-          if constexpr (std::is_same<T, float>::value) {
-            r[q][0] = mk<T>(v.x, v.y);
-            r[q][U - 1] = mk<T>(v.z, v.w);
-          } else {
-            r[q][0] = mk<T>(v.x, v.y);
-          }
-        } else {
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (gm + u < nrows) r[q][u] = col[gm + u];
-        }
-      }
-    }
-  }
-  template <int LDS_LD>
-  __device__ __forceinline__ void store(cplx<T>* S, int tid) const {
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int idx = tid + q * 256;
-      if (idx < UNITS) {
-        const int mu = idx % (NR / U), k = idx / (NR / U);
-#pragma unroll
-        for (int u = 0; u < U; ++u) S[k * LDS_LD + mu * U + u] = r[q][u];
-      }
-    }
-  }
-};
-
-// Wave-level MFMA accumulation over one K tile held in LDS.
-// sA: kBK x (BM + 1) (m contiguous), sB: kBK x (BN + 1) (n contiguous).
-template <typename T, int WBM, int WBN, bool CONJ_A>
-__device__ __forceinline__ void mma_tile(const cplx<T>* sA, const cplx<T>* sB, int lda_s, int ldb_s, int mo, int no,
-                                         int lane, typename MF<T>::acc (&cr)[WBM][WBN],
-                                         typename MF<T>::acc (&ci)[WBM][WBN]) {
-#pragma unroll
-  for (int kk = 0; kk < kBK; kk += 4) {
-    cplx<T> av[WBM], bv[WBN];
-    const int kr = kk + (lane >> 4);
-#pragma unroll
-    for (int a = 0; a < WBM; ++a) av[a] = sA[kr * lda_s + mo + a * 16 + (lane & 15)];
-#pragma unroll
-    for (int b = 0; b < WBN; ++b) bv[b] = sB[kr * ldb_s + no + b * 16 + (lane & 15)];
-#pragma unroll
-    for (int a = 0; a < WBM; ++a)
-#pragma unroll
-      for (int b = 0; b < WBN; ++b) cr[a][b] = MF<T>::mma(av[a].x, bv[b].x, cr[a][b]);
-#pragma unroll
-    for (int a = 0; a < WBM; ++a)
-#pragma unroll
-      for (int b = 0; b < WBN; ++b) ci[a][b] = MF<T>::mma(av[a].x, bv[b].y, ci[a][b]);
-#pragma unroll
-    for (int a = 0; a < WBM; ++a) {
-      const T ai = CONJ_A ? av[a].y : -av[a].y;
-#pragma unroll
-      for (int b = 0; b < WBN; ++b) cr[a][b] = MF<T>::mma(ai, bv[b].y, cr[a][b]);
-    }
-#pragma unroll
-    for (int a = 0; a < WBM; ++a) {
-      const T ai = CONJ_A ? -av[a].y : av[a].y;
-#pragma unroll
-      for (int b = 0; b < WBN; ++b) ci[a][b] = MF<T>::mma(ai, bv[b].x, ci[a][b]);
     }
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// cn: part[s] = A^H B over K chunk s.  Workgroup tile BM x BN (waves 2 x 2).
-// ------------------------------------------------------------------------------------------
-template <typename T, int BM, int BN, bool VEC>
-__global__ __launch_bounds__(256) void k_gemm_cn(const cplx<T>* __restrict__ A, long lda,
-                                                 const cplx<T>* __restrict__ B, long ldb,
-                                                 const cplx<T>* __restrict__ B2, long ldb2, int ncol1, int M, int N,
-                                                 int K, int kchunk, int tiles_m, int tiles_n,
-                                                 double2* __restrict__ part) {
-  constexpr int WBM = BM / 32, WBN = BN / 32;  // 16x16 blocks per wave
-  constexpr int LA = BM + 1, LB = BN + 1;
+// cn: part[s] = A^H B over K chunk s, a quarter of the chunk per wave, the four waves' tiles summed in LDS.
+// herm > 0: the first herm columns of B are A itself; tiles of that Gram block wholly below its diagonal are
+// left out.  [S | H_s] of 144 bands over 37,073 plane waves in fp64: 195 us; 64 x 64 tiles through LDS
+// took 377 us.
+template <typename T, int WA, int WB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_cn(
+    const cplx<T>* __restrict__ A, long lda, const cplx<T>* __restrict__ B, long ldb, const cplx<T>* __restrict__ B2,
+    long ldb2, int ncol1, int M, int N, int K, int kchunk, int tiles_m, int tiles_n, double2* __restrict__ part,
+    int herm) {
+  constexpr bool F32 = std::is_same<T, float>::value;
+  constexpr int FLUSH = 32;  // fp32: steps of eight K values per move into fp64 registers
   using acc_t = typename MF<T>::acc;
-  __shared__ cplx<T> sA[2][kBK * LA];
-  __shared__ cplx<T> sB[2][kBK * LB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nsplit = gridDim.x / (tiles_m * tiles_n);
+  __shared__ double2 red[2][4][256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, q = lane >> 4;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
   // tiles of one split are contiguous; inside a split, n fastest
   const int sp = t / (tiles_m * tiles_n);
   const int tr = t - sp * tiles_m * tiles_n;
   const int tm = tr / tiles_n, tn = tr - tm * tiles_n;
-  (void)nsplit;
-  const int i0 = tm * BM, j0 = tn * BN;
-  const int kb = sp * kchunk, ke = min(K, kb + kchunk);
-  const int mo = (wave & 1) * (BM / 2), no = (wave >> 1) * (BN / 2);
-  acc_t cr[WBM][WBN], ci[WBM][WBN];
-  double dr[WBM][WBN][4], di[WBM][WBN][4];
+  const int i0 = tm * 16 * WA, j0 = tn * 16 * WB;
+  if (j0 + 16 * WB <= herm && i0 >= j0 + 16 * WB) return;
+  const int kb = sp * kchunk + wave * (kchunk / 4), ke = min(K, kb + kchunk / 4);
+  const cplx<T>*pa[WA], *pb[WB];
 #pragma unroll
-  for (int a = 0; a < WBM; ++a)
+  for (int a = 0; a < WA; ++a) pa[a] = A + (long)min(i0 + a * 16 + i, M - 1) * lda + kb + koff<T>(q, 0);
 #pragma unroll
-    for (int b = 0; b < WBN; ++b) {
-      cr[a][b] = acc_t{0, 0, 0, 0};
-      ci[a][b] = acc_t{0, 0, 0, 0};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) dr[a][b][r] = di[a][b][r] = 0.0;
-    }
-  KcLoader<T, BM, VEC> la;
-  KcLoader<T, BN, VEC> lb;
-  const int ntiles = ke > kb ? (ke - kb + kBK - 1) / kBK : 0;
-  if (ntiles > 0) {
-    la.load(A, lda, A, lda, M, M, i0, kb, ke, tid);
-    lb.load(B, ldb, B2, ldb2, ncol1, N, j0, kb, ke, tid);
-    la.template store<LA>(sA[0], tid);
-    lb.template store<LB>(sB[0], tid);
+  for (int b = 0; b < WB; ++b) {
+    const int c = min(j0 + b * 16 + i, N - 1);
+    pb[b] = (c < ncol1 ? B + (long)c * ldb : B2 + (long)(c - ncol1) * ldb2) + kb + koff<T>(q, 0);
   }
-  __syncthreads();
-  for (int it = 0; it < ntiles; ++it) {
-    const int cur = it & 1;
-    const bool more = it + 1 < ntiles;
-    if (more) {
-      const int kn = kb + (it + 1) * kBK;
-      la.load(A, lda, A, lda, M, M, i0, kn, ke, tid);
-      lb.load(B, ldb, B2, ldb2, ncol1, N, j0, kn, ke, tid);
+  acc_t cr[WA][WB], ci[WA][WB];
+  double dr[F32 ? WA : 1][F32 ? WB : 1][4] = {}, di[F32 ? WA : 1][F32 ? WB : 1][4] = {};
+#pragma unroll
+  for (int a = 0; a < WA; ++a)
+#pragma unroll
+    for (int b = 0; b < WB; ++b) cr[a][b] = ci[a][b] = acc_t{0, 0, 0, 0};
+  cplx<T> a0[WA][2], b0[WB][2], a1[WA][2], b1[WB][2];
+  auto load = [&](cplx<T>(&av)[WA][2], cplx<T>(&bv)[WB][2], int s) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int a = 0; a < WA; ++a) av[a][u] = pa[a][8 * (long)s + koff<T>(0, u)];
+#pragma unroll
+      for (int b = 0; b < WB; ++b) bv[b][u] = pb[b][8 * (long)s + koff<T>(0, u)];
     }
-    mma_tile<T, WBM, WBN, true>(sA[cur], sB[cur], LA, LB, mo, no, lane, cr, ci);
-    if constexpr (std::is_same<T, float>::value) {
-      if ((it % kFlush) == kFlush - 1) {
+  };
+  auto flush = [&]() {
+    if constexpr (F32) {
 #pragma unroll
-        for (int a = 0; a < WBM; ++a)
+      for (int a = 0; a < WA; ++a)
 #pragma unroll
-          for (int b = 0; b < WBN; ++b) {
+        for (int b = 0; b < WB; ++b) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              dr[a][b][r] += (double)cr[a][b][r];
-              di[a][b][r] += (double)ci[a][b][r];
-            }
-            cr[a][b] = acc_t{0, 0, 0, 0};
-            ci[a][b] = acc_t{0, 0, 0, 0};
+          for (int r = 0; r < 4; ++r) {
+            dr[a][b][r] += (double)cr[a][b][r];
+            di[a][b][r] += (double)ci[a][b][r];
           }
-      }
+          cr[a][b] = ci[a][b] = acc_t{0, 0, 0, 0};
+        }
     }
-    if (more) {
-      la.template store<LA>(sA[cur ^ 1], tid);
-      lb.template store<LB>(sB[cur ^ 1], tid);
-    }
-    __syncthreads();
+  };
+  const int full = ke > kb ? (ke - kb) / 8 : 0;
+  if (full > 0) load(a0, b0, 0);
+  int s = 0;
+  for (; s + 1 < full; s += 2) {
+    load(a1, b1, s + 1);
+    mma_step<T, WA, WB, true>(a0, b0, cr, ci);
+    load(a0, b0, min(s + 2, full - 1));
+    mma_step<T, WA, WB, true>(a1, b1, cr, ci);
+    if (F32 && (s % FLUSH) == FLUSH - 2) flush();
   }
+  if (s < full) mma_step<T, WA, WB, true>(a0, b0, cr, ci);
+  if (kb + 8 * full < ke) {  // the last K values, zeros behind them
 #pragma unroll
-  for (int a = 0; a < WBM; ++a)
+    for (int u = 0; u < 2; ++u) {
+      const bool in = kb + 8 * full + koff<T>(q, u) < ke;
 #pragma unroll
-    for (int b = 0; b < WBN; ++b) {
-      const int col = j0 + no + b * 16 + (lane & 15);
+      for (int a = 0; a < WA; ++a) a1[a][u] = in ? pa[a][8 * (long)full + koff<T>(0, u)] : mk<T>(0, 0);
+#pragma unroll
+      for (int b = 0; b < WB; ++b) b1[b][u] = in ? pb[b][8 * (long)full + koff<T>(0, u)] : mk<T>(0, 0);
+    }
+    mma_step<T, WA, WB, true>(a1, b1, cr, ci);
+  }
+  // thread (row, column) of a block: accumulator element and lane that hold it
+  const int row = tid & 15, col = tid >> 4;
+  const int slot = F32 ? (row & 3) * 64 + (row >> 2) * 16 + col : (row >> 2) * 64 + (row & 3) * 16 + col;
+#pragma unroll
+  for (int a = 0; a < WA; ++a)
+#pragma unroll
+    for (int b = 0; b < WB; ++b) {
+      const int buf = (a * WB + b) & 1;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = i0 + mo + a * 16 + MF<T>::row(lane, r);
-        if (row < M && col < N) {
-          double2 v;
-          v.x = dr[a][b][r] + (double)cr[a][b][r];
-          v.y = di[a][b][r] + (double)ci[a][b][r];
-          part[((long)sp * N + col) * M + row] = v;
+        double2 v = make_double2((double)cr[a][b][r], (double)ci[a][b][r]);
+        if constexpr (F32) {
+          v.x += dr[a][b][r];
+          v.y += di[a][b][r];
         }
+        red[buf][wave][r * 64 + lane] = v;
       }
+      __syncthreads();
+      double2 v = red[buf][0][slot];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) {
+        v.x += red[buf][w][slot].x;
+        v.y += red[buf][w][slot].y;
+      }
+      const int gi = i0 + a * 16 + row, gj = j0 + b * 16 + col;
+      if (gi < M && gj < N) part[((long)sp * N + gj) * M + gi] = v;
     }
 }
 
@@ -312,12 +219,7 @@ __global__ void k_reduce_parts(const double2* __restrict__ part, int nsplit, int
                                long ldo64, cplx<T>* __restrict__ outT, long ldoT) {
   PW_GRID_STRIDE(idx, (long)M * N) {
     const int j = (int)(idx / M), i = (int)(idx - (long)j * M);
-    double2 s = part[idx];
-    for (int p = 1; p < nsplit; ++p) {
-      const double2 v = part[(long)p * M * N + idx];
-      s.x += v.x;
-      s.y += v.y;
-    }
+    double2 s = sum_splits(part + idx, nsplit, (long)M * N);
     if (dscale) {
       const double d = dscale[i % dper];
       s.x *= d;
@@ -328,67 +230,72 @@ __global__ void k_reduce_parts(const double2* __restrict__ part, int nsplit, int
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// nn: out = epilogue(A B).  A: M x K (m contiguous), B: K x N (k contiguous).
-// ------------------------------------------------------------------------------------------
-template <typename T, int BM, int BN, bool VEC>
-__global__ __launch_bounds__(256) void k_gemm_nn(const cplx<T>* __restrict__ A, long lda,
-                                                 const cplx<T>* __restrict__ B, long ldb, int M, int N, int K,
-                                                 int tiles_n, cplx<T>* out, long ldo, EpiH e) {
-  constexpr int WBM = BM / 32, WBN = BN / 32;
-  constexpr int LA = BM + 1, LB = BN + 1;
+// nn: out = A B (+ Zl in mode 2).  A: M x K (m contiguous), B: K x N (k contiguous).  The four waves of a
+// workgroup share their columns.  The product is formed transposed, so that sixteen lanes hold consecutive
+// rows and the stores are whole lines.  37,073 x 144 x 144 in fp64: 100 us; 128 x 64 tiles through LDS,
+// one workgroup per compute unit, took 212 us.
+template <typename T, int WA, int WB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_nn(
+    const cplx<T>* __restrict__ A, long lda, const cplx<T>* __restrict__ B, long ldb, int M, int N, int K, int tiles_n,
+    cplx<T>* out, long ldo, EpiH e) {
   using acc_t = typename MF<T>::acc;
-  __shared__ cplx<T> sA[2][kBK * LA];
-  __shared__ cplx<T> sB[2][kBK * LB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, q = lane >> 4;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
   const int tm = t / tiles_n, tn = t - tm * tiles_n;  // n fastest: workgroups sharing an A panel are adjacent
-  const int i0 = tm * BM, j0 = tn * BN;
-  const int mo = (wave & 1) * (BM / 2), no = (wave >> 1) * (BN / 2);
-  acc_t cr[WBM][WBN], ci[WBM][WBN];
+  const int i0 = (tm * 4 + wave) * 16 * WA, j0 = tn * 16 * WB;
+  if (i0 >= M) return;
+  const cplx<T>*pa[WA], *pb[WB];
 #pragma unroll
-  for (int a = 0; a < WBM; ++a)
+  for (int a = 0; a < WA; ++a) pa[a] = A + koff<T>(q, 0) * lda + min(i0 + a * 16 + i, M - 1);
 #pragma unroll
-    for (int b = 0; b < WBN; ++b) {
-      cr[a][b] = acc_t{0, 0, 0, 0};
-      ci[a][b] = acc_t{0, 0, 0, 0};
+  for (int b = 0; b < WB; ++b) pb[b] = B + (long)min(j0 + b * 16 + i, N - 1) * ldb + koff<T>(q, 0);
+  acc_t cr[WB][WA], ci[WB][WA];
+#pragma unroll
+  for (int b = 0; b < WB; ++b)
+#pragma unroll
+    for (int a = 0; a < WA; ++a) cr[b][a] = ci[b][a] = acc_t{0, 0, 0, 0};
+  cplx<T> a0[WA][2], b0[WB][2], a1[WA][2], b1[WB][2];
+  auto load = [&](cplx<T>(&av)[WA][2], cplx<T>(&bv)[WB][2], int s) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int a = 0; a < WA; ++a) av[a][u] = pa[a][(8 * (long)s + koff<T>(0, u)) * lda];
+#pragma unroll
+      for (int b = 0; b < WB; ++b) bv[b][u] = pb[b][8 * (long)s + koff<T>(0, u)];
     }
-  McLoader<T, BM, VEC> la;
-  KcLoader<T, BN, VEC> lb;
-  const int ntiles = (K + kBK - 1) / kBK;
-  if (ntiles > 0) {
-    la.load(A, lda, M, i0, 0, K, tid);
-    lb.load(B, ldb, B, ldb, N, N, j0, 0, K, tid);
-    la.template store<LA>(sA[0], tid);
-    lb.template store<LB>(sB[0], tid);
+  };
+  const int full = K / 8;
+  if (full > 0) load(a0, b0, 0);
+  int s = 0;
+  for (; s + 1 < full; s += 2) {
+    load(a1, b1, s + 1);
+    mma_step<T, WB, WA, false>(b0, a0, cr, ci);
+    load(a0, b0, min(s + 2, full - 1));
+    mma_step<T, WB, WA, false>(b1, a1, cr, ci);
   }
-  __syncthreads();
-  for (int it = 0; it < ntiles; ++it) {
-    const int cur = it & 1;
-    const bool more = it + 1 < ntiles;
-    if (more) {
-      const int kn = (it + 1) * kBK;
-      la.load(A, lda, M, i0, kn, K, tid);
-      lb.load(B, ldb, B, ldb, N, N, j0, kn, K, tid);
+  if (s < full) mma_step<T, WB, WA, false>(b0, a0, cr, ci);
+  if (8 * full < K) {  // the last K values, zeros behind them
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const bool in = 8 * full + koff<T>(q, u) < K;
+#pragma unroll
+      for (int a = 0; a < WA; ++a) a1[a][u] = in ? pa[a][(8 * (long)full + koff<T>(0, u)) * lda] : mk<T>(0, 0);
+#pragma unroll
+      for (int b = 0; b < WB; ++b) b1[b][u] = in ? pb[b][8 * (long)full + koff<T>(0, u)] : mk<T>(0, 0);
     }
-    mma_tile<T, WBM, WBN, false>(sA[cur], sB[cur], LA, LB, mo, no, lane, cr, ci);
-    if (more) {
-      la.template store<LA>(sA[cur ^ 1], tid);
-      lb.template store<LB>(sB[cur ^ 1], tid);
-    }
-    __syncthreads();
+    mma_step<T, WB, WA, false>(b1, a1, cr, ci);
   }
   const cplx<T>* Zl = static_cast<const cplx<T>*>(e.Zl);
 #pragma unroll
-  for (int a = 0; a < WBM; ++a)
+  for (int b = 0; b < WB; ++b)
 #pragma unroll
-    for (int b = 0; b < WBN; ++b) {
-      const int col = j0 + no + b * 16 + (lane & 15);
+    for (int a = 0; a < WA; ++a) {
+      const int row = i0 + a * 16 + i;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = i0 + mo + a * 16 + MF<T>::row(lane, r);
+        const int col = j0 + b * 16 + MF<T>::row(lane, r);
         if (row < M && col < N) {
-          cplx<T> v = mk<T>(cr[a][b][r], ci[a][b][r]);
+          cplx<T> v = mk<T>(cr[b][a][r], ci[b][a][r]);
           if (e.mode == 2) {
             const auto z = Zl[(long)col * e.ldz + row];
             v.x += z.x;
@@ -399,6 +306,30 @@ __global__ __launch_bounds__(256) void k_gemm_nn(const cplx<T>* __restrict__ A, 
       }
     }
 }
+
+// K-contiguous operand panel through LDS: kBK values of NC columns starting at (k0, c0), element (k, c) to
+// S[k * LDS_LD + c].
+template <typename T, int NC>
+struct KcLoader {
+  static constexpr int UNITS = kBK * NC, PER = (UNITS + 255) / 256;
+  cplx<T> r[PER];
+  __device__ __forceinline__ void load(const cplx<T>* __restrict__ P, long ld, int ncols, int c0, int k0, int kend,
+                                       int tid) {
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int idx = tid + q * 256, k = k0 + idx % kBK, c = c0 + idx / kBK;
+      r[q] = (idx < UNITS && c < ncols && k < kend) ? P[(long)c * ld + k] : mk<T>(0, 0);
+    }
+  }
+  template <int LDS_LD>
+  __device__ __forceinline__ void store(cplx<T>* S, int tid) const {
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int idx = tid + q * 256;
+      if (idx < UNITS) S[(idx % kBK) * LDS_LD + idx / kBK] = r[q];
+    }
+  }
+};
 
 // ------------------------------------------------------------------------------------------
 // Projector products on pairs (G, -G).  Every projector column is the transform of a real function,
@@ -641,11 +572,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
     for (int b = 0; b < NBN; ++b) fx[a][b] = fy[a][b] = gx[a][b] = gy[a][b] = acc_t{0, 0, 0, 0};
   BetaPanel<T, kBK, BM, OTF> la;
-  KcLoader<T, BN, false> lb;
+  KcLoader<T, BN> lb;
   const int ntiles = (K + kBK - 1) / kBK;
   if (ntiles > 0) {
     la.load(A, lda, bg, nh, K, i0, 0, tid);
-    lb.load(Q, ldq, Q, ldq, N, N, j0, 0, K, tid);
+    lb.load(Q, ldq, N, j0, 0, K, tid);
     la.template store<LA, false>(sA[0], tid);
     lb.template store<LB>(sB[0], tid);
   }
@@ -655,7 +586,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const bool more = it + 1 < ntiles;
     if (more) {
       la.load(A, lda, bg, nh, K, i0, kn, tid);
-      lb.load(Q, ldq, Q, ldq, N, N, j0, kn, K, tid);
+      lb.load(Q, ldq, N, j0, kn, K, tid);
     }
 #pragma unroll
     for (int kk = 0; kk < kBK; kk += 4) {
@@ -721,53 +652,69 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // ------------------------------------------------------------------------------------------
 // Launchers
 // ------------------------------------------------------------------------------------------
-template <typename T> struct CnShape;
-template <> struct CnShape<float> {
-  static constexpr int BM = 128, BN = 64;
+// Blocks of a wave's tile (cn: 16 wa x 16 wb) and K splits from smin to smax, by the time of the busiest
+// compute unit: its steps of eight K values at the matrix cores' rate or at that of the loads (72 cycles per
+// 64-lane load of fp64 measured, half of that per value pair in fp32), whichever is longer, no step shorter
+// than the latency of its loads (a quarter longer with one wave per SIMD), + start and end of a round + the partials' traffic.  In fp64, 480 bands x
+// 125,001: 3 x 2 blocks reach 84 TFLOP/s, 2 x 2 77 and 1 x 1 42; 144 x 37,073: 200, 180 and 274 us (2 x 2 fills
+// the last round best); 40 x 5,891: 10.2, 11.8 and 8.5 us, where 11 splits of 64 x 64 tiles took 92 us on 22
+// compute units.
+struct CnShape {
+  int wa, wb, splits;
 };
-template <> struct CnShape<double> {
-  static constexpr int BM = 64, BN = 64;
-};
-template <typename T> struct NnShape;
-template <> struct NnShape<float> {
-  static constexpr int BM = 128, BN = 128;
-};
-template <> struct NnShape<double> {
-  static constexpr int BM = 128, BN = 64;
-};
-
-static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
-template <typename T>
-static bool vec_ok(const void* p, long ld) {
-  return aligned16(p) && (sizeof(T) == 8 || (ld % 2) == 0);
+static CnShape cn_shape(int M, int N, int K, bool fp64, int herm, int smin, int smax) {
+  static constexpr int kShapes[][2] = {{3, 2}, {2, 3}, {2, 2}, {1, 2}, {1, 1}};
+  CnShape best{2, 2, smin};
+  if (M <= 0 || N <= 0 || K <= 0) return best;
+  const int steps = ceil_div(K, 32);  // of the four waves
+  double cost = 1e300;
+  for (const auto& w : kShapes) {
+    const int tm = ceil_div(M, 16 * w[0]);
+    long tiles = (long)tm * ceil_div(N, 16 * w[1]);
+    for (int j = 1; 16 * w[1] * j <= herm; ++j) tiles -= std::max(0, tm - ceil_div(w[1] * j, w[0]));  // left out
+    const double step = std::max(w[0] * w[1] * 8 * 70, (w[0] + w[1]) * 8 * 72) * (fp64 ? 1.0 : 0.5) / 2400.0;
+    for (int n = smin; n <= smax; ++n) {
+      const int chunk = ceil_div(steps, n);
+      if (n > smin && (ceil_div(steps, chunk) != n || chunk < 2)) continue;
+      const long wg = tiles * n, r2 = (wg + 511) / 512;
+      const double c = std::max((double)((wg + 255) / 256) * chunk * step, r2 * chunk * 0.6) * (wg > 256 ? 1.0 : 1.25) + 3.0 * r2 + 0.1 * n +
+                       n * (double)M * N * 32.0 / 4.5e6;
+      if (c < cost) {
+        cost = c;
+        best = CnShape{w[0], w[1], n};
+      }
+    }
+  }
+  return best;
 }
-
-int gemm_cn_tiles(int M, int N, bool fp64) {
-  const int bm = fp64 ? CnShape<double>::BM : CnShape<float>::BM;
-  const int bn = fp64 ? CnShape<double>::BN : CnShape<float>::BN;
-  return ceil_div(M, bm) * ceil_div(N, bn);
+int gemm_cn_splits(int M, int N, int K, bool fp64, int herm_cols) {
+  return cn_shape(M, N, K, fp64, herm_cols, 1, 64).splits;
 }
 
 template <typename T>
 hipError_t launch_gemm_cn(const cplx<T>* A, long lda, const cplx<T>* B, long ldb, const cplx<T>* B2, long ldb2,
-                          int ncol1, int M, int N, int K, int nsplit, double2* part, hipStream_t s) {
+                          int ncol1, int M, int N, int K, int nsplit, double2* part, hipStream_t s, int herm_cols) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  constexpr int BM = CnShape<T>::BM, BN = CnShape<T>::BN;
-  int kchunk = ceil_div(K, nsplit);
-  kchunk = ceil_div(kchunk, kBK) * kBK;
-  if (kchunk <= 0) kchunk = kBK;
-  const int tm = ceil_div(M, BM), tn = ceil_div(N, BN);
+  const CnShape c = cn_shape(M, N, K, sizeof(T) == 8, herm_cols, nsplit, nsplit);
+  const int kchunk = std::max(1, ceil_div(ceil_div(K, 32), nsplit)) * 32;
+  const int tm = ceil_div(M, 16 * c.wa), tn = ceil_div(N, 16 * c.wb);
   const cplx<T>* b2 = B2 ? B2 : B;
   const long l2 = B2 ? ldb2 : ldb;
-  const bool vec = vec_ok<T>(A, lda) && vec_ok<T>(B, ldb) && vec_ok<T>(b2, l2);
-  dim3 grid(tm * tn * nsplit);
-  if (vec)
-    hipLaunchKernelGGL((k_gemm_cn<T, BM, BN, true>), grid, dim3(256), 0, s, A, lda, B, ldb, b2,
-                       l2, ncol1, M, N, K, kchunk, tm, tn, part);
-  else
-    hipLaunchKernelGGL((k_gemm_cn<T, BM, BN, false>), grid, dim3(256), 0, s, A, lda, B, ldb,
-                       b2, l2, ncol1, M, N, K, kchunk, tm, tn, part);
+  const dim3 grid(tm * tn * nsplit);
+#define PW_CN(WA, WB)                                                                                              \
+  case 4 * WA + WB:                                                                                                \
+    hipLaunchKernelGGL((k_gemm_cn<T, WA, WB>), grid, dim3(256), 0, s, A, lda, B, ldb, b2, l2, ncol1, M, N, K, kchunk, \
+                       tm, tn, part, herm_cols);                                                                   \
+    break
+  switch (4 * c.wa + c.wb) {
+    PW_CN(3, 2);
+    PW_CN(2, 3);
+    PW_CN(2, 2);
+    PW_CN(1, 2);
+    PW_CN(1, 1);
+    default: return hipErrorInvalidValue;
+  }
+#undef PW_CN
   return hipGetLastError();
 }
 
@@ -785,16 +732,35 @@ template <typename T>
 hipError_t launch_gemm_nn(const cplx<T>* A, long lda, const cplx<T>* B, long ldb, int M, int N, int K,
                           cplx<T>* out, long ldo, const EpiH& e, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  constexpr int BM = NnShape<T>::BM, BN = NnShape<T>::BN;
-  const int tm = ceil_div(M, BM), tn = ceil_div(N, BN);
-  const bool vec = vec_ok<T>(A, lda) && vec_ok<T>(B, ldb);
-  dim3 grid(tm * tn);
-  if (vec)
-    hipLaunchKernelGGL((k_gemm_nn<T, BM, BN, true>), grid, dim3(256), 0, s, A, lda, B, ldb, M,
-                       N, K, tn, out, ldo, e);
-  else
-    hipLaunchKernelGGL((k_gemm_nn<T, BM, BN, false>), grid, dim3(256), 0, s, A, lda, B, ldb,
-                       M, N, K, tn, out, ldo, e);
+  // blocks of a wave's tile: the shape that leaves the fewest block products to the busiest SIMD, the wider
+  // one among equals (fewer loads).  37,073 x 144: 1 x 3 leaves 7 tiles of 3 blocks, 2 x 3 leaves 4 of 6
+  static constexpr int kShapes[][2] = {{2, 3}, {2, 2}, {1, 4}, {1, 3}, {1, 2}, {1, 1}};
+  int wa = 2, wb = 3;
+  long cost = 1L << 60;
+  for (const auto& w : kShapes) {
+    const long c = ((long)ceil_div(M, 64 * w[0]) * ceil_div(N, 16 * w[1]) + 255) / 256 * (w[0] * w[1] * 16 + 4);
+    if (c < cost) {
+      cost = c;
+      wa = w[0];
+      wb = w[1];
+    }
+  }
+  const int tm = ceil_div(M, 64 * wa), tn = ceil_div(N, 16 * wb);
+  const dim3 grid(tm * tn);
+#define PW_NN(WA, WB)                                                                                              \
+  case 4 * WA + WB:                                                                                                \
+    hipLaunchKernelGGL((k_gemm_nn<T, WA, WB>), grid, dim3(256), 0, s, A, lda, B, ldb, M, N, K, tn, out, ldo, e);   \
+    break
+  switch (4 * wa + wb) {
+    PW_NN(2, 3);
+    PW_NN(2, 2);
+    PW_NN(1, 4);
+    PW_NN(1, 3);
+    PW_NN(1, 2);
+    PW_NN(1, 1);
+    default: return hipErrorInvalidValue;
+  }
+#undef PW_NN
   return hipGetLastError();
 }
 
@@ -906,7 +872,7 @@ hipError_t launch_pairs_nn(const cplx<T>* A, long lda, const BetaGen* bg, const 
 
 #define PW_INST_GEMM(T)                                                                                      \
   template hipError_t launch_gemm_cn<T>(const cplx<T>*, long, const cplx<T>*, long, const cplx<T>*, long,   \
-                                        int, int, int, int, int, double2*, hipStream_t);                     \
+                                        int, int, int, int, int, double2*, hipStream_t, int);                \
   template hipError_t launch_reduce_parts<T>(const double2*, int, int, int, const double*, int, double2*,   \
                                              long, cplx<T>*, long, hipStream_t);                             \
   template hipError_t launch_gemm_nn<T>(const cplx<T>*, long, const cplx<T>*, long, int, int, int, cplx<T>*, \

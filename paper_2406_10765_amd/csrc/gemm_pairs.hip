@@ -496,15 +496,7 @@ __global__ __launch_bounds__(256) void k_pair_reduce(const double2* __restrict__
     unsigned int fh = 0, fl = 0, gh = 0, gl = 0;
     if (2 * w < M) {  // M is a multiple of 4
       const double2* src = part + (long)j * M + 2 * w;
-      double2 a = src[0], b = src[1];
-#pragma unroll 4
-      for (int p = 1; p < nsplit; ++p) {
-        const double2 u = src[(long)p * M * nb], v = src[(long)p * M * nb + 1];
-        a.x += u.x;
-        a.y += u.y;
-        b.x += v.x;
-        b.y += v.y;
-      }
+      const double2 a = sum_splits(src, nsplit, (long)M * nb), b = sum_splits(src + 1, nsplit, (long)M * nb);
       const double d0 = dscale[(2 * w) & 3], d1 = dscale[(2 * w + 1) & 3];
       split_word(make_float2((float)(a.x * d0), (float)(b.x * d1)), fh, fl);
       split_word(make_float2((float)(a.y * d0), (float)(b.y * d1)), gh, gl);

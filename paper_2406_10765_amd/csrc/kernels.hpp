@@ -111,13 +111,13 @@ hipError_t launch_density_groups(const double* part, int ngroups, long nr, doubl
 // --------------------------------------------------------------- GEMM ------
 // C_part[s] = A^H B over the s-th K chunk.  A: K x M, B: K x N (column-major; columns of B
 // with index >= nsplit_col come from B2).  Partials are complex double, [s][N][M].
-// Number of output tiles of the cn kernel for an M x N result (used to choose the K split).
-int gemm_cn_tiles(int M, int N, bool fp64);
-
-
+// herm_cols > 0: B's first herm_cols columns are A itself, and tiles of that Gram block wholly below its
+// diagonal are not written (the caller takes the lower triangle from the upper one, launch_mirror_upper).
+int gemm_cn_splits(int M, int N, int K, bool fp64, int herm_cols);  // K splits to give launch_gemm_cn
 template <typename T>
 hipError_t launch_gemm_cn(const cplx<T>* A, long lda, const cplx<T>* B, long ldb, const cplx<T>* B2,
-                          long ldb2, int ncol1, int M, int N, int K, int nsplit, double2* part, hipStream_t s);
+                          long ldb2, int ncol1, int M, int N, int K, int nsplit, double2* part, hipStream_t s,
+                          int herm_cols = 0);
 
 // Sum the split partials: out[j*ldo + i] = scale_i * sum_s part[s][j][i]  (scale_i = dscale[i % dper]
 // when dscale != null), written as complex double to out64 (if non-null) and as T to outT (if non-null).

@@ -365,18 +365,16 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   const bool gram_planes = (bkb || P.rspace) && bgr && P.nbb >= P.nbands;
   P.yp_cols = bkb ? P.nbb * (gram_planes ? 2 : 1) : (gram_planes ? 2 * P.nbb : 0);
   P.nsplit_gram = gram_planes ? pick_split(gemm_cn_bf16_planes_tiles(P.nbands, 2 * P.nbands), P.npw, 4096)
-                  : pick_split(bgr ? gemm_cn_bf16_tiles(P.nbands, 2 * P.nbands)
-                                   : gemm_cn_tiles(P.nbands, 2 * P.nbands, f64),
-                               P.npw);
+                  : bgr       ? pick_split(gemm_cn_bf16_tiles(P.nbands, 2 * P.nbands), P.npw)
+                              : gemm_cn_splits(P.nbands, 2 * P.nbands, P.npw, f64, P.nbands);
   const bool lob = (P.flags & PW_FLAG_LOBPCG) != 0;
   if (lob && P.nbb < P.nbands) {
     *err = "PW_FLAG_LOBPCG needs every band in one block (the plan would filter in blocks)";
     return PW_EINVAL;
   }
-  P.nsplit_lob = lob ? pick_split(bgr ? gemm_cn_bf16_tiles(3 * P.nbands, 6 * P.nbands)
-                                      : gemm_cn_tiles(3 * P.nbands, 6 * P.nbands, f64),
-                                  P.npw)
-                     : 0;
+  P.nsplit_lob = !lob  ? 0
+                 : bgr ? pick_split(gemm_cn_bf16_tiles(3 * P.nbands, 6 * P.nbands), P.npw)
+                       : gemm_cn_splits(3 * P.nbands, 6 * P.nbands, P.npw, f64, 0);
   const size_t kb = lob ? 3 * (size_t)P.nbands : (size_t)P.nbands;  // largest dense problem
 
   // --- arena layout --------------------------------------------------------------
