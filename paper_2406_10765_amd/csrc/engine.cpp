@@ -601,6 +601,9 @@ struct Engine {
         return PW_OK;
       }
     }
+    // bands per pass: the stick batch, and as many |psi|^2 grids as u0 holds
+    const int per = (int)std::min<long>(P.fft_batch, u0_elems / nr);
+    if (per < 1) return fail(h, PW_EINVAL, "density: the work buffer cannot hold one real-space grid");
     if (pencil_n_supported(g.n1) && pencil_n_supported(g.n2)) {
       // pencil form in the three work blocks (u0, u1, zb): one FP64 grid per band group, enough groups for
       // two waves of 8 rows per SIMD, then the pencil intermediate of as many bands as fit
@@ -625,9 +628,6 @@ struct Engine {
         return PW_OK;
       }
     }
-    // bands per pass: the stick batch, and as many |psi|^2 grids as u0 holds
-    const int per = (int)std::min<long>(P.fft_batch, u0_elems / nr);
-    if (per < 1) return fail(h, PW_EINVAL, "density: the work buffer cannot hold one real-space grid");
     for (int b0 = 0; b0 < nb; b0 += per) {
       const int nbt = std::min(per, nb - b0);
       PW_TIMED(PW_PH_STICKS_INV, launch_sticks_inv<T>(X + (long)b0 * ld, ld, SB, nbt, st, g, tw3, P.fl, h->stream));

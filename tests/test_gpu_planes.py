@@ -99,3 +99,21 @@ def test_noalloc(ncells, ecut, grid, prec):
     print("pencil noalloc", ncells, grid, err, flush=True)
     assert err < (1e-12 if prec == pw.PW_FP64 else 2e-5)
     h.close()
+
+
+@pytest.mark.parametrize("prec", [pw.PW_FP64, pw.PW_MIXED])
+def test_density_work_buffer_limit(prec):
+    """On every route the density needs one real-space grid in the first work block, 2 ceil16(npw) nbands reals."""
+    for nb in (1, 2, 3, 4, 5, 6, 9):
+        cell = synth.silicon_cell((1, 1, 2), 10.0, nbands=nb, disp_seed=3)
+        h = pw.Handle(cell, prec)
+        n1, n2, n3 = (int(v) for v in h.info.fft_n)
+        fits = 2 * ((h.npw + 15) // 16 * 16) * nb >= n1 * n2 * n3
+        X = h.random_block(nb, 3)
+        if fits:
+            rho = h.density(X, np.ones(nb))
+            assert np.isfinite(rho.cpu().numpy()).all()
+        else:
+            with pytest.raises(pw.PWError, match="work buffer"):
+                h.density(X, np.ones(nb))
+        h.close()
