@@ -54,7 +54,6 @@ template <> struct MF<float> {
   static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
 };
 
-constexpr int kBK = 16;  // projectors per K tile of the nonlocal product on pairs
 constexpr int kXcd = 8;  // XCDs per MI355X
 
 // Tile index -> (tm, tn, split) with the tiles of one XCD contiguous.  Launch order
@@ -307,30 +306,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
-// K-contiguous operand panel through LDS: kBK values of NC columns starting at (k0, c0), element (k, c) to
-// S[k * LDS_LD + c].
-template <typename T, int NC>
-struct KcLoader {
-  static constexpr int UNITS = kBK * NC, PER = (UNITS + 255) / 256;
-  cplx<T> r[PER];
-  __device__ __forceinline__ void load(const cplx<T>* __restrict__ P, long ld, int ncols, int c0, int k0, int kend,
-                                       int tid) {
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int idx = tid + q * 256, k = k0 + idx % kBK, c = c0 + idx / kBK;
-      r[q] = (idx < UNITS && c < ncols && k < kend) ? P[(long)c * ld + k] : mk<T>(0, 0);
-    }
-  }
-  template <int LDS_LD>
-  __device__ __forceinline__ void store(cplx<T>* S, int tid) const {
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int idx = tid + q * 256;
-      if (idx < UNITS) S[(idx % kBK) * LDS_LD + idx / kBK] = r[q];
-    }
-  }
-};
-
 // ------------------------------------------------------------------------------------------
 // Projector products on pairs (G, -G).  Every projector column is the transform of a real function,
 // beta(-G) = conj beta(G) (its l = 1 columns times i where needed, which V_NL does not see), and a
@@ -343,21 +318,29 @@ struct KcLoader {
 //               V_NL y[h] = zf + i zg, V_NL y[npw - 1 - h] = conj(zf) + i conj(zg)
 // half the multiplications and half the table of the complex products over the whole sphere.
 //
-// Four waves along M, all columns of the tile in each; the tile's width is the multiple of 16 up to 64
-// that pads the band count least.  Bound by the matrix cores (64 cycles per fp64 instruction): what
-// counts is two workgroups per compute unit, so that one's barriers and loads run under the other's
-// products, and a split whose last round is full.  2,048 projectors x 1,088 bands x 147,834 half rows
-// in fp64: projection 44.7 ms and nonlocal product 42.3 ms (59 and 62 TFLOP/s); the complex products
-// over the whole sphere, one or two workgroups per compute unit, took 95.1 and 98.2 ms.
+// The projection runs four waves along M, all columns of the tile in each, through LDS (every column needs two
+// loads, which the four waves share).  Bound by the matrix cores (64 cycles per fp64 instruction): what counts
+// is two workgroups per compute unit, so that one's barriers and loads run under the other's products, and a
+// split whose last round is full.  2,048 projectors x 1,088 bands x 147,834 half rows in fp64: projection
+// 41.6 ms, nonlocal product 35.2 ms (63 and 75 TFLOP/s; 41.6 ms through LDS); the complex products over the
+// whole sphere took 95.1 and 98.2 ms.
 // ------------------------------------------------------------------------------------------
-template <typename T> struct PairCfg;
+template <typename T> struct PairCfg;  // K tile of the projection
 template <> struct PairCfg<double> {
-  static constexpr int BKC = 8, HB = 1, CYC = 64;  // K tile of the projection, row blocks per wave (nonlocal)
+  static constexpr int BK = 8;
 };
 template <> struct PairCfg<float> {
-  static constexpr int BKC = 16, HB = 2, CYC = 32;
+  static constexpr int BK = 16;
 };
 
+// The four projectors of an atom at one half row: radial factors r, phase e.
+template <typename T>
+__device__ __forceinline__ void beta_four(const double4& r, const double2& e, cplx<T> (&v)[4]) {
+  v[0] = mk<T>((T)(r.x * e.x), (T)(r.x * e.y));
+  v[1] = mk<T>((T)(-r.y * e.y), (T)(r.y * e.x));
+  v[2] = mk<T>((T)(-r.z * e.y), (T)(r.z * e.x));
+  v[3] = mk<T>((T)(-r.w * e.y), (T)(r.w * e.x));
+}
 // The four projectors of atom a at half row g (zero past the half sphere / the atoms).
 template <typename T>
 __device__ __forceinline__ void beta_gen4(const BetaGen& bg, int g, int a, cplx<T> (&v)[4]) {
@@ -371,16 +354,11 @@ __device__ __forceinline__ void beta_gen4(const BetaGen& bg, int g, int a, cplx<
   const double2 e1 = p[n1 + bg.h1], e2 = p[bg.o2 + n2 + bg.h2], e3 = p[bg.o3 + n3 + bg.h3];
   const double2 e12 = make_double2(e1.x * e2.x - e1.y * e2.y, e1.x * e2.y + e1.y * e2.x);
   const double2 e = make_double2(e12.x * e3.x - e12.y * e3.y, e12.x * e3.y + e12.y * e3.x);
-  const double4 r = *reinterpret_cast<const double4*>(bg.rad + 4 * (long)g);
-  v[0] = mk<T>((T)(r.x * e.x), (T)(r.x * e.y));
-  v[1] = mk<T>((T)(-r.y * e.y), (T)(r.y * e.x));
-  v[2] = mk<T>((T)(-r.z * e.y), (T)(r.z * e.x));
-  v[3] = mk<T>((T)(-r.w * e.y), (T)(r.w * e.x));
+  beta_four<T>(*reinterpret_cast<const double4*>(bg.rad + 4 * (long)g), e, v);
 }
 
-// Projector panels: COLS projectors x ROWS half rows, element (row, column) to S[row * LDS_LD + column]
-// (projection, ROWS = K) or S[column * LDS_LD + row] (nonlocal, ROWS = M).  From the table (row-contiguous
-// columns) or generated, four projectors of an atom per unit.
+// Projector panels: COLS projectors x ROWS half rows, element (row, column) to S[row * LDS_LD + column].  From
+// the table (row-contiguous columns) or generated, four projectors of an atom per unit.
 template <typename T, int COLS, int ROWS, bool OTF>
 struct BetaPanel {
   static constexpr int W = OTF ? 4 : 1;  // projectors per unit
@@ -399,14 +377,14 @@ struct BetaPanel {
       }
     }
   }
-  template <int LDS_LD, bool ROWMAJOR>
+  template <int LDS_LD>
   __device__ __forceinline__ void store(cplx<T>* S, int tid) const {
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const int idx = tid + q * 256, row = idx % ROWS, col = W * (idx / ROWS);
       if (idx < UNITS) {
 #pragma unroll
-        for (int m = 0; m < W; ++m) S[ROWMAJOR ? row * LDS_LD + col + m : (col + m) * LDS_LD + row] = r[q][m];
+        for (int m = 0; m < W; ++m) S[row * LDS_LD + col + m] = r[q][m];
       }
     }
   }
@@ -449,7 +427,7 @@ template <typename T, int WBM, int NBN, bool OTF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_pairs_cn(
     const cplx<T>* __restrict__ A, long lda, BetaGen bg, const cplx<T>* __restrict__ Y, long ldy, int M, int N, int npw,
     int nh, int kchunk, int tiles_m, int tiles_n, double2* __restrict__ part) {
-  constexpr int BK = PairCfg<T>::BKC, BM = 64 * WBM, BN = 16 * NBN, LA = BM + 1, LB = BN + 1;
+  constexpr int BK = PairCfg<T>::BK, BM = 64 * WBM, BN = 16 * NBN, LA = BM + 1, LB = BN + 1;
   constexpr int FLUSH = 256 / BK;  // fp32: K tiles per move into fp64 registers
   constexpr bool F32 = std::is_same<T, float>::value;
   using acc_t = typename MF<T>::acc;
@@ -475,7 +453,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   if (ntiles > 0) {
     la.load(A, lda, bg, ke, M, kb, i0, tid);
     lb.load(Y, ldy, npw, ke, N, j0, kb, tid);
-    la.template store<LA, true>(sA[0], tid);
+    la.template store<LA>(sA[0], tid);
     lb.template store<LB>(sF[0], sG[0], nh, kb, tid);
   }
   __syncthreads();
@@ -528,7 +506,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       }
     }
     if (more) {
-      la.template store<LA, true>(sA[cur ^ 1], tid);
+      la.template store<LA>(sA[cur ^ 1], tid);
       lb.template store<LB>(sF[cur ^ 1], sG[cur ^ 1], nh, kn, tid);
     }
     __syncthreads();
@@ -553,89 +531,131 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
-// out = EpiH(mode 1) with V_NL psi = beta q over K projectors.  Tile 64 HB half rows x 16 NBN bands.
-template <typename T, int NBN, bool OTF>
+// out = EpiH(mode 1) with V_NL psi = beta q over K projectors, a wave per tile of 16 WA half rows x 16 WB bands
+// like the complex products (operands straight from memory, the four waves of a workgroup on the same
+// bands, the product transposed so that sixteen lanes hold consecutive rows).  Generated projectors: a lane
+// makes the four of one atom for its row, whose radial factors stay in registers.
+// The epilogue moves three times the block's bytes: 256 projectors x 144 bands, 18,537 half rows in fp64 138 us
+// (65 at the matrix cores' rate, 54 for the bytes; 170 us through LDS), generated 112 us (162 through LDS).
+template <typename T, int WA, int WB, bool OTF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_pairs_nn(
     const cplx<T>* __restrict__ A, long lda, BetaGen bg, const cplx<T>* __restrict__ Q, long ldq, int npw, int nh, int N,
     int K, int tiles_n, cplx<T>* out, long ldo, EpiH e) {
-  constexpr int HB = PairCfg<T>::HB, BM = 64 * HB, BN = 16 * NBN, LA = BM + 1, LB = BN + 1;
+  constexpr int U = OTF ? 4 : 2, STEP = 4 * U;  // projectors per lane and step, per step
   using acc_t = typename MF<T>::acc;
-  __shared__ cplx<T> sA[2][kBK * LA];
-  __shared__ cplx<T> sB[2][kBK * LB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, q = lane >> 4;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
   const int tm = t / tiles_n, tn = t - tm * tiles_n;  // n fastest: workgroups sharing an A panel are adjacent
-  const int i0 = tm * BM, j0 = tn * BN, mo = wave * 16 * HB;
-  acc_t fx[HB][NBN], fy[HB][NBN], gx[HB][NBN], gy[HB][NBN];
+  const int i0 = (tm * 4 + wave) * 16 * WA, j0 = tn * 16 * WB;
+  if (i0 >= nh) return;
+  auto ko = [](int g, int u) { return OTF ? 4 * g + u : koff<T>(g, u); };
+  const cplx<T>*pa[WA], *pb[WB];
+  int m1[OTF ? WA : 1], m2[OTF ? WA : 1], m3[OTF ? WA : 1];
+  double4 rad[OTF ? WA : 1];
 #pragma unroll
-  for (int a = 0; a < HB; ++a)
-#pragma unroll
-    for (int b = 0; b < NBN; ++b) fx[a][b] = fy[a][b] = gx[a][b] = gy[a][b] = acc_t{0, 0, 0, 0};
-  BetaPanel<T, kBK, BM, OTF> la;
-  KcLoader<T, BN> lb;
-  const int ntiles = (K + kBK - 1) / kBK;
-  if (ntiles > 0) {
-    la.load(A, lda, bg, nh, K, i0, 0, tid);
-    lb.load(Q, ldq, N, j0, 0, K, tid);
-    la.template store<LA, false>(sA[0], tid);
-    lb.template store<LB>(sB[0], tid);
+  for (int a = 0; a < WA; ++a) {
+    const int h = min(i0 + a * 16 + i, nh - 1);
+    if constexpr (OTF) {
+      m1[a] = bg.miller[3 * h] + bg.h1;
+      m2[a] = bg.o2 + bg.miller[3 * h + 1] + bg.h2;
+      m3[a] = bg.o3 + bg.miller[3 * h + 2] + bg.h3;
+      rad[a] = *reinterpret_cast<const double4*>(bg.rad + 4 * (long)h);
+      pa[a] = nullptr;
+    } else {
+      pa[a] = A + ko(q, 0) * lda + h;
+    }
   }
-  __syncthreads();
-  for (int it = 0; it < ntiles; ++it) {
-    const int cur = it & 1, kn = (it + 1) * kBK;
-    const bool more = it + 1 < ntiles;
-    if (more) {
-      la.load(A, lda, bg, nh, K, i0, kn, tid);
-      lb.load(Q, ldq, N, j0, kn, K, tid);
+#pragma unroll
+  for (int b = 0; b < WB; ++b) pb[b] = Q + (long)min(j0 + b * 16 + i, N - 1) * ldq + ko(q, 0);
+  acc_t fx[WB][WA], fy[WB][WA], gx[WB][WA], gy[WB][WA];
+#pragma unroll
+  for (int b = 0; b < WB; ++b)
+#pragma unroll
+    for (int a = 0; a < WA; ++a) fx[b][a] = fy[b][a] = gx[b][a] = gy[b][a] = acc_t{0, 0, 0, 0};
+  auto load = [&](cplx<T>(&av)[WA][U], cplx<T>(&bv)[WB][U], int s) {
+    if constexpr (OTF) {
+      const double2* p = bg.ph + (long)(4 * s + q) * bg.w;
+#pragma unroll
+      for (int a = 0; a < WA; ++a) {
+        const double2 e1 = p[m1[a]], e2 = p[m2[a]], e3 = p[m3[a]];
+        const double2 e12 = make_double2(e1.x * e2.x - e1.y * e2.y, e1.x * e2.y + e1.y * e2.x);
+        beta_four<T>(rad[a], make_double2(e12.x * e3.x - e12.y * e3.y, e12.x * e3.y + e12.y * e3.x), av[a]);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int a = 0; a < WA; ++a) av[a][u] = pa[a][(STEP * (long)s + ko(0, u)) * lda];
     }
 #pragma unroll
-    for (int kk = 0; kk < kBK; kk += 4) {
-      const int kr = kk + (lane >> 4);
-      cplx<T> av[HB], bv[NBN];
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int a = 0; a < HB; ++a) av[a] = sA[cur][kr * LA + mo + a * 16 + (lane & 15)];
+      for (int b = 0; b < WB; ++b) bv[b][u] = pb[b][STEP * (long)s + ko(0, u)];
+  };
+  auto mma = [&](const cplx<T>(&av)[WA][U], const cplx<T>(&bv)[WB][U]) {
 #pragma unroll
-      for (int b = 0; b < NBN; ++b) bv[b] = sB[cur][kr * LB + b * 16 + (lane & 15)];
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int a = 0; a < HB; ++a)
+      for (int b = 0; b < WB; ++b)
 #pragma unroll
-        for (int b = 0; b < NBN; ++b) {
-          fx[a][b] = MF<T>::mma(av[a].x, bv[b].x, fx[a][b]);
-          fy[a][b] = MF<T>::mma(av[a].y, bv[b].x, fy[a][b]);
-          gx[a][b] = MF<T>::mma(av[a].x, bv[b].y, gx[a][b]);
-          gy[a][b] = MF<T>::mma(av[a].y, bv[b].y, gy[a][b]);
+        for (int a = 0; a < WA; ++a) {
+          fx[b][a] = MF<T>::mma(bv[b][u].x, av[a][u].x, fx[b][a]);
+          fy[b][a] = MF<T>::mma(bv[b][u].x, av[a][u].y, fy[b][a]);
+          gx[b][a] = MF<T>::mma(bv[b][u].y, av[a][u].x, gx[b][a]);
+          gy[b][a] = MF<T>::mma(bv[b][u].y, av[a][u].y, gy[b][a]);
         }
+  };
+  const int full = K / STEP;
+  cplx<T> a0[WA][U], b0[WB][U], a1[WA][U], b1[WB][U];
+  if (full > 0) load(a0, b0, 0);
+  int s = 0;
+  for (; s + 1 < full; s += 2) {
+    load(a1, b1, s + 1);
+    mma(a0, b0);
+    load(a0, b0, min(s + 2, full - 1));
+    mma(a1, b1);
+  }
+  if (s < full) mma(a0, b0);
+  if (STEP * full < K) {  // the last projectors, zeros behind them
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = STEP * full + ko(q, u) < K;
+#pragma unroll
+      for (int a = 0; a < WA; ++a)
+        if constexpr (!OTF) a1[a][u] = in ? pa[a][(STEP * (long)full + ko(0, u)) * lda] : mk<T>(0, 0);
+#pragma unroll
+      for (int b = 0; b < WB; ++b) b1[b][u] = in ? pb[b][STEP * (long)full + ko(0, u)] : mk<T>(0, 0);
     }
-    if (more) {
-      la.template store<LA, false>(sA[cur ^ 1], tid);
-      lb.template store<LB>(sB[cur ^ 1], tid);
+    if constexpr (OTF) {
+#pragma unroll
+      for (int a = 0; a < WA; ++a) beta_gen4<T>(bg, min(i0 + a * 16 + i, nh - 1), 4 * full + q, a1[a]);
     }
-    __syncthreads();
+    mma(a1, b1);
   }
   const T* kin = static_cast<const T*>(e.kin);
   const T alpha = (T)e.alpha, cc = (T)e.c, beta = (T)e.beta;
 #pragma unroll
-  for (int a = 0; a < HB; ++a)
+  for (int b = 0; b < WB; ++b)
 #pragma unroll
-    for (int b = 0; b < NBN; ++b) {
-      __builtin_amdgcn_sched_barrier(0);  // one block at a time: bounded register use
-      const int col = j0 + b * 16 + (lane & 15);
+    for (int r = 0; r < 4; ++r) {
+      __builtin_amdgcn_sched_barrier(0);  // one column at a time: bounded register use
+      const int col = j0 + b * 16 + MF<T>::row(lane, r);
       if (col >= N) continue;
       const cplx<T>* Y = static_cast<const cplx<T>*>(e.Y) + (long)col * e.ldy;
       const cplx<T>* Zl = static_cast<const cplx<T>*>(e.Zl) + (long)col * e.ldz;
       const cplx<T>* Yp = e.Yp ? static_cast<const cplx<T>*>(e.Yp) + (long)col * e.ldp : nullptr;
       cplx<T>* o = out + (long)col * ldo;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int h = i0 + mo + a * 16 + MF<T>::row(lane, r);
+      for (int a = 0; a < WA; ++a) {
+        const int h = i0 + a * 16 + i;
         if (h >= nh) continue;
         const int g = npw - 1 - h;  // == h at G = 0
         const T kc = kin[h] - cc;
         const cplx<T> yp = Y[h], ym = Y[g], zp = Zl[h], zm = Zl[g];
-        cplx<T> p = mk<T>(alpha * (kc * yp.x + zp.x + (fx[a][b][r] - gy[a][b][r])),
-                          alpha * (kc * yp.y + zp.y + (fy[a][b][r] + gx[a][b][r])));
-        cplx<T> m = mk<T>(alpha * (kc * ym.x + zm.x + (fx[a][b][r] + gy[a][b][r])),
-                          alpha * (kc * ym.y + zm.y + (gx[a][b][r] - fy[a][b][r])));
+        cplx<T> p = mk<T>(alpha * (kc * yp.x + zp.x + (fx[b][a][r] - gy[b][a][r])),
+                          alpha * (kc * yp.y + zp.y + (fy[b][a][r] + gx[b][a][r])));
+        cplx<T> m = mk<T>(alpha * (kc * ym.x + zm.x + (fx[b][a][r] + gy[b][a][r])),
+                          alpha * (kc * ym.y + zm.y + (gx[b][a][r] - fy[b][a][r])));
         if (Yp) {
           const cplx<T> qp = Yp[h], qm = Yp[g];
           p.x -= beta * qp.x;
@@ -728,33 +748,41 @@ hipError_t launch_reduce_parts(const double2* part, int nsplit, int M, int N, co
   return hipGetLastError();
 }
 
+// Blocks of a wave's tile of an nn product (16 wa rows x 16 wb columns, four waves along the rows): the shape that
+// leaves the fewest block products to the busiest compute unit, the wider one among equals (fewer loads).
+// 37,073 x 144: 1 x 3 leaves 7 tiles of 3 blocks to a SIMD and takes 100 us, 2 x 3 leaves 4 of 6 and takes
+// 109 us, 1 x 1 has no idle SIMD but three times the loads: 114 us.
+struct NnShape {
+  int wa, wb;
+};
+static NnShape nn_shape(int M, int N, int max_blocks) {
+  static constexpr int kShapes[][2] = {{2, 3}, {2, 2}, {1, 3}, {1, 2}, {1, 1}};
+  NnShape best{1, 1};
+  long cost = 1L << 60;
+  for (const auto& w : kShapes) {
+    const long c = ((long)ceil_div(M, 64 * w[0]) * ceil_div(N, 16 * w[1]) + 255) / 256 * (w[0] * w[1] * 16 + 4);
+    if (w[0] * w[1] <= max_blocks && c < cost) {
+      cost = c;
+      best = NnShape{w[0], w[1]};
+    }
+  }
+  return best;
+}
+
 template <typename T>
 hipError_t launch_gemm_nn(const cplx<T>* A, long lda, const cplx<T>* B, long ldb, int M, int N, int K,
                           cplx<T>* out, long ldo, const EpiH& e, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  // blocks of a wave's tile: the shape that leaves the fewest block products to the busiest SIMD, the wider
-  // one among equals (fewer loads).  37,073 x 144: 1 x 3 leaves 7 tiles of 3 blocks, 2 x 3 leaves 4 of 6
-  static constexpr int kShapes[][2] = {{2, 3}, {2, 2}, {1, 4}, {1, 3}, {1, 2}, {1, 1}};
-  int wa = 2, wb = 3;
-  long cost = 1L << 60;
-  for (const auto& w : kShapes) {
-    const long c = ((long)ceil_div(M, 64 * w[0]) * ceil_div(N, 16 * w[1]) + 255) / 256 * (w[0] * w[1] * 16 + 4);
-    if (c < cost) {
-      cost = c;
-      wa = w[0];
-      wb = w[1];
-    }
-  }
-  const int tm = ceil_div(M, 64 * wa), tn = ceil_div(N, 16 * wb);
+  const NnShape w = nn_shape(M, N, 6);
+  const int tm = ceil_div(M, 64 * w.wa), tn = ceil_div(N, 16 * w.wb);
   const dim3 grid(tm * tn);
 #define PW_NN(WA, WB)                                                                                              \
   case 4 * WA + WB:                                                                                                \
     hipLaunchKernelGGL((k_gemm_nn<T, WA, WB>), grid, dim3(256), 0, s, A, lda, B, ldb, M, N, K, tn, out, ldo, e);   \
     break
-  switch (4 * wa + wb) {
+  switch (4 * w.wa + w.wb) {
     PW_NN(2, 3);
     PW_NN(2, 2);
-    PW_NN(1, 4);
     PW_NN(1, 3);
     PW_NN(1, 2);
     PW_NN(1, 1);
@@ -776,7 +804,7 @@ static int pair_rows(int M, int w, bool fp64) { return M > 64 && (fp64 || w < 64
 PairsCn pairs_cn_plan(int M, int nb, int nh, bool fp64, long cap) {
   PairsCn best{64, 1};
   if (M <= 0 || nb <= 0 || nh <= 0) return best;
-  const int bk = fp64 ? PairCfg<double>::BKC : PairCfg<float>::BKC, ktiles = ceil_div(nh, bk);
+  const int bk = fp64 ? PairCfg<double>::BK : PairCfg<float>::BK, ktiles = ceil_div(nh, bk);
   double cost = 1e300;
   for (int w = 64; w >= 16; w -= 16) {
     const int rows = pair_rows(M, w, fp64);
@@ -795,27 +823,11 @@ PairsCn pairs_cn_plan(int M, int nb, int nh, bool fp64, long cap) {
   }
   return best;
 }
-// Bands per tile of the nonlocal product: rounds of two workgroups per compute unit x (columns + what a
-// tile costs whatever its width).  Narrow tiles fill the chip for small cells (85 row tiles x 101 bands: 4 of
-// 32), wide ones read the projector panel less often.
-static int pairs_nn_width(int row_tiles, int nb) {
-  int best = 64;
-  long cost = 1L << 60;
-  for (int w = 64; w >= 16; w -= 16) {
-    const long c = ((long)row_tiles * ceil_div(nb, w) + 511) / 512 * (w + 16);
-    if (c < cost) {
-      cost = c;
-      best = w;
-    }
-  }
-  return best;
-}
-
 template <typename T>
 hipError_t launch_pairs_cn(const cplx<T>* A, long lda, const BetaGen* bg, const cplx<T>* Y, long ldy, int M, int nb,
                            int npw, const PairsCn& c, double2* part, hipStream_t s) {
   if (M <= 0 || nb <= 0) return hipSuccess;
-  constexpr int BK = PairCfg<T>::BKC;
+  constexpr int BK = PairCfg<T>::BK;
   const int nh = (npw + 1) / 2, kchunk = ceil_div(ceil_div(nh, BK), c.splits) * BK;
   const int w = c.width, rows = pair_rows(M, w, sizeof(T) == 8), tm = ceil_div(M, rows), tn = ceil_div(nb, w);
   const dim3 grid(tm * tn * c.splits);
@@ -848,23 +860,26 @@ template <typename T>
 hipError_t launch_pairs_nn(const cplx<T>* A, long lda, const BetaGen* bg, const cplx<T>* Q, long ldq, int npw, int nb,
                            int K, cplx<T>* out, long ldo, const EpiH& e, hipStream_t s) {
   if (nb <= 0) return hipSuccess;
-  const int nh = (npw + 1) / 2, tm = ceil_div(nh, 64 * PairCfg<T>::HB), w = pairs_nn_width(tm, nb), tn = ceil_div(nb, w);
+  const int nh = (npw + 1) / 2;
+  // Blocks at most: few projectors leave more waves to hide the epilogue (256 x 144 bands, 18,537 half rows, fp64:
+  // 1 x 3 139 us, 2 x 2 155; generated 1 x 1 112, 1 x 2 121), many want fewer loads (2,048 x 1,088: 2 x 2 35.2 ms,
+  // 1 x 3 39.0; generated, 864 x 480: 1 x 2 3.41 ms, 1 x 1 3.52); the line lies between 256 and 512 projectors
+  // (512 x 256: 2 x 2 634 us, 1 x 2 742; generated 1 x 2 709, 1 x 1 722).
+  const NnShape w = nn_shape(nh, nb, bg ? (K < 512 ? 1 : 2) : (K < 512 ? 3 : 4));
+  const int tm = ceil_div(nh, 64 * w.wa), tn = ceil_div(nb, 16 * w.wb);
   const dim3 grid(tm * tn);
   const BetaGen g = bg ? *bg : BetaGen{};
-#define PW_PNN(NBN)                                                                                                  \
-  case 16 * NBN:                                                                                                     \
-    if (bg)                                                                                                          \
-      hipLaunchKernelGGL((k_pairs_nn<T, NBN, true>), grid, dim3(256), 0, s, A, lda, g, Q, ldq, npw, nh, nb, K, tn, out, \
-                         ldo, e);                                                                                    \
-    else                                                                                                             \
-      hipLaunchKernelGGL((k_pairs_nn<T, NBN, false>), grid, dim3(256), 0, s, A, lda, g, Q, ldq, npw, nh, nb, K, tn, out, \
-                         ldo, e);                                                                                    \
-    break
-  switch (w) {
-    PW_PNN(1);
-    PW_PNN(2);
-    PW_PNN(3);
-    PW_PNN(4);
+#define PW_PNN(WA, WB, OTF)                                                                                          \
+  hipLaunchKernelGGL((k_pairs_nn<T, WA, WB, OTF>), grid, dim3(256), 0, s, A, lda, g, Q, ldq, npw, nh, nb, K, tn, out, \
+                     ldo, e)
+  switch (4 * w.wa + w.wb) {
+    case 10: PW_PNN(2, 2, false); break;
+    case 7: PW_PNN(1, 3, false); break;
+    case 6:
+      if (bg) PW_PNN(1, 2, true); else PW_PNN(1, 2, false);
+      break;
+    default:
+      if (bg) PW_PNN(1, 1, true); else PW_PNN(1, 1, false);
   }
 #undef PW_PNN
   return hipGetLastError();
