@@ -263,13 +263,18 @@ __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
 // x0 .. x0+nx-1 and rows y0 .. y0+ny-1 (mod 128 on the plane) that contain every point of the disc
 // the ball cuts from the plane; a point lies in the ball when dx^2 + (dy^2 + dz^2) <= R^2.  The
 // Gaussian factors as e^{-dx^2/(2 s^2)} e^{-(dy^2 + dz^2)/(2 s^2)}.  Both passes evaluate points
-// through rs_colpart / rs_row / rs_in, so they see the same points and the same values.
-//  * The projection pass holds the plane in LDS (row y in natural x order, word y * 128 + x) and
-//    gives each wave whole (atom, plane) entries: its lanes cover the disc, 16, 32 or 64 columns
-//    at a time, and one reduction across the wave ends each entry.
+// with the same expressions, so they see the same points and the same values.
+//  * The projection pass holds the plane in LDS (row y in x order, word y * 128 + (x ^ 8 (y & 1))) and
+//    gives each wave whole (atom, plane) entries, 8 columns x 8 rows at a time; one reduction across the
+//    wave ends each entry.
 //  * The pass of V(r) adds D P on the x pass itself, where lane (l, t) of wave w holds the 16 values
 //    of row y = 8w + l at x = t + 8k in registers: the wave walks the entries of its 8-row band and
 //    visits only the 8-column blocks that an entry's columns meet (a wave-uniform mask).
+// Both are bound by the issue of vector instructions (four waves on a SIMD) and by the LDS crossbar, so the
+// row factors of the D P pass and the column factors of the projections, which the lanes share, are made by
+// one lane and fetched by the others; fetching the other two as well was slower.  36 bands of 512 atoms,
+// 128 x 128 x 128: projections 370 us and D P pass 543 us; 506 and 660 us with every factor made by every lane
+// and sums across the wave by 36 exchanges.
 // value of lane k of v (k uniform over the wave)
 __device__ __forceinline__ float rs_lane(float v, int k) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
@@ -320,80 +325,114 @@ __device__ __forceinline__ RsEntry rs_entry(const RsLaneEnt& l, int k) {
   return e;
 }
 
-// Row part of row y (0 .. 127): whether it is in the entry's rows, dy, dy^2 + dz^2 and
-// e^{-(dy^2 + dz^2)/(2 s^2)}.
+// Row part of row y (0 .. 127): dy, e^{-(dy^2 + dz^2)/(2 s^2)} and the largest dx^2 inside the ball (negative
+// outside the entry's rows and beyond the ball).
 struct RsRow {
-  bool ok;
-  float dy, s, gyz;
+  float dy, gyz, lim;
 };
-__device__ __forceinline__ RsRow rs_row(const RsDesc& d, const RsEntry& e, int y) {
+__device__ __forceinline__ RsRow rs_rowpart(const RsDesc& d, float dy, float dz2, bool ok) {
   RsRow w;
-  const int oy = (y - e.y0) & 127;
-  w.ok = oy < e.ny;
-  w.dy = fmaf((float)oy, d.hy, e.by);
-  w.s = fmaf(w.dy, w.dy, e.dz2);
-  w.gyz = __builtin_amdgcn_exp2f(w.s * d.k2);
+  w.dy = dy;
+  const float s = fmaf(dy, dy, dz2);
+  w.gyz = __builtin_amdgcn_exp2f(s * d.k2);
+  w.lim = ok ? d.r2 - s : -1.f;
   return w;
+}
+__device__ __forceinline__ RsRow rs_row(const RsDesc& d, const RsEntry& e, int y) {
+  const int oy = (y - e.y0) & 127;
+  return rs_rowpart(d, fmaf((float)oy, d.hy, e.by), e.dz2, oy < e.ny);
 }
 // Column part of column x (0 .. 127): dx, dx^2 and e^{-dx^2/(2 s^2)}.  A column outside the entry's
 // range needs no test of its own: its dx exceeds the disc radius of the enlarged range radius, so
-// the ball test below rejects it (by a margin of 2e-4 of R^2, far above FP32 rounding).
+// the ball test dx^2 <= lim rejects it (by a margin of 2e-4 of R^2, far above FP32 rounding).
 struct RsCol {
   float dx, dx2, gx;
 };
-__device__ __forceinline__ RsCol rs_colpart(const RsDesc& d, const RsEntry& e, int x) {
+__device__ __forceinline__ RsCol rs_colpart(const RsDesc& d, const RsEntry& e, int ox) {
   RsCol c;
-  const int ox = (x - e.x0) & 127;
   c.dx = fmaf((float)ox, d.hx, e.bx);
   c.dx2 = c.dx * c.dx;
   c.gx = __builtin_amdgcn_exp2f(c.dx2 * d.k2);
   return c;
 }
-__device__ __forceinline__ bool rs_in(const RsDesc& d, const RsCol& c, const RsRow& w) {
-  return w.ok && c.dx2 + w.s <= d.r2;
+// value of the lane at byte address a (mod 256; 4 bytes a lane)
+__device__ __forceinline__ float rs_from(float v, int a) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(a, __float_as_int(v)));
 }
+__device__ __forceinline__ int rs_from(int v, int a) { return __builtin_amdgcn_ds_bpermute(a, v); }
 
-__device__ __forceinline__ float rs_wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// a + its partner 32 (16) lanes away in lanes with that bit clear, b + its partner in the others
+__device__ __forceinline__ float rs_half32(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
+  return __int_as_float(p[0]) + __int_as_float(p[1]);
+}
+__device__ __forceinline__ float rs_half16(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_int(a), __float_as_int(b), false, false);
+  return __int_as_float(p[0]) + __int_as_float(p[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float rs_ror_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+// sum over each row of 16 lanes, in all of them
+__device__ __forceinline__ float rs_row_sum(float v) {
+  v = rs_ror_add<0x128>(v);
+  v = rs_ror_add<0x124>(v);
+  v = rs_ror_add<0x122>(v);
+  return rs_ror_add<0x121>(v);
 }
 
 // Adds sum_a sum_m sqrt(Omega) p_m(r - tau_a) dp_{a,m} to this lane's 16 values of row y (x = t + 8k),
 // atoms in the order of the band's entry list.  With p_0 = c0 g, p_m = c1 d_m g and g = gx gyz the
-// term is gx (w0 + dx w1), w0 = gyz (c0 dp_0 + c1 (dy dp_y + dz dp_z)), w1 = gyz c1 dp_x.
+// term is gx (w0 + dx w1), w0 = gyz (c0 dp_0 + c1 (dy dp_y + dz dp_z)), w1 = gyz c1 dp_x.  Of eight entries,
+// lane (l, t) makes w0, w1 and the ball's limit of entry t on row l.
 __device__ __forceinline__ void rs_add_regs(float2 (&r)[16], const RsDesc& rd, int z, int w, int y, int t,
                                             const float2* dp, int lane) {
-  const int e0 = rd.boff[16 * z + w], e1 = rd.boff[16 * z + w + 1];
+  // w is the same in the whole wave: so are the entries and the branches on them
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int e0 = rd.boff[16 * z + wu], e1 = rd.boff[16 * z + wu + 1];
   for (int base = e0; base < e1; base += 64) {
+    // lane k: entry base + k; dp holds (c0 D P_0, c1 D P_x, c1 D P_y, c1 D P_z)
     RsLaneEnt le = rs_empty();
-    float2 q0 = make_float2(0.f, 0.f), q1 = q0, q2 = q0, q3 = q0;
+    float2 q0 = make_float2(0.f, 0.f), q1 = q0, q2 = q0;
     if (base + lane < e1) {
       const RsEnt en = rd.bent[base + lane];
       le = rs_load(en);
       const float2* c = dp + 4 * en.atom;
+      const float2 q3 = c[3];
       q0 = c[0];
       q1 = c[1];
       q2 = c[2];
-      q3 = c[3];
+      q0.x = fmaf(en.dz, q3.x, q0.x);
+      q0.y = fmaf(en.dz, q3.y, q0.y);
     }
     const int cnt = min(64, e1 - base);
-    for (int k = 0; k < cnt; ++k) {
-      const RsEntry e = rs_entry(le, k);
-      const RsRow rw = rs_row(rd, e, y);
-      // dp holds (c0 D P_0, c1 D P_x, c1 D P_y, c1 D P_z)
-      const float ax = fmaf(e.dz, rs_lane(q3.x, k), rs_lane(q0.x, k));
-      const float ay = fmaf(e.dz, rs_lane(q3.y, k), rs_lane(q0.y, k));
-      const float w0x = rw.gyz * fmaf(rw.dy, rs_lane(q2.x, k), ax);
-      const float w0y = rw.gyz * fmaf(rw.dy, rs_lane(q2.y, k), ay);
-      const float w1x = rw.gyz * rs_lane(q1.x, k), w1y = rw.gyz * rs_lane(q1.y, k);
+    for (int k8 = 0; k8 < cnt; k8 += 8) {
+      const int a8 = 4 * (k8 + t);
+      const float dz = rs_from(le.dz, a8);
+      const int yr = rs_from(le.yr, a8);
+      const int oy = (y - yr) & 127;  // the low 16 bits hold y0
+      const RsRow rw = rs_rowpart(rd, fmaf((float)oy, rd.hy, rs_from(le.by, a8)), dz * dz, oy < (yr >> 16));
+      const float w0x = rw.gyz * fmaf(rw.dy, rs_from(q2.x, a8), rs_from(q0.x, a8));
+      const float w0y = rw.gyz * fmaf(rw.dy, rs_from(q2.y, a8), rs_from(q0.y, a8));
+      const float w1x = rw.gyz * rs_from(q1.x, a8), w1y = rw.gyz * rs_from(q1.y, a8);
+      const int n8 = min(8, cnt - k8);
+      int al = 4 * (lane & 56);
+      for (int j = 0; j < n8; ++j, al += 4) {
+        const float u0x = rs_from(w0x, al), u0y = rs_from(w0y, al), u1x = rs_from(w1x, al), u1y = rs_from(w1y, al);
+        const float lim = rs_from(rw.lim, al);
+        RsEntry e;
+        const int xr = rs_lane(le.xr, k8 + j);
+        e.bx = rs_lane(le.bx, k8 + j);
+        const unsigned mask = (unsigned)rs_lane(le.mask, k8 + j);
 #pragma unroll
-      for (int kk = 0; kk < 16; ++kk) {
-        if (e.mask & (1u << kk)) {
-          const RsCol cc = rs_colpart(rd, e, t + 8 * kk);
-          const float gx = rs_in(rd, cc, rw) ? cc.gx : 0.f;
-          r[kk].x += gx * fmaf(cc.dx, w1x, w0x);
-          r[kk].y += gx * fmaf(cc.dx, w1y, w0y);
+        for (int kk = 0; kk < 16; ++kk) {
+          if (mask & (1u << kk)) {
+            const RsCol c = rs_colpart(rd, e, (t - xr + 8 * kk) & 127);  // the low bits of xr hold x0
+            const float gx = c.dx2 <= lim ? c.gx : 0.f;
+            r[kk].x += gx * fmaf(c.dx, u1x, u0x);
+            r[kk].y += gx * fmaf(c.dx, u1y, u0y);
+          }
         }
       }
     }
@@ -794,7 +833,8 @@ hipError_t launch_density128(const float2* SB, const int* colstart, const GridDe
   return hipGetLastError();
 }
 
-// Inverse x pass of row y (as in xinv_row_acc); the row then holds psi in natural x order.
+// Inverse x pass of row y (as in xinv_row_acc); the row then holds psi(x) at word x ^ 8 (y & 1): eight columns of
+// two neighbouring rows lie in different banks.
 __device__ __forceinline__ void xinv_row_store(float2* plane, const float2* tw, int y, int t, int n1max) {
   constexpr int N = 128, A = 8, B = 16;
   const int sy = (((y >> 4) ^ y) & 1) << 3, py = (y & 1) << 3;
@@ -828,13 +868,9 @@ __device__ __forceinline__ void xinv_row_store(float2* plane, const float2* tw, 
   for (int n2 = 0; n2 < B; ++n2) r2[n2] = row[B * t + (n2 ^ t ^ py)];
   SmallDft<float, B, +1>::run(r2);  // r2[k2] = psi at x = t + 8 k2
   wave_sync();
-  // natural x order (no swizzle): the projection loop then addresses a point as y * 128 + x
 #pragma unroll
-  for (int k2 = 0; k2 < B; ++k2) row[t + A * k2] = r2[k2];
+  for (int k2 = 0; k2 < B; ++k2) row[(t + A * k2) ^ py] = r2[k2];
 }
-
-// log2 of the lanes per row of an entry: 16, 32 or 64 columns at a time (64 / lx rows per step).
-__device__ __forceinline__ int rs_lxs(int nx) { return nx <= 16 ? 4 : (nx <= 32 ? 5 : 6); }
 
 // Inverse pass with the projections: a workgroup takes plane z of band b, transforms it inside LDS
 // (inverse y on the active columns, inverse x on every row), then each wave takes entries of the
@@ -868,7 +904,7 @@ __global__ __launch_bounds__(1024) void k_rs_proj128(const float2* __restrict__ 
   __syncthreads();
   float2* pb = part + (long)b * rd.nent * 4;
   // this wave's entries e0 + wv + 16 k, their data loaded one entry per lane
-  for (int base = e0 + wv; base < e1; base += NW * 64) {
+  for (int base = e0 + __builtin_amdgcn_readfirstlane(wv); base < e1; base += NW * 64) {
     RsLaneEnt le = rs_empty();
     if (base + NW * lane < e1) le = rs_load(rd.zent[base + NW * lane]);
     const int cnt = min(64, (e1 - base + NW - 1) / NW);
@@ -876,41 +912,67 @@ __global__ __launch_bounds__(1024) void k_rs_proj128(const float2* __restrict__ 
       const int e = base + NW * k;
       const RsEntry en = rs_entry(le, k);
       float s0x = 0.f, s0y = 0.f, sxx = 0.f, sxy = 0.f, syx = 0.f, syy = 0.f;
-      const int lxs = rs_lxs(en.nx), lx = 1 << lxs, rps = 64 >> lxs;
-      const int lr = lane >> lxs, lc = lane & (lx - 1);
-      if (en.nx > 16 && en.nx <= 32) {
-        // 16 lanes per row, each with two columns 16 apart, four rows per step: one row factor
-        // serves two points
-        const int lr4 = lane >> 4, lc4 = lane & 15;
-        const int xa = (en.x0 + lc4) & (N - 1), xb = (en.x0 + lc4 + 16) & (N - 1);
-        const RsCol ca = rs_colpart(rd, en, xa), cb = rs_colpart(rd, en, xb);
-        const bool okb = lc4 + 16 < en.nx;  // the first column is always in the range
-        for (int q = lr4; q < en.ny; q += 4) {
-          const int y = (en.y0 + q) & (N - 1);
-          const RsRow rw = rs_row(rd, en, y);
-          const float ga = rs_in(rd, ca, rw) ? ca.gx * rw.gyz : 0.f;
-          const float gb = (okb && rs_in(rd, cb, rw)) ? cb.gx * rw.gyz : 0.f;
-          const float2 va = plane[y * N + xa], vb = plane[y * N + xb];
-          const float gxa = ga * ca.dx, gxb = gb * cb.dx;
-          s0x = fmaf(ga, va.x, fmaf(gb, vb.x, s0x));
-          s0y = fmaf(ga, va.y, fmaf(gb, vb.y, s0y));
-          sxx = fmaf(gxa, va.x, fmaf(gxb, vb.x, sxx));
-          sxy = fmaf(gxa, va.y, fmaf(gxb, vb.y, sxy));
-          // sum of g psi over the row's two points, times dy for p_y
-          const float tx = fmaf(ga, va.x, gb * vb.x), ty = fmaf(ga, va.y, gb * vb.y);
-          syx = fmaf(rw.dy, tx, syx);
-          syy = fmaf(rw.dy, ty, syy);
+      if (en.nx <= 64 && en.ny <= 64) {
+        // this lane's column t + 8 l
+        const RsCol cw = rs_colpart(rd, en, t + 8 * l);
+        const int swz = ((en.y0 + l) & 1) << 3;
+        auto cols = [&](auto ncol, int c0) {
+          constexpr int NC = decltype(ncol)::value;
+          float d2[NC], gx[NC], gd[NC];
+          int off[NC];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            const int a = 4 * t + 4 * c0 + 32 * c;
+            const float dx = rs_from(cw.dx, a);
+            gx[c] = rs_from(cw.gx, a);
+            d2[c] = dx * dx;
+            gd[c] = gx[c] * dx;
+            off[c] = ((en.x0 + c0 + 8 * c + t) & (N - 1)) ^ swz;
+          }
+          int yo = (en.y0 + l) * N;
+          float fq = (float)l;
+          for (int q = 0; q < en.ny; q += 8, fq += 8.f, yo += 8 * N) {
+            const RsRow rw = rs_rowpart(rd, fmaf(fq, rd.hy, en.by), en.dz2, true);
+            const float2* row = plane + (yo & (N * N - 1));
+            float2 v[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) v[c] = row[off[c]];
+            float tx = 0.f, ty = 0.f, mx = 0.f, my = 0.f;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+              const bool in = d2[c] <= rw.lim;
+              const float ga = in ? gx[c] : 0.f, gb = in ? gd[c] : 0.f;
+              tx = fmaf(ga, v[c].x, tx);
+              ty = fmaf(ga, v[c].y, ty);
+              mx = fmaf(gb, v[c].x, mx);
+              my = fmaf(gb, v[c].y, my);
+            }
+            const float gyz = rw.gyz, gdy = gyz * rw.dy;
+            s0x = fmaf(gyz, tx, s0x);
+            s0y = fmaf(gyz, ty, s0y);
+            sxx = fmaf(gyz, mx, sxx);
+            sxy = fmaf(gyz, my, sxy);
+            syx = fmaf(gdy, tx, syx);
+            syy = fmaf(gdy, ty, syy);
+          }
+        };
+        for (int c0 = 0; c0 < en.nx; c0 += 32) {
+          const int nx = en.nx - c0;
+          if (nx > 24) cols(std::integral_constant<int, 4>{}, c0);
+          else if (nx > 16) cols(std::integral_constant<int, 3>{}, c0);
+          else if (nx > 8) cols(std::integral_constant<int, 2>{}, c0);
+          else cols(std::integral_constant<int, 1>{}, c0);
         }
       } else {
-        for (int xc = 0; xc < en.nx; xc += lx) {
-          const int x = (en.x0 + xc + lc) & (N - 1);
-          const RsCol cc = rs_colpart(rd, en, x);
-          const bool colok = xc + lc < en.nx;  // lanes past the range would alias its first columns
-          for (int q = lr; q < en.ny; q += rps) {
+        for (int xc = 0; xc < en.nx; xc += 64) {
+          const int x = (en.x0 + xc + lane) & (N - 1);
+          const RsCol cc = rs_colpart(rd, en, (x - en.x0) & (N - 1));
+          const bool colok = xc + lane < en.nx;  // lanes past the range would alias its first columns
+          for (int q = 0; q < en.ny; ++q) {
             const int y = (en.y0 + q) & (N - 1);
             const RsRow rw = rs_row(rd, en, y);
-            const float gg = (colok && rs_in(rd, cc, rw)) ? cc.gx * rw.gyz : 0.f;
-            const float2 v = plane[y * N + x];
+            const float gg = (colok && cc.dx2 <= rw.lim) ? cc.gx * rw.gyz : 0.f;
+            const float2 v = plane[y * N + (x ^ ((y & 1) << 3))];
             const float gxv = gg * cc.dx, gyv = gg * rw.dy;
             s0x = fmaf(gg, v.x, s0x);
             s0y = fmaf(gg, v.y, s0y);
@@ -921,17 +983,20 @@ __global__ __launch_bounds__(1024) void k_rs_proj128(const float2* __restrict__ 
           }
         }
       }
-      s0x = rs_wave_sum(s0x);
-      s0y = rs_wave_sum(s0y);
-      sxx = rs_wave_sum(sxx);
-      sxy = rs_wave_sum(sxy);
-      syx = rs_wave_sum(syx);
-      syy = rs_wave_sum(syy);
-      if (lane == 0) {
+      // rows of 16 lanes: u = sums of (s0x, sxx, s0y, sxy), v = (syx, syx, syy, syy)
+      const float u = rs_row_sum(rs_half16(rs_half32(s0x, s0y), rs_half32(sxx, sxy)));
+      const float h = rs_half32(syx, syy), v = rs_row_sum(rs_half16(h, h));
+      if ((lane & 15) == 0) {
         const float c0 = rd.c0, c1 = rd.c1, c1z = rd.c1 * en.dz;
-        float4* o = reinterpret_cast<float4*>(pb + (long)e * 4);
-        o[0] = make_float4(c0 * s0x, c0 * s0y, c1 * sxx, c1 * sxy);
-        o[1] = make_float4(c1 * syx, c1 * syy, c1z * s0x, c1z * s0y);
+        float* o = reinterpret_cast<float*>(pb + (long)e * 4);
+        const int im = lane >> 5;  // 0: real parts, 1: imaginary parts
+        if (lane & 16) {
+          o[2 + im] = c1 * u;
+        } else {
+          o[im] = c0 * u;
+          o[4 + im] = c1 * v;
+          o[6 + im] = c1z * u;
+        }
       }
     }
   }

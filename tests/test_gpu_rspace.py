@@ -74,6 +74,18 @@ def test_rspace_apply_h_matches_oracle_realspace(name, nb, nsigma):
     h.close()
 
 
+@pytest.mark.parametrize("nsigma", [0.8, 1.9, 3.2, 4.6, 6.3])
+def test_rspace_range_widths(nsigma):
+    """Ranges of an atom of at most 8, 19, 32, 46 and 63 columns and rows: every number of 8-column groups of the
+    projection, its second group of 32, and ranges that wrap; the tolerance of the routes above."""
+    cell, model, h, X, p, R, out = rs_case("si64", 2, 77, nsigma=nsigma)
+    ref = O.apply_h(model, X)
+    err = float(np.abs(out - ref[p]).max() / np.abs(ref).max())
+    say("rspace apply_h si64 R", R, "columns", 2 * R / (cell.L[0] / 128), "rel err", err)
+    assert err < 2e-5
+    h.close()
+
+
 @pytest.mark.parametrize("ncells,grid", [((1, 1, 1), (128, 128, 96)), ((1, 1, 2), (128, 128, 192))])
 def test_rspace_apply_h_other_z_grids(ncells, grid):
     # z planes other than 128 (and an orthorhombic cell: different steps along x, y and z)
