@@ -868,22 +868,42 @@ struct Engine {
     double* dS = h->at<double>(P.lay.ework);
     double* piv_d = h->at<double>(P.lay.scal) + 3;  // [8, 8 + 2 kLanczosChunk) hold the Lanczos pairs
     if (min_pivot > 0.0) PW_HIP(launch_diag_copy(S, nb, nb, dS, h->stream));
-    rocblas_status rs = rocsolver_zpotrf(h->blas, rocblas_fill_lower, nb, Sz, nb, info_d);
+    const bool small = dense_small_supported(nb);
+    rocblas_status rs = rocblas_status_success;
+    if (small)
+      PW_HIP(launch_potrf_small(S, nb, info_d, h->stream));
+    else
+      rs = rocsolver_zpotrf(h->blas, rocblas_fill_lower, nb, Sz, nb, info_d);
     if (rs != rocblas_status_success)
       return fail(h, PW_EDEVICE, std::string("rocsolver_zpotrf: ") + rocblas_status_to_string(rs));
     if (min_pivot > 0.0) PW_HIP(launch_min_pivot(S, nb, nb, dS, piv_d, h->stream));
-    int info[2] = {0, 0};
+    int info = 0;
     double piv = 1.0;
-    PW_HIP(hipMemcpyAsync(&info[0], info_d, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    PW_HIP(hipMemcpyAsync(&info, info_d, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     if (min_pivot > 0.0) PW_HIP(hipMemcpyAsync(&piv, piv_d, sizeof(double), hipMemcpyDeviceToHost, h->stream));
     PW_HIP(hipStreamSynchronize(h->stream));
-    if (info[0] > 0) {
+    if (info > 0) {
       h->tend(PW_PH_EIGSOLVE);
       return fail(h, PW_ENOTPD, "Cholesky of the Gram matrix failed (rank-deficient block)");
     }
     if (min_pivot > 0.0 && !(piv > min_pivot)) {
       h->tend(PW_PH_EIGSOLVE);
       return fail(h, PW_ENOTPD, "Gram matrix numerically singular (a Cholesky pivot below the drop tolerance)");
+    }
+    if (small) {
+      // the partials are no longer needed: their storage (2 nb^2 at least) holds X, then the reflectors, tau,
+      // the subdiagonal and the tridiagonal eigenvectors
+      double2* V = parts;
+      double2* tau = V + (size_t)nb * nb;
+      double* E = reinterpret_cast<double*>(tau + nb);
+      double* Z = E + nb;
+      PW_HIP(launch_standard_small(S, Hs, nb, V, h->stream));
+      PW_HIP(launch_hetrd_small(Hs, nb, V, tau, eig_d, E, h->stream));
+      rs = rocsolver_dstedc(h->blas, rocblas_evect_tridiagonal, nb, eig_d, E, Z, nb, info_d + 1);
+      if (rs != rocblas_status_success)
+        return fail(h, PW_EDEVICE, std::string("rocsolver_dstedc: ") + rocblas_status_to_string(rs));
+      PW_HIP(launch_back_small(V, tau, S, Z, nb, Hs, h->stream));
+      return dense_info(info_d + 1);
     }
     rs = rocblas_ztrsm(h->blas, rocblas_side_left, rocblas_fill_lower, rocblas_operation_none,
                        rocblas_diagonal_non_unit, nb, nb, &one, Sz, nb, Hz, nb);
@@ -900,10 +920,16 @@ struct Engine {
                        rocblas_diagonal_non_unit, nb, nb, &one, Sz, nb, Hz, nb);
     if (rs != rocblas_status_success)
       return fail(h, PW_EDEVICE, std::string("rocblas_ztrsm: ") + rocblas_status_to_string(rs));
+    return dense_info(info_d + 1);
+  }
+
+  // End of the dense solve: its convergence flag.
+  pw_status dense_info(const int* info_d) {
+    int info = 0;
     h->tend(PW_PH_EIGSOLVE);
-    PW_HIP(hipMemcpyAsync(&info[1], info_d + 1, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    PW_HIP(hipMemcpyAsync(&info, info_d, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     PW_HIP(hipStreamSynchronize(h->stream));
-    if (info[1] > 0) return fail(h, PW_ENUMERIC, "dense eigensolver did not converge");
+    if (info > 0) return fail(h, PW_ENUMERIC, "dense eigensolver did not converge");
     return PW_OK;
   }
 

@@ -313,6 +313,17 @@ hipError_t launch_scale_cols_lam(const double2* in, long ldi, cplx<T>* out, long
 // Hermitian part: A <- (A + A^H)/2, n x n complex double
 hipError_t launch_hermitize(double2* A, long lda, int n, hipStream_t s);
 // Hermitian matrix from its upper triangle: A(i, j) <- conj(A(j, i)) for i > j, Im A(i, i) <- 0
+// Small dense problems (dense_small.hip), matrices n x n with leading dimension n.
+bool dense_small_supported(int n);
+// S = L L^H in S's lower triangle; *info = 0, or 1 + the first column with a pivot that is not positive.
+hipError_t launch_potrf_small(double2* S, int n, int* info, hipStream_t s);
+// H <- L^{-1} H L^{-H} (H Hermitian; X: n x n scratch).
+hipError_t launch_standard_small(const double2* L, double2* H, int n, double2* X, hipStream_t s);
+// Q^H A Q = T (A's lower triangle is read): reflectors to V (n x n - 1), tau, T's diagonal to D, subdiagonal to E.
+hipError_t launch_hetrd_small(const double2* A, int n, double2* V, double2* tau, double* D, double* E, hipStream_t s);
+// C = L^{-H} Q Z (Z real).
+hipError_t launch_back_small(const double2* V, const double2* tau, const double2* L, const double* Z, int n, double2* C,
+                             hipStream_t s);
 hipError_t launch_mirror_upper(double2* A, long lda, int n, hipStream_t s);
 // r_j = || W_j - lam_j X_j ||_2 with double accumulation; flag[0] |= non-finite seen
 template <typename T>

@@ -97,17 +97,19 @@ def test_steps_of_different_widths_share_the_planes(degree):
 
 
 @pytest.mark.parametrize("prec", [pw.PW_FP64, pw.PW_MIXED])
-@pytest.mark.parametrize("nbands,ld_extra", [(17, 0), (49, 1), (101, 2)])
+@pytest.mark.parametrize("nbands,ld_extra", [(17, 0), (49, 1), (101, 2), (145, 0)])
 def test_gram_and_rotation_tiles(prec, nbands, ld_extra):
     """Rayleigh-Ritz alone (degree 0) over the tiles of the complex products, their remainders in bands, rows and K
-    values, and the Gram tiles left out below the diagonal: Ritz values as the FP64 oracle's, X^H X = I.  Relative
+    values, the Gram tiles left out below the diagonal, and both dense solvers (one workgroup from 4 to 144 bands, rows
+    in steps of 48 and 64): Ritz values as the FP64 oracle's, X^H X = I.  Relative
     tolerances: 1e-11 in FP64 and 2e-5 in FP32, the accuracy of H X with a margin for the FP64 solve."""
     tol = 1e-11 if prec == pw.PW_FP64 else 2e-5
     cell = cell_with_atoms(3, nbands=nbands)
     m = O.model_from_cell(cell)
     h = pw.Handle(cell, prec, flags=0)
     inv = np.argsort(pw.permutation_to(m.miller, h.gvectors()))
-    for nb in {17: (1, 2, 15, 16, 17), 49: (31, 32, 33, 47, 48, 49), 101: (63, 64, 65, 80, 95, 97, 101)}[nbands]:
+    for nb in {17: (1, 2, 3, 4, 5, 15, 16, 17), 49: (31, 32, 33, 47, 48, 49), 101: (63, 64, 65, 80, 95, 96, 97, 101),
+               145: (127, 128, 129, 143, 144, 145)}[nbands]:
         X = synth.random_block(h.npw, nb, 3 + nb)
         X = X if prec == pw.PW_FP64 else X.astype(np.complex64)
         Xd = h.to_device(X, h.npw + ld_extra)
