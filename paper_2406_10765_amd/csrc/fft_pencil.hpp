@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256) void k_pencil_yinv(const cplx<T>* __restrict__
     for (int n1 = 0; n1 < A; ++n1) {
       const int y = B * n1 + t + TT * i;
       const int n2 = 2 * y < N ? y : y - N;
-      r1[i][n1] = (n2 <= m && -n2 <= m) ? sb[cs + n2 + m] : mk<T>(0, 0);
+      r1[i][n1] = (!grid_empty(A * B, B, n1) && n2 <= m && -n2 <= m) ? sb[cs + n2 + m] : mk<T>(0, 0);
     }
   if (l >= PL::LPW) return;  // the lanes past the last line (TT does not divide 64)
   PL::template stage1<+1>(r1, t, tw);
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void k_pencil_yfwd(cplx<T>* __restrict__ SB, c
     for (int k2 = 0; k2 < B; ++k2) {
       const int y = t + TT * j + A * k2;
       const int n2 = 2 * y < N ? y : y - N;
-      if (n2 <= m && -n2 <= m) sb[cs + n2 + m] = cscale<T>(r2[j][k2], scale);
+      if (!grid_empty(A * B, A, k2) && n2 <= m && -n2 <= m) sb[cs + n2 + m] = cscale<T>(r2[j][k2], scale);
     }
   }
 }
@@ -208,7 +208,7 @@ __device__ __forceinline__ void pencil_x_inv(const cplx<T>* __restrict__ row, in
     for (int n1 = 0; n1 < A; ++n1) {
       const int x = B * n1 + t + TT * i;
       const int k = 2 * x < N ? x : x - N;
-      r1[i][n1] = (act && k <= n1max && -k <= n1max) ? row[k + n1max] : mk<T>(0, 0);
+      r1[i][n1] = (!grid_empty(A * B, B, n1) && act && k <= n1max && -k <= n1max) ? row[k + n1max] : mk<T>(0, 0);
     }
   PL::template stage1<+1>(r1, t, tw);
   PL::first_to_second(w, t, r1, r2);
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256) void k_pencil_x(cplx<T>* __restrict__ G1, cons
       for (int q1 = 0; q1 < A; ++q1) {
         const int x = B * q1 + t + TT * i;
         const int k = 2 * x < N ? x : x - N;
-        if (act && k <= g.n1max && -k <= g.n1max) row[k + g.n1max] = r1[i][q1];
+        if (!grid_empty(A * B, B, q1) && act && k <= g.n1max && -k <= g.n1max) row[k + g.n1max] = r1[i][q1];
       }
     }
   }

@@ -42,9 +42,10 @@ namespace pw {
 // Bound by the issue of the butterflies and LDS accesses; sticks and barriers of one workgroup wait under
 // the others of the compute unit.  Per band of H X (us), before with a workgroup barrier per exchange and
 // zeroing, scatter and gather of the whole plane, and now:
-//   FP32  54^2 0.83 -> 0.64 (144 bands), 64^2 0.88 -> 0.76, 81^2 2.20 -> 1.63, 96^2 4.14 -> 3.98 (440 bands),
-//         108^2 7.76 (pencil form) -> 6.87
-//   FP64  54^2 1.40 -> 1.15, 64^2 1.65 -> 1.20, 81^2 5.28 -> 3.17 (128 bands), 96^2 10.3 -> 8.54
+//   FP32  54^2 0.83 -> 0.60 (144 bands), 64^2 0.88 -> 0.71, 81^2 2.20 -> 1.51, 96^2 4.14 -> 3.81 (440 bands),
+//         108^2 7.76 (pencil form) -> 6.18
+//   FP64  54^2 1.40 -> 1.05, 64^2 1.65 -> 1.15, 81^2 5.28 -> 2.95 (128 bands), 96^2 10.3 -> 8.0
+// of which leaving out the empty blocks (grid_empty) and the products with quarter turns gives 5 to 10%.
 template <typename T, int N> struct PlanePitch;
 template <> struct PlanePitch<float, 24> { static constexpr int TT = 2, R = 30, BX = 7, AX = 5, WPE = 1, LOOP = 0; };
 template <> struct PlanePitch<float, 27> { static constexpr int TT = 3, R = 27, BX = 9, AX = 3, WPE = 1, LOOP = 0; };
@@ -148,7 +149,7 @@ __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
         for (int n1 = 0; n1 < A; ++n1) {
           const int e = B * n1 + t + TT * i;
           const int n2 = 2 * e < N ? e : e - N;
-          r1[i][n1] = (n2 <= m && -n2 <= m && S::has1(t, i)) ? sb[cs + n2 + m] : zero;
+          r1[i][n1] = (!grid_empty(N, B, n1) && n2 <= m && -n2 <= m && S::has1(t, i)) ? sb[cs + n2 + m] : zero;
         }
 #pragma unroll
       for (int i = 0; i < I1; ++i) SmallDft<T, A, +1>::run(r1[i]);
@@ -174,7 +175,9 @@ __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
         for (int n1 = 0; n1 < A; ++n1) {
           const int x = B * n1 + t + TT * i;
           const int k = 2 * x < N ? x : x - N;
-          r1[i][n1] = (k <= n1max && -k <= n1max && S::has1(t, i)) ? plane[S::at(y, k + n1max)] : zero;
+          r1[i][n1] = (!grid_empty(N, B, n1) && k <= n1max && -k <= n1max && S::has1(t, i))
+                          ? plane[S::at(y, k + n1max)]
+                          : zero;
         }
 #pragma unroll
       for (int i = 0; i < I1; ++i) SmallDft<T, A, +1>::run(r1[i]);
@@ -219,7 +222,8 @@ __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
         for (int q1 = 0; q1 < A; ++q1) {
           const int x = B * q1 + t + TT * i;
           const int k = 2 * x < N ? x : x - N;
-          if (row_on && S::has1(t, i) && k <= n1max && -k <= n1max) plane[S::at(y, k + n1max)] = r1[i][q1];
+          if (!grid_empty(N, B, q1) && row_on && S::has1(t, i) && k <= n1max && -k <= n1max)
+            plane[S::at(y, k + n1max)] = r1[i][q1];
         }
     }
     __syncthreads();
@@ -245,7 +249,8 @@ __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
         for (int k2 = 0; k2 < B; ++k2) {
           const int e = t + TT * j + A * k2;
           const int n2 = 2 * e < N ? e : e - N;
-          if (n2 <= m && -n2 <= m && S::has2(t, j)) sb[cs + n2 + m] = cscale<T>(r2[j][k2], scale);
+          if (!grid_empty(N, A, k2) && n2 <= m && -n2 <= m && S::has2(t, j))
+            sb[cs + n2 + m] = cscale<T>(r2[j][k2], scale);
         }
       }
     }
@@ -490,7 +495,7 @@ __global__ __launch_bounds__(1024) void k_plane128(float2* __restrict__ SB, cons
       for (int n1 = 0; n1 < A; ++n1) {
         const int y = B * n1 + t + 8 * i;
         const int n2 = y < N / 2 ? y : y - N;
-        r1[i][n1] = (n2 <= m && -n2 <= m) ? sb[cs + n2 + m] : zero;
+        r1[i][n1] = (!grid_empty(N, B, n1) && n2 <= m && -n2 <= m) ? sb[cs + n2 + m] : zero;
       }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -545,7 +550,7 @@ __global__ __launch_bounds__(1024) void k_plane128(float2* __restrict__ SB, cons
       for (int n1 = 0; n1 < A; ++n1) {
         const int x = B * n1 + t + 8 * i;
         const int k = x < N / 2 ? x : x - N;
-        r1[i][n1] = (k <= n1max && -k <= n1max) ? row[(k + n1max) ^ sy] : zero;
+        r1[i][n1] = (!grid_empty(N, B, n1) && k <= n1max && -k <= n1max) ? row[(k + n1max) ^ sy] : zero;
       }
     wave_sync();
 #pragma unroll
@@ -590,7 +595,7 @@ __global__ __launch_bounds__(1024) void k_plane128(float2* __restrict__ SB, cons
       for (int q1 = 0; q1 < A; ++q1) {
         const int x = B * q1 + t + 8 * i;
         const int k = x < N / 2 ? x : x - N;
-        if (k <= n1max && -k <= n1max) row[(k + n1max) ^ sy] = r1[i][q1];
+        if (!grid_empty(N, B, q1) && k <= n1max && -k <= n1max) row[(k + n1max) ^ sy] = r1[i][q1];
       }
   }
   __syncthreads();
@@ -640,7 +645,7 @@ __global__ __launch_bounds__(1024) void k_plane128(float2* __restrict__ SB, cons
       for (int k2 = 0; k2 < B; ++k2) {
         const int y = t + A * k2;
         const int n2 = y < N / 2 ? y : y - N;
-        if (n2 <= m && -n2 <= m) sb[cs + n2 + m] = cscale<T>(r2[k2], scale);
+        if (!grid_empty(N, A, k2) && n2 <= m && -n2 <= m) sb[cs + n2 + m] = cscale<T>(r2[k2], scale);
       }
   }
 }
@@ -662,7 +667,7 @@ __device__ __forceinline__ void yinv_load(const float2* __restrict__ sb, const i
     for (int n1 = 0; n1 < A; ++n1) {
       const int y = B * n1 + t + 8 * i;
       const int n2 = y < N / 2 ? y : y - N;
-      r[i][n1] = (n2 <= m && -n2 <= m) ? sb[cs + n2 + m] : make_float2(0.f, 0.f);
+      r[i][n1] = (!grid_empty(N, B, n1) && n2 <= m && -n2 <= m) ? sb[cs + n2 + m] : make_float2(0.f, 0.f);
     }
 }
 
@@ -723,7 +728,7 @@ __device__ __forceinline__ void xinv_row_acc(float2* plane, const float2* tw, in
     for (int n1 = 0; n1 < A; ++n1) {
       const int x = B * n1 + t + 8 * i;
       const int k = x < N / 2 ? x : x - N;
-      r1[i][n1] = (k <= n1max && -k <= n1max) ? row[(k + n1max) ^ sy] : make_float2(0.f, 0.f);
+      r1[i][n1] = (!grid_empty(N, B, n1) && k <= n1max && -k <= n1max) ? row[(k + n1max) ^ sy] : make_float2(0.f, 0.f);
     }
   wave_sync();
 #pragma unroll
@@ -802,6 +807,9 @@ __global__ void k_density_groups(const double* __restrict__ part, int ngroups, l
   }
 }
 
+// the grids that the plane kernels assume (grid_empty)
+static bool alias_free(const GridDesc& g) { return g.n1 > 3 * g.n1max && g.n2 > 3 * g.n2max; }
+
 hipError_t launch_density_groups(const double* part, int ngroups, long nr, double* rho, bool first, hipStream_t s) {
   hipLaunchKernelGGL(k_density_groups, dim3(stride_blocks(nr)), dim3(256), 0, s, part, ngroups, nr, rho, first ? 1 : 0);
   return hipGetLastError();
@@ -846,7 +854,7 @@ __device__ __forceinline__ void xinv_row_store(float2* plane, const float2* tw, 
     for (int n1 = 0; n1 < A; ++n1) {
       const int x = B * n1 + t + 8 * i;
       const int k = x < N / 2 ? x : x - N;
-      r1[i][n1] = (k <= n1max && -k <= n1max) ? row[(k + n1max) ^ sy] : make_float2(0.f, 0.f);
+      r1[i][n1] = (!grid_empty(N, B, n1) && k <= n1max && -k <= n1max) ? row[(k + n1max) ^ sy] : make_float2(0.f, 0.f);
     }
   wave_sync();
 #pragma unroll
@@ -1033,7 +1041,7 @@ __global__ void k_rs_reduce(const float2* __restrict__ part, RsDesc rd, int nbt,
 hipError_t launch_rs_proj128(const float2* SB, const int* colstart, const GridDesc& g, const float2* tw,
                              const RsDesc& rd, int nbatch, float2* part, hipStream_t s) {
   if (nbatch <= 0 || rd.nent <= 0) return hipSuccess;
-  if (g.n1 != 128 || g.n2 != 128 || g.n1a > 128) return hipErrorInvalidValue;
+  if (g.n1 != 128 || g.n2 != 128 || !alias_free(g)) return hipErrorInvalidValue;
   const size_t lds = (size_t)(128 * 128 + 128) * sizeof(float2);
   hipLaunchKernelGGL(k_rs_proj128, dim3(g.n3, nbatch), dim3(1024), lds, s, SB, colstart, g, tw, rd, part);
   return hipGetLastError();
@@ -1051,7 +1059,7 @@ hipError_t launch_plane128_nl(float2* SB, const float* V, int nbatch, const int*
                               const float2* tw, float scale, const RsDesc& rd, const float2* dp, int nproj,
                               hipStream_t s) {
   if (nbatch <= 0) return hipSuccess;
-  if (g.n1 != 128 || g.n2 != 128 || g.n1a > 128) return hipErrorInvalidValue;
+  if (g.n1 != 128 || g.n2 != 128 || !alias_free(g)) return hipErrorInvalidValue;
   const size_t lds = (size_t)(128 * 128 + 128) * sizeof(float2);
   hipLaunchKernelGGL(k_plane128<true>, dim3(g.n3, nbatch), dim3(1024), lds, s, SB, V, colstart, g, tw, scale, rd, dp,
                      nproj);
@@ -1112,7 +1120,7 @@ __global__ __launch_bounds__(256) void k_sticks_inv_n(const cplx<T>* __restrict_
   for (int i = 0; i < I1; ++i)
 #pragma unroll
     for (int n1 = 0; n1 < A; ++n1) {
-      const int e = act ? stick_index(B * n1 + t + TT * i, h, N) : -1;
+      const int e = act && !grid_empty(N, B, n1) ? stick_index(B * n1 + t + TT * i, h, N) : -1;
       r1[i][n1] = e >= 0 ? xs[e] : mk<T>(0, 0);
     }
   __syncthreads();  // twiddles
@@ -1208,7 +1216,7 @@ __global__ __launch_bounds__(256) void k_sticks_fwd_n(const cplx<T>* __restrict_
 #pragma unroll
     for (int k2 = 0; k2 < B; ++k2) {
       const int e = stick_index(k1 + A * k2, h, N);
-      if (e >= 0) {
+      if (!grid_empty(N, A, k2) && e >= 0) {
         if constexpr (UPD) {
           const long i = (long)sk.off + e;
           const float2 y = u.Y[(long)b * u.ldy + i];
@@ -1344,6 +1352,7 @@ bool plane_n_supported(int n1, int n2, int real_bytes, size_t max_lds) {
 template <typename T>
 hipError_t launch_plane_n(cplx<T>* SB, const T* V, int nbatch, const int* colstart, const GridDesc& g,
                           const cplx<T>* tw, T scale, hipStream_t s) {
+  if (!alias_free(g)) return hipErrorInvalidValue;
   if constexpr (std::is_same<T, float>::value) {
     if (g.n1 == 128) {
       const size_t lds = (size_t)(128 * 128 + 128) * sizeof(float2);
@@ -1366,23 +1375,19 @@ hipError_t launch_plane_n(cplx<T>* SB, const T* V, int nbatch, const int* colsta
 
 void pw_allow_large_lds_plane_n() {
   const int bytes = (int)(160 * 1024);
-#define PW_ALLOW(NN, AA, BB)                                                                                     \
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane_w<float, AA, BB>),                           \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);                                 \
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane_w<double, AA, BB>),                          \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  auto allow = [&](const void* k) {
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  };
+#define PW_ALLOW(NN, AA, BB)                                     \
+  allow(reinterpret_cast<const void*>(&k_plane_w<float, AA, BB>)); \
+  allow(reinterpret_cast<const void*>(&k_plane_w<double, AA, BB>));
   PW_PLANE_SIZES(PW_ALLOW)
 #undef PW_ALLOW
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane_w<float, 6, 18>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane128<false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_plane128<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            bytes);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rs_proj128), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            bytes);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_density128), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            bytes);
+  allow(reinterpret_cast<const void*>(&k_plane_w<float, 6, 18>));
+  allow(reinterpret_cast<const void*>(&k_plane128<false>));
+  allow(reinterpret_cast<const void*>(&k_plane128<true>));
+  allow(reinterpret_cast<const void*>(&k_rs_proj128));
+  allow(reinterpret_cast<const void*>(&k_density128));
 }
 
 template hipError_t launch_plane_n<float>(cplx<float>*, const float*, int, const int*, const GridDesc&,

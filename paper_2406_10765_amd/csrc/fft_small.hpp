@@ -78,7 +78,10 @@ struct SmallDft {
         SmallDft<T, F, SG>::run(u);
         sfor<F>([&](auto ki) {
           constexpr int kf = decltype(ki)::value;
-          if constexpr (g * kf != 0) {
+          if constexpr (g * kf != 0 && 4 * g * kf % S == 0) {  // a quarter, half or three quarter turn
+            constexpr int q = 4 * g * kf / S % 4;
+            u[kf] = q == 2 ? mk<T>(-u[kf].x, -u[kf].y) : cmuli<T>(u[kf], q == 1 ? SG : -SG);
+          } else if constexpr (g * kf != 0) {
             constexpr int turn = 2 * g * kf > S ? g * kf - S : g * kf;  // angle within [-pi, pi]
             constexpr double ang = SG * 2.0 * kPiC * (double)turn / (double)S;
             constexpr T wc = (T)ccos(ang), ws = (T)csin(ang);
@@ -99,6 +102,13 @@ struct SmallDft {
     }
   }
 };
+
+// A plan's grids have N >= 3 nmax + 1 points along each axis, so points nmax < e < N - nmax hold no plane wave:
+// whether the points S block .. S block + S - 1 are all empty, whatever the sphere.  The sized kernels leave out
+// the loads, terms and stores of such blocks.
+__device__ __host__ __forceinline__ constexpr bool grid_empty(int N, int S, int block) {
+  return S * block > (N - 1) / 3 && S * block + S - 1 < N - (N - 1) / 3;
+}
 
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
 

@@ -117,3 +117,27 @@ def test_density_work_buffer_limit(prec):
             with pytest.raises(pw.PWError, match="work buffer"):
                 h.density(X, np.ones(nb))
         h.close()
+
+
+@pytest.mark.parametrize("n", [24, 27, 32, 48, 54, 64, 81, 96, 108, 128])
+@pytest.mark.parametrize("prec", [pw.PW_FP64, pw.PW_MIXED])
+def test_smallest_alias_free_grids(n, prec):
+    """The largest sphere each size allows, n > 3 nmax, across the planes and along z: the blocks of grid points that
+    the kernels leave out start right behind it.  H X as above."""
+    nmax = (n - 1) // 3
+    step = 2.0 * np.pi / 5.0  # ecut 12.5: |G| <= 5
+    for grid, top in (((n, n, 24), (nmax, nmax, 7)), ((24, 24, n), (7, 7, nmax))):
+        L = tuple((k + 0.4) * step for k in top)
+        cell = synth.Cell(L=L, tau=np.array([[1.0, 2.0, 0.5], [0.3 * L[0], 0.6 * L[1], 3.0]]), ecut=12.5, nbands=2)
+        m = O.model_from_cell(cell, grid=grid)
+        assert tuple(np.abs(m.miller).max(axis=0)) == top
+        h = pw.Handle(cell, prec, fft_n=grid)
+        p = pw.permutation_to(m.miller, h.gvectors())
+        X = synth.random_block(m.npw, 2, 5)
+        if prec == pw.PW_MIXED:
+            X = X.astype(np.complex64).astype(np.complex128)
+        ref = O.apply_h(m, X)[p]
+        err = float(np.abs(h.to_host(h.apply_h(h.to_device(X[p]))) - ref).max() / np.abs(ref).max())
+        print("alias-free grid", grid, "prec", prec, "npw", m.npw, "err", err, flush=True)
+        assert err < (1e-12 if prec == pw.PW_FP64 else 2e-5)
+        h.close()
