@@ -516,23 +516,25 @@ namespace {
 // Tile shapes of the projection, by what a K tile costs a compute unit that runs `per_cu` of them.
 struct ProjShape {
   int rows, bands, per_cu;
-  double us;  // per K tile of 16 words
+  double us, lat;  // per K tile of 16 words: of a full compute unit's time, and from its loads to its products
 };
-constexpr ProjShape kProj[4] = {{256, 128, 1, 1.7}, {128, 64, 2, 1.1}, {64, 32, 3, 0.9}, {256, 16, 1, 2.0}};
+constexpr ProjShape kProj[4] = {
+    {256, 128, 1, 1.7, 1.7}, {128, 64, 2, 0.55, 0.9}, {64, 32, 3, 0.3, 0.3}, {256, 16, 1, 2.0, 2.0}};
 
-// The largest tile that the product fills; up to 16 bands (a Lanczos vector) the table's one read is the
+// The largest tile that the product fills: 64 x 32 below 65,536 outputs (256 projectors x 144 bands, 18,537 half
+// rows: 38.5 us, 44.5 us in 128 x 64; 864 x 440: 882 and 534 us); up to 16 bands (a Lanczos vector) the table's one read is the
 // cost and the narrow tile keeps three stages of it in flight (one band, 2,048 projectors: 0.48 ms, 5.0 TB/s
 // of a 2.4 GB table; 1.65 ms as complex products in 256 x 128 tiles).
 int proj_shape(int M, int nb) {
   if (nb <= 16 && M >= 256) return 3;
   if (M >= 256 && nb >= 96 && (long)M * nb >= (1L << 17)) return 0;
-  if (M >= 128 && nb >= 48) return 1;
+  if (M >= 128 && nb >= 48 && (long)M * nb >= (1L << 16)) return 1;
   return 2;
 }
 
 }  // namespace
 
-// K splits: the number that minimises rounds x (K tiles per workgroup + its start and end) plus the
+// K splits: the number that minimises the busiest compute unit's K tiles + the start and end of each round + the
 // partials' traffic, at most cap (what the partials' buffer holds) and 64.  With 72 tiles (2,048 projectors,
 // 1,088 bands) 7 splits fill 504 of 512 places in two rounds; their partials are an eighth of those of the
 // 57 short chunks the complex products balanced their tail with (reduction 0.41 ms there).  With one tile
@@ -546,8 +548,9 @@ int pairs_proj_splits(int M, int nb, int ktiles, long cap) {
   for (int n = 1; n <= 64 && n <= ktiles && (n == 1 || n <= cap); ++n) {
     const int chunk = ceil_div(ktiles, n);
     if (ceil_div(ktiles, chunk) != n) continue;
-    const double rounds = (double)((tiles * n + slots - 1) / slots);
-    const double c = rounds * (chunk * s.us + 6.0) + 0.04 * n + n * (double)M * nb * 32.0 / 4.5e6;
+    const double rounds = (double)((tiles * n + slots - 1) / slots), per_cu = (double)((tiles * n + 255) / 256);
+    const double c = std::max(per_cu * s.us, rounds * s.lat) * chunk + 6.0 * rounds + 0.02 * n +
+                     n * (double)M * nb * 32.0 / 4.5e6;
     if (c < cost) {
       cost = c;
       best = n;
@@ -593,11 +596,15 @@ hipError_t launch_pairs_nl(const unsigned int* Ah, const unsigned int* Al, long 
     hipLaunchKernelGGL((k_pairs_nl<WM, WN, HB, CB, NS, WPE>), dim3(ceil_div(nh, 16 * HB * WM) * tn),                \
                        dim3(64 * WM * WN), 0, s, Ah, Al, lda, Bh, Bl, ldb, npw, nh, nb, ktiles, tn, out, ldo, e);   \
   } while (0)
-  // 128 half rows x 128 bands when that leaves several tiles per compute unit; 64 x 64 (two workgroups per
-  // compute unit) below; 128 x 16 for few bands, where the table's read is the cost (one band, 2,048
+  // 128 half rows x 128 bands when that leaves several tiles per compute unit and pads the bands by at most a
+  // tenth more than 64 would (1,088 bands: 8.64 ms, 9.45 in 64 x 64; 440 bands, 40,363 half rows: 616 us and 563);
+  // 64 x 64 (two workgroups per compute unit) below, 64 x 48 where it pads less (144 bands, 18,537 half rows:
+  // 43.6 us, 48.7 in 64 x 64; at equal padding they are equal); 128 x 16 for few bands, where the table's read is the cost (one band, 2,048
   // projectors: 0.56 ms; 2.1 ms as complex products in 128 x 128 tiles)
   if (nb <= 16 && ktiles >= 8) PW_NL(4, 1, 2, 2, 3, 1);
-  else if (nb >= 96 && (long)ceil_div(nh, 128) * ceil_div(nb, 128) >= 512) PW_NL(2, 4, 4, 4, 2, 2);
+  else if (nb >= 96 && (long)ceil_div(nh, 128) * ceil_div(nb, 128) >= 512 && 20 * ceil_div(nb, 128) <= 11 * ceil_div(nb, 64))
+    PW_NL(2, 4, 4, 4, 2, 2);
+  else if (48 * ceil_div(nb, 48) < 64 * ceil_div(nb, 64)) PW_NL(4, 1, 1, 6, 2, 2);
   else PW_NL(2, 2, 2, 4, 2, 2);
 #undef PW_NL
   return hipGetLastError();

@@ -66,6 +66,8 @@ int main(int argc, char** argv) {
   }
   for (int j0 = 0; j0 < nb; j0 += 64)
     for (int k0 : {0, m32 / 2 - 16}) kgroups(8, true, j0, nb, m32 / 2, k0);
+  for (int j0 = 0; j0 < nb; j0 += 48)
+    for (int k0 : {0, m32 / 2 - 16}) kgroups(6, true, j0, nb, m32 / 2, k0);
   for (int j0 = 0; j0 < nb; j0 += 128)
     for (int k0 : {0, m32 / 2 - 16}) kgroups(16, true, j0, nb, m32 / 2, k0);
   std::printf("npw=%d nproj=%d nb=%d: %ld checked, %ld wrong\n", npw, M, nb, checked, bad);

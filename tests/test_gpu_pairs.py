@@ -58,13 +58,15 @@ def test_precisions_tables_and_families(prec, flags, form, natoms):
 
 @pytest.mark.parametrize("ecut", [6.0, 8.0])
 def test_projection_tile_shapes(ecut):
-    # 256 projectors: the narrow shape (<= 16 bands), 64 x 32 (17 .. 47) and 128 x 64 (from 48)
+    # 256 projectors: the narrow shape (<= 16 bands) and 64 x 32; nonlocal tiles of 64 x 48 and 64 x 64
     check(synth.silicon_cell((2, 2, 2), ecut, nbands=129, disp_seed=5), (1, 15, 16, 17, 47, 48, 63, 65, 129), cols=3)
 
 
 def test_largest_tiles_with_remainders():
-    # 864 projectors x 153 bands: 256 x 128 projection tiles; 131 bands x 257 row tiles: 128 x 128 nonlocal tiles
-    check(synth.silicon_cell((3, 3, 3), 6.0, nbands=153, disp_seed=5), (152, 153), cols=3)
+    # 864 projectors x 153 bands: 256 x 128 projection tiles, x 77 .. 95: 128 x 64; 249 bands x 257 row tiles: 128 x 128
+    # nonlocal tiles
+    check(synth.silicon_cell((3, 3, 3), 6.0, nbands=153, disp_seed=5), (77, 95, 152, 153), cols=3)
+    check(synth.silicon_cell((3, 3, 4), 11.5, nbands=251, disp_seed=6), (249, 251), cols=3)
     check(synth.silicon_cell((3, 3, 4), 11.5, nbands=131, disp_seed=6), (129, 131), cols=3)
 
 
