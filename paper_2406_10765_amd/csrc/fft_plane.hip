@@ -1017,17 +1017,29 @@ __global__ void k_rs_reduce(const float2* __restrict__ part, RsDesc rd, int nbt,
   PW_GRID_STRIDE(idx, (long)nbt * rd.natoms) {
     const int j = (int)(idx / rd.natoms), a = (int)(idx - (long)j * rd.natoms);
     double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int k = rd.aoff[a]; k < rd.aoff[a + 1]; ++k) {
-      const float4* q = reinterpret_cast<const float4*>(part + ((long)j * rd.nent + rd.aent[k]) * 4);
-      const float4 u = q[0], v = q[1];
-      s[0] += u.x;
-      s[1] += u.y;
-      s[2] += u.z;
-      s[3] += u.w;
-      s[4] += v.x;
-      s[5] += v.y;
-      s[6] += v.z;
-      s[7] += v.w;
+    // four entries in flight: the sums wait for nothing but their loads
+    const int k1 = rd.aoff[a + 1];
+    for (int k = rd.aoff[a]; k < k1; k += 4) {
+      float4 u[4], v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4* q = reinterpret_cast<const float4*>(part + ((long)j * rd.nent + rd.aent[min(k + i, k1 - 1)]) * 4);
+        u[i] = q[0];
+        v[i] = q[1];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (k + i < k1) {
+          s[0] += u[i].x;
+          s[1] += u[i].y;
+          s[2] += u[i].z;
+          s[3] += u[i].w;
+          s[4] += v[i].x;
+          s[5] += v[i].y;
+          s[6] += v[i].z;
+          s[7] += v[i].w;
+        }
+      }
     }
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
