@@ -411,7 +411,12 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   for (int gi = 0; gi < P.npw; ++gi)
     for (int i = 0; i < 3; ++i) P.hmax[i] = std::max(P.hmax[i], std::abs(P.miller[3 * gi + i]));
   P.bwidth = (2 * P.hmax[0] + 1) + (2 * P.hmax[1] + 1) + (2 * P.hmax[2] + 1);
-  L.beta = take(otf || P.rspace ? 0 : cb * P.ldh * (bkb ? P.nproj32 : P.nproj));
+  // The table over half the sphere takes the room a table over all of it would, less the pencil intermediate of
+  // planes that could also run inside LDS: plans keep the sizes that arenas were made for, and the forms without
+  // a table are smaller by a whole one.
+  const size_t half = cb * P.ldh * (bkb ? P.nproj32 : P.nproj), whole = cb * P.ldw * P.nproj;
+  const size_t shared = P.fl.pencil_n && P.fl.fused ? per_band_g1 * P.fft_batch : 0;
+  L.beta = take(otf || P.rspace ? 0 : std::max(half, whole - std::min(whole, shared)));
   L.brad = take(otf ? sizeof(double) * 4 * P.npw : 0);
   L.bph = take(otf ? 16 * (size_t)P.natoms * P.bwidth : 0);
   const bool blocked = P.nbb < P.nbands;
