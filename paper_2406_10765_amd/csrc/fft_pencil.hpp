@@ -8,9 +8,9 @@
 // their real and imaginary parts one after the other, so that a wave needs 8 bytes per element in both
 // precisions and eight waves of FP64 lines fit a compute unit.
 // Bound by the traffic of G1 (written and read twice), which a batch keeps in the last-level cache.
-// H X of 1,088 bands on 128^3 in FP64: the three passes take 34, 54 and 78 us per 5 bands (beside the
+// H X of 1,088 bands on 128^3 in FP64: the three passes take 38, 51 and 85 us per 6 bands (beside the
 // projection's stream), the generic passes they replace took 327, 251 and 89 us per 6; 101 bands on
-// 32 x 64 x 96 in FP32: 155 us, the generic fused plane 297 us.
+// 32 x 64 x 96 in FP32: 98 us (155 with rows of whole 128 bytes), the generic fused plane 297 us.
 #pragma once
 
 #include "fft_small.hpp"
