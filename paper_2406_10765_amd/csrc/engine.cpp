@@ -604,6 +604,22 @@ struct Engine {
     // bands per pass: the stick batch, and as many |psi|^2 grids as u0 holds
     const int per = (int)std::min<long>(P.fft_batch, u0_elems / nr);
     if (per < 1) return fail(h, PW_EINVAL, "density: the work buffer cannot hold one real-space grid");
+    if (P.fl.sized && g.n1 != 128) {
+      // planes inside LDS: one FP64 grid per band group in the work blocks (one fits: the limit above)
+      double* part = reinterpret_cast<double*>(h->at<unsigned char>(P.lay.u0));
+      const size_t room = P.lay.zb - P.lay.u0 + sizeof(cplx<T>) * P.ldw * P.nbb;
+      const int fit = (int)std::min<size_t>(1024, room / (sizeof(double) * nr));
+      for (int b0 = 0; b0 < nb; b0 += P.fft_batch) {
+        const int nbt = std::min(P.fft_batch, nb - b0);
+        const int most = std::max(1, std::min({density_plane_groups(g, P.real_bytes), fit, nbt}));
+        const int ng = ceil_div(nbt, ceil_div(nbt, most));  // no empty group
+        PW_TIMED(PW_PH_STICKS_INV, launch_sticks_inv<T>(X + (long)b0 * ld, ld, SB, nbt, st, g, tw3, P.fl, h->stream));
+        PW_TIMED(PW_PH_PLANE,
+                 launch_density_plane_n<T>(SB, nbt, cs, g, tw1, occ + b0, ng, part, h->stream));
+        PW_TIMED(PW_PH_OTHER, launch_density_groups(part, ng, nr, rho, b0 == 0, h->stream));
+      }
+      return PW_OK;
+    }
     if (pencil_n_supported(g.n1) && pencil_n_supported(g.n2)) {
       // pencil form in the three work blocks (u0, u1, zb): one FP64 grid per band group, enough groups for
       // two waves of 8 rows per SIMD, then the pencil intermediate of as many bands as fit

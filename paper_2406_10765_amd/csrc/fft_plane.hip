@@ -88,11 +88,15 @@ struct PlaneShape : PlanePitch<T, A * B> {
 };
 
 // Grid (n3, band groups), 64 NW threads; bands blockIdx.y, blockIdx.y + gridDim.y, ...
-template <typename T, int A, int B>
+// DENS: the charge density.  A workgroup takes bands [group per, (group + 1) per), stops behind the inverse x pass
+// and adds occ_b |psi_b|^2 to FP64 registers of its rows' points, bands in order: part[group][z][y][x].  Bound by
+// the sticks' one read: 144 bands on 64^3 in FP64 101 us, 207 as pencil passes through HBM.
+template <typename T, int A, int B, bool DENS>
 __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
-    __attribute__((amdgpu_waves_per_eu(PlaneShape<T, A, B>::WPE))) void k_plane_w(
+    __attribute__((amdgpu_waves_per_eu(DENS ? 1 : PlaneShape<T, A, B>::WPE))) void k_plane_w(
         cplx<T>* __restrict__ SB, const T* __restrict__ V, const int* __restrict__ colstart, GridDesc g,
-        const cplx<T>* __restrict__ twg, T scale, int nbatch) {
+        const cplx<T>* __restrict__ twg, T scale, int nbatch, const double* __restrict__ occ, int per,
+        double* __restrict__ part) {
   using S = PlaneShape<T, A, B>;
   constexpr int N = S::N, TT = S::TT, I1 = S::I1, J2 = S::J2, LPW = S::LPW, NW = S::NW;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -105,7 +109,8 @@ __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
   for (int i = tid; i < N; i += 64 * NW) tw[i] = twg[i];
   const bool row_on = on && wv * LPW + l < N;  // this thread's row
   const int y = min(wv * LPW + l, N - 1);
-  const T* vz = V + ((long)z * N + y) * N;
+  const T* vz = DENS ? nullptr : V + ((long)z * N + y) * N;
+  double sum[DENS ? J2 : 1][DENS ? B : 1] = {};
   __syncthreads();
   const cplx<T> zero = mk<T>(0, 0);
   // W_N^{n2 k1} of stage 1 (n2 = t + TT i), conjugated for the inverse
@@ -195,11 +200,22 @@ __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
 #pragma unroll
         for (int n2 = 0; n2 < B; ++n2) r2[j][n2] = row[S::inv_word(y, k1, n2)];
         SmallDft<T, B, +1>::run(r2[j]);
+        if constexpr (DENS) {
+          const double o = occ[b];
+#pragma unroll
+          for (int k2 = 0; k2 < B; ++k2)
+            sum[j][k2] += o * ((double)r2[j][k2].x * r2[j][k2].x + (double)r2[j][k2].y * r2[j][k2].y);
+          continue;
+        }
 #pragma unroll
         for (int k2 = 0; k2 < B; ++k2) r2[j][k2] = cscale<T>(r2[j][k2], vz[k1 + A * k2]);
         SmallDft<T, B, -1>::run(r2[j]);  // over m2 = k2, output q2
 #pragma unroll
         for (int q2 = 1; q2 < B; ++q2) r2[j][q2] = cmul<T>(r2[j][q2], tw[(k1 * q2) % N]);
+      }
+      if constexpr (DENS) {
+        __syncthreads();  // the next band's columns go over these rows
+        return;
       }
       wave_sync();
 #pragma unroll
@@ -255,7 +271,16 @@ __global__ __launch_bounds__((64 * PlaneShape<T, A, B>::NW))
       }
     }
   };
-  if constexpr (S::LOOP) {
+  if constexpr (DENS) {
+    const int b1 = min(nbatch, ((int)blockIdx.y + 1) * per);
+    for (int b = blockIdx.y * per; b < b1; ++b) one_band(b);
+    double* pz = part + (((long)blockIdx.y * g.n3 + z) * N + y) * N;
+#pragma unroll
+    for (int j = 0; j < J2; ++j)
+      if (row_on && S::has2(t, j))
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) pz[t + TT * j + A * k2] = sum[j][k2];
+  } else if constexpr (S::LOOP) {
     for (int b = blockIdx.y; b < nbatch; b += gridDim.y) one_band(b);
   } else {
     one_band(blockIdx.y);
@@ -1333,8 +1358,18 @@ static hipError_t launch_plane_w(cplx<T>* SB, const T* V, int nbatch, const int*
   // LOOP: two rounds of the workgroups a device holds (16 waves per CU at these register counts)
   const int per_cu = std::max(1, std::min((int)(160 * 1024 / S::LDS), 16 / S::NW));
   const int groups = S::LOOP ? std::max(1, std::min(nbatch, 2 * 256 * per_cu / g.n3)) : nbatch;
-  hipLaunchKernelGGL((k_plane_w<T, A, B>), dim3(g.n3, groups), dim3(64 * S::NW), S::LDS, s, SB, V, colstart, g, tw,
-                     scale, nbatch);
+  hipLaunchKernelGGL((k_plane_w<T, A, B, false>), dim3(g.n3, groups), dim3(64 * S::NW), S::LDS, s, SB, V, colstart, g,
+                     tw, scale, nbatch, (const double*)nullptr, 0, (double*)nullptr);
+  return hipGetLastError();
+}
+
+template <typename T, int A, int B>
+static hipError_t launch_density_w(const cplx<T>* SB, int nbatch, const int* colstart, const GridDesc& g,
+                                   const cplx<T>* tw, const double* occ, int ngroups, double* part, hipStream_t s) {
+  using S = PlaneShape<T, A, B>;
+  hipLaunchKernelGGL((k_plane_w<T, A, B, true>), dim3(g.n3, ngroups), dim3(64 * S::NW), S::LDS, s,
+                     const_cast<cplx<T>*>(SB), (const T*)nullptr, colstart, g, tw, (T)1, nbatch, occ,
+                     ceil_div(nbatch, ngroups), part);
   return hipGetLastError();
 }
 
@@ -1385,17 +1420,49 @@ hipError_t launch_plane_n(cplx<T>* SB, const T* V, int nbatch, const int* colsta
   }
 }
 
+// Band groups of the density on planes inside LDS: two rounds of the workgroups that a device holds.
+int density_plane_groups(const GridDesc& g, int real_bytes) {
+  const size_t lds = (size_t)(g.n1 * g.n2 + g.n1) * 2 * real_bytes;  // a little under the kernel's own
+  const int per_cu = std::max(1, std::min((int)(160 * 1024 / lds), 4));
+  return std::max(1, 2 * 256 * per_cu / g.n3);
+}
+
+template <typename T>
+hipError_t launch_density_plane_n(const cplx<T>* SB, int nbatch, const int* colstart, const GridDesc& g,
+                                  const cplx<T>* tw, const double* occ, int ngroups, double* part, hipStream_t s) {
+  if (!alias_free(g) || nbatch < 1 || ngroups < 1) return hipErrorInvalidValue;
+  if constexpr (std::is_same<T, float>::value) {
+    if (g.n1 == 108) return launch_density_w<T, 6, 18>(SB, nbatch, colstart, g, tw, occ, ngroups, part, s);
+  }
+  switch (g.n1) {
+#define PW_CASE(NN, AA, BB) \
+  case NN:                  \
+    return launch_density_w<T, AA, BB>(SB, nbatch, colstart, g, tw, occ, ngroups, part, s);
+    PW_PLANE_SIZES(PW_CASE)
+#undef PW_CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+template hipError_t launch_density_plane_n<float>(const cplx<float>*, int, const int*, const GridDesc&,
+                                                  const cplx<float>*, const double*, int, double*, hipStream_t);
+template hipError_t launch_density_plane_n<double>(const cplx<double>*, int, const int*, const GridDesc&,
+                                                   const cplx<double>*, const double*, int, double*, hipStream_t);
+
 void pw_allow_large_lds_plane_n() {
   const int bytes = (int)(160 * 1024);
   auto allow = [&](const void* k) {
     (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   };
 #define PW_ALLOW(NN, AA, BB)                                     \
-  allow(reinterpret_cast<const void*>(&k_plane_w<float, AA, BB>)); \
-  allow(reinterpret_cast<const void*>(&k_plane_w<double, AA, BB>));
+  allow(reinterpret_cast<const void*>(&k_plane_w<float, AA, BB, false>)); \
+  allow(reinterpret_cast<const void*>(&k_plane_w<float, AA, BB, true>)); \
+  allow(reinterpret_cast<const void*>(&k_plane_w<double, AA, BB, true>)); \
+  allow(reinterpret_cast<const void*>(&k_plane_w<double, AA, BB, false>));
   PW_PLANE_SIZES(PW_ALLOW)
 #undef PW_ALLOW
-  allow(reinterpret_cast<const void*>(&k_plane_w<float, 6, 18>));
+  allow(reinterpret_cast<const void*>(&k_plane_w<float, 6, 18, false>));
+  allow(reinterpret_cast<const void*>(&k_plane_w<float, 6, 18, true>));
   allow(reinterpret_cast<const void*>(&k_plane128<false>));
   allow(reinterpret_cast<const void*>(&k_plane128<true>));
   allow(reinterpret_cast<const void*>(&k_rs_proj128));

@@ -106,6 +106,12 @@ hipError_t launch_pencil_yfwd_n(cplx<T>* SB, const cplx<T>* G1, int nbatch, cons
 template <typename T>
 hipError_t launch_pencil_density_n(const cplx<T>* G1, int nbatch, const GridDesc& g, int pitch, const cplx<T>* tw1,
                                    const double* occ, int ngroups, double* part, hipStream_t s);
+int density_plane_groups(const GridDesc& g, int real_bytes);
+// part[group][z][y][x] = sum of occ_b |psi_b|^2 over the group's bands, square planes inside LDS (sizes of
+// launch_plane_n, not 128).
+template <typename T>
+hipError_t launch_density_plane_n(const cplx<T>* SB, int nbatch, const int* colstart, const GridDesc& g,
+                                  const cplx<T>* tw, const double* occ, int ngroups, double* part, hipStream_t s);
 hipError_t launch_density_groups(const double* part, int ngroups, long nr, double* rho, bool first, hipStream_t s);
 
 // --------------------------------------------------------------- GEMM ------

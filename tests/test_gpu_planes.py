@@ -141,3 +141,21 @@ def test_smallest_alias_free_grids(n, prec):
         print("alias-free grid", grid, "prec", prec, "npw", m.npw, "err", err, flush=True)
         assert err < (1e-12 if prec == pw.PW_FP64 else 2e-5)
         h.close()
+
+
+@pytest.mark.parametrize("n", [24, 27, 32, 48, 54, 64, 81, 96, 108])
+@pytest.mark.parametrize("prec", [pw.PW_FP64, pw.PW_MIXED])
+def test_density_on_square_planes(n, prec):
+    """The charge density inside LDS for every compiled square plane (FP64 108: pencil passes), one band, one per
+    group and several per group; tolerances as above."""
+    m, h, p = model_and_handle(synth.make_cell("si8", modes=True), prec, 70, (n, n, 24))
+    X = synth.random_block(m.npw, 70, 3 + n)
+    if prec == pw.PW_MIXED:
+        X = X.astype(np.complex64).astype(np.complex128)
+    for nb in (1, 3, 70):
+        occ = np.linspace(2.0, 0.1, nb)
+        rho = O.density(X[:, :nb], occ, m.miller, m.grid).transpose(2, 1, 0)
+        err = float(np.abs(h.density(h.to_device(X[p][:, :nb]), occ).cpu().numpy() - rho).max() / rho.max())
+        print("density plane", n, "prec", prec, "nb", nb, "err", err, flush=True)
+        assert err < (1e-12 if prec == pw.PW_FP64 else 1e-5)
+    h.close()
