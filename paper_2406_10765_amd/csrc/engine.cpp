@@ -604,45 +604,28 @@ struct Engine {
     // bands per pass: the stick batch, and as many |psi|^2 grids as u0 holds
     const int per = (int)std::min<long>(P.fft_batch, u0_elems / nr);
     if (per < 1) return fail(h, PW_EINVAL, "density: the work buffer cannot hold one real-space grid");
-    if (P.fl.sized && g.n1 != 128) {
-      // planes inside LDS: one FP64 grid per band group in the work blocks (one fits: the limit above)
+    if (P.fl.sized ? g.n1 != 128 : P.fl.pencil_n) {
+      // one FP64 grid per band group in the work blocks (u0, u1, zb; one fits: the limit above), planes inside
+      // LDS or as pencils (groups for two waves of 8 rows per SIMD)
       double* part = reinterpret_cast<double*>(h->at<unsigned char>(P.lay.u0));
       const size_t room = P.lay.zb - P.lay.u0 + sizeof(cplx<T>) * P.ldw * P.nbb;
       const int fit = (int)std::min<size_t>(1024, room / (sizeof(double) * nr));
+      const int want = P.fl.sized ? density_plane_groups(g, P.real_bytes)
+                                  : (int)std::min<long>(16, std::max<long>(1, 32768 / ((long)g.n3 * g.n2)));
       for (int b0 = 0; b0 < nb; b0 += P.fft_batch) {
-        const int nbt = std::min(P.fft_batch, nb - b0);
-        const int most = std::max(1, std::min({density_plane_groups(g, P.real_bytes), fit, nbt}));
+        const int nbt = std::min(P.fft_batch, nb - b0), most = std::max(1, std::min({want, fit, nbt}));
         const int ng = ceil_div(nbt, ceil_div(nbt, most));  // no empty group
         PW_TIMED(PW_PH_STICKS_INV, launch_sticks_inv<T>(X + (long)b0 * ld, ld, SB, nbt, st, g, tw3, P.fl, h->stream));
-        PW_TIMED(PW_PH_PLANE,
-                 launch_density_plane_n<T>(SB, nbt, cs, g, tw1, occ + b0, ng, part, h->stream));
+        if (P.fl.sized) {
+          PW_TIMED(PW_PH_PLANE, launch_density_plane_n<T>(SB, nbt, cs, g, tw1, occ + b0, ng, part, h->stream));
+        } else {
+          PW_TIMED(PW_PH_PENCIL_YINV, launch_pencil_yinv_n<T>(SB, G1, nbt, cs, g, P.fl.pitch, tw2, h->stream));
+          PW_TIMED(PW_PH_PENCIL_X,
+                   launch_pencil_density_n<T>(G1, nbt, g, P.fl.pitch, tw1, occ + b0, ng, part, h->stream));
+        }
         PW_TIMED(PW_PH_OTHER, launch_density_groups(part, ng, nr, rho, b0 == 0, h->stream));
       }
       return PW_OK;
-    }
-    if (pencil_n_supported(g.n1) && pencil_n_supported(g.n2)) {
-      // pencil form in the three work blocks (u0, u1, zb): one FP64 grid per band group, enough groups for
-      // two waves of 8 rows per SIMD, then the pencil intermediate of as many bands as fit
-      unsigned char* w0 = h->at<unsigned char>(P.lay.u0);
-      const size_t room = P.lay.zb - P.lay.u0 + sizeof(cplx<T>) * P.ldw * P.nbb;
-      const size_t grid_bytes = sizeof(double) * nr, g1_bytes = (size_t)g.n3 * g.n2 * P.fl.pitch * sizeof(cplx<T>);
-      int ngroups = (int)std::min<long>(16, std::max<long>(1, 32768 / ((long)g.n3 * g.n2)));
-      while (ngroups > 1 && 2 * ngroups * grid_bytes > room) --ngroups;
-      const size_t parts_bytes = (ngroups * grid_bytes + kArenaAlign - 1) / kArenaAlign * kArenaAlign;
-      const int bands = room > parts_bytes ? (int)std::min<size_t>(P.fft_batch, (room - parts_bytes) / g1_bytes) : 0;
-      if (bands >= 1) {
-        double* part = reinterpret_cast<double*>(w0);
-        cplx<T>* GP = reinterpret_cast<cplx<T>*>(w0 + parts_bytes);
-        for (int b0 = 0; b0 < nb; b0 += bands) {
-          const int nbt = std::min(bands, nb - b0), ng = std::min(ngroups, nbt);
-          PW_TIMED(PW_PH_STICKS_INV, launch_sticks_inv<T>(X + (long)b0 * ld, ld, SB, nbt, st, g, tw3, P.fl, h->stream));
-          PW_TIMED(PW_PH_PENCIL_YINV, launch_pencil_yinv_n<T>(SB, GP, nbt, cs, g, P.fl.pitch, tw2, h->stream));
-          PW_TIMED(PW_PH_PENCIL_X,
-                   launch_pencil_density_n<T>(GP, nbt, g, P.fl.pitch, tw1, occ + b0, ng, part, h->stream));
-          PW_TIMED(PW_PH_OTHER, launch_density_groups(part, ng, nr, rho, b0 == 0, h->stream));
-        }
-        return PW_OK;
-      }
     }
     for (int b0 = 0; b0 < nb; b0 += per) {
       const int nbt = std::min(per, nb - b0);
