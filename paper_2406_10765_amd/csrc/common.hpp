@@ -100,6 +100,7 @@ struct GridDesc {
   int n1max;          // max |n1| over sticks; active x columns xa = n1 + n1max in [0, n1a)
   int n1a;            // 2 * n1max + 1
   int n2max;          // max |n2| over sticks
+  int n3max;          // max |n3|
   FftPlan p1, p2, p3; // radix plans for the three axes
 };
 

@@ -332,6 +332,7 @@ PencilTask pencil_tasks(int lines, long planes) {
 template <typename T>
 hipError_t launch_pencil_yinv_n(const cplx<T>* SB, cplx<T>* G1, int nbatch, const int* colstart, const GridDesc& g,
                                 int pitch, const cplx<T>* tw2, hipStream_t s) {
+  if (g.n2max > plane_top(g.n2)) return hipErrorInvalidValue;
   switch (g.n2) {
 #define PW_CASE(NN, AA, BB)                                                                                         \
   case NN: {                                                                                                        \
@@ -349,6 +350,7 @@ hipError_t launch_pencil_yinv_n(const cplx<T>* SB, cplx<T>* G1, int nbatch, cons
 template <typename T>
 hipError_t launch_pencil_yfwd_n(cplx<T>* SB, const cplx<T>* G1, int nbatch, const int* colstart, const GridDesc& g,
                                 int pitch, const cplx<T>* tw2, T scale, hipStream_t s) {
+  if (g.n2max > plane_top(g.n2)) return hipErrorInvalidValue;
   switch (g.n2) {
 #define PW_CASE(NN, AA, BB)                                                                                         \
   case NN: {                                                                                                        \
@@ -366,6 +368,7 @@ hipError_t launch_pencil_yfwd_n(cplx<T>* SB, const cplx<T>* G1, int nbatch, cons
 template <typename T>
 hipError_t launch_pencil_x_n(cplx<T>* G1, const T* V, int nbatch, const GridDesc& g, int pitch, const cplx<T>* tw1,
                              hipStream_t s) {
+  if (g.n1max > plane_top(g.n1)) return hipErrorInvalidValue;
   switch (g.n1) {
 #define PW_CASE(NN, AA, BB)                                                                                       \
   case NN: {                                                                                                      \
@@ -388,6 +391,7 @@ template <typename T>
 hipError_t launch_pencil_density_n(const cplx<T>* G1, int nbatch, const GridDesc& g, int pitch, const cplx<T>* tw1,
                                    const double* occ, int ngroups, double* part, hipStream_t s) {
   const int per = ceil_div(nbatch, ngroups);
+  if (g.n1max > plane_top(g.n1)) return hipErrorInvalidValue;
   switch (g.n1) {
 #define PW_CASE(NN, AA, BB)                                                                                        \
   case NN: {                                                                                                       \

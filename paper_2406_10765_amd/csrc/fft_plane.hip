@@ -832,8 +832,8 @@ __global__ void k_density_groups(const double* __restrict__ part, int ngroups, l
   }
 }
 
-// the grids that the plane kernels assume (grid_empty)
-static bool alias_free(const GridDesc& g) { return g.n1 > 3 * g.n1max && g.n2 > 3 * g.n2max; }
+// the spheres that the plane kernels carry (grid_empty)
+static bool alias_free(const GridDesc& g) { return g.n1max <= plane_top(g.n1) && g.n2max <= plane_top(g.n2); }
 
 hipError_t launch_density_groups(const double* part, int ngroups, long nr, double* rho, bool first, hipStream_t s) {
   hipLaunchKernelGGL(k_density_groups, dim3(stride_blocks(nr)), dim3(256), 0, s, part, ngroups, nr, rho, first ? 1 : 0);
@@ -1157,7 +1157,7 @@ __global__ __launch_bounds__(256) void k_sticks_inv_n(const cplx<T>* __restrict_
   for (int i = 0; i < I1; ++i)
 #pragma unroll
     for (int n1 = 0; n1 < A; ++n1) {
-      const int e = act && !grid_empty(N, B, n1) ? stick_index(B * n1 + t + TT * i, h, N) : -1;
+      const int e = act && !stick_empty(N, B, n1) ? stick_index(B * n1 + t + TT * i, h, N) : -1;
       r1[i][n1] = e >= 0 ? xs[e] : mk<T>(0, 0);
     }
   __syncthreads();  // twiddles
@@ -1253,7 +1253,7 @@ __global__ __launch_bounds__(256) void k_sticks_fwd_n(const cplx<T>* __restrict_
 #pragma unroll
     for (int k2 = 0; k2 < B; ++k2) {
       const int e = stick_index(k1 + A * k2, h, N);
-      if (!grid_empty(N, A, k2) && e >= 0) {
+      if (!stick_empty(N, A, k2) && e >= 0) {
         if constexpr (UPD) {
           const long i = (long)sk.off + e;
           const float2 y = u.Y[(long)b * u.ldy + i];
@@ -1293,6 +1293,7 @@ bool sticks_n_supported(int n3) {
 template <typename T>
 hipError_t launch_sticks_inv_n(const cplx<T>* X, long ldx, cplx<T>* SB, int nbatch, const Stick* st,
                                const GridDesc& g, const cplx<T>* tw3, hipStream_t s) {
+  if (g.n3max > stick_top(g.n3)) return hipErrorInvalidValue;
   switch (g.n3) {
 #define PW_CASE(NN, AA, BB)                                                                                   \
   case NN:                                                                                                    \
@@ -1309,6 +1310,7 @@ hipError_t launch_sticks_inv_n(const cplx<T>* X, long ldx, cplx<T>* SB, int nbat
 template <typename T>
 hipError_t launch_sticks_fwd_n(const cplx<T>* SB, cplx<T>* Z, long ldz, int nbatch, const Stick* st,
                                const GridDesc& g, const cplx<T>* tw3, hipStream_t s) {
+  if (g.n3max > stick_top(g.n3)) return hipErrorInvalidValue;
   switch (g.n3) {
 #define PW_CASE(NN, AA, BB)                                                                                   \
   case NN:                                                                                                    \
@@ -1324,6 +1326,7 @@ hipError_t launch_sticks_fwd_n(const cplx<T>* SB, cplx<T>* Z, long ldz, int nbat
 
 hipError_t launch_sticks_fwd_upd(const float2* SB, float2* out, long ldo, int nbatch, const Stick* st,
                                  const GridDesc& g, const float2* tw3, const StickUpd& u, hipStream_t s) {
+  if (g.n3max > stick_top(g.n3)) return hipErrorInvalidValue;
   switch (g.n3) {
 #define PW_CASE(NN, AA, BB)                                                                                     \
   case NN:                                                                                                      \

@@ -103,11 +103,22 @@ struct SmallDft {
   }
 };
 
-// A plan's grids have N >= 3 nmax + 1 points along each axis, so points nmax < e < N - nmax hold no plane wave:
-// whether the points S block .. S block + S - 1 are all empty, whatever the sphere.  The sized kernels leave out
-// the loads, terms and stores of such blocks.
-__device__ __host__ __forceinline__ constexpr bool grid_empty(int N, int S, int block) {
-  return S * block > (N - 1) / 3 && S * block + S - 1 < N - (N - 1) / 3;
+// Largest |n| that the sized kernels carry on N points.  A plan has N >= 3 nmax + 1 points along each axis with
+// nmax = floor(sqrt(2 ecut) L / 2 pi), rounded.  Across the planes no stick lies beyond nmax; along z a stick
+// reaches nmax + 1 where the cutoff falls on a shell and rounding took nmax below it.
+constexpr int plane_top(int N) { return (N - 1) / 3; }
+constexpr int stick_top(int N) { return (N - 1) / 3 + 1; }
+// Points top < e < N - top hold no plane wave: whether the points S block .. S block + S - 1 are all empty, whatever
+// the sphere.  The sized kernels leave out the loads, terms and stores of such blocks; their launchers check the
+// sphere against the top.
+__device__ __host__ __forceinline__ constexpr bool points_empty(int N, int S, int block, int top) {
+  return S * block > top && S * block + S - 1 < N - top;
+}
+__device__ __host__ __forceinline__ constexpr bool grid_empty(int N, int S, int block) {  // across the planes
+  return points_empty(N, S, block, plane_top(N));
+}
+__device__ __host__ __forceinline__ constexpr bool stick_empty(int N, int S, int block) {  // along z
+  return points_empty(N, S, block, stick_top(N));
 }
 
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }

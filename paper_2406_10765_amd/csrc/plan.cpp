@@ -284,10 +284,11 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
     }
     if (P.n[i] > 512) { *err = "grid dimension above 512 is not supported"; return PW_EINVAL; }
   }
-  int n1max = 0, n2max = 0;
+  int n1max = 0, n2max = 0, n3max = 0;
   for (const Stick& s : P.sticks) {
     n1max = std::max(n1max, std::abs(s.n1));
     n2max = std::max(n2max, std::abs(s.n2));
+    n3max = std::max(n3max, (s.len - 1) / 2);
   }
   GridDesc& g = P.g;
   g.n1 = P.n[0];
@@ -298,6 +299,7 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   g.n1max = n1max;
   g.n1a = 2 * n1max + 1;
   g.n2max = n2max;
+  g.n3max = n3max;
   g.p1 = radix_plan(g.n1);
   g.p2 = radix_plan(g.n2);
   g.p3 = radix_plan(g.n3);
