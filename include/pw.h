@@ -164,6 +164,10 @@ typedef struct pw_handle_s pw_handle;
 /* Sizes of a description, host only (no device needed).  PW_EINVAL for a bad description. */
 pw_status pw_plan(const pw_cell_desc *desc, pw_info *out);
 
+/* Arena bytes up to which pw_setup makes use of them, host only: footprint_bytes, or more where the
+ * FFT intermediates of a cell fit it in several batches only (at most about 200 MB more). */
+pw_status pw_plan_arena(const pw_cell_desc *desc, size_t *useful_bytes);
+
 /* Miller indices of the basis of a description, host only: npw * 3 ints in stick order. */
 pw_status pw_plan_gvectors(const pw_cell_desc *desc, int *miller_host);
 
@@ -173,7 +177,8 @@ pw_status pw_plan_gvectors(const pw_cell_desc *desc, int *miller_host);
  * cutoff sphere of Section II-A; the grid is the alias-free one (reading of the Section II-A
  * grid rule); the projectors act atom by atom as in Section III-A.
  * arena_dev: caller device memory of arena_bytes >= pw_plan(...).footprint_bytes
- * (PW_ENOMEM otherwise).  hip_stream: a hipStream_t (NULL = default stream).
+ * (PW_ENOMEM otherwise; bytes beyond it, up to pw_plan_arena, go into larger FFT batches: the same
+ * results to rounding).  hip_stream: a hipStream_t (NULL = default stream).
  * Synchronises the stream before returning.
  */
 pw_status pw_setup(const pw_cell_desc *desc, void *arena_dev, size_t arena_bytes, void *hip_stream,

@@ -225,7 +225,7 @@ struct Engine {
 
   bool flag(unsigned f) const { return (P.flags & f) != 0; }
   // With split-precision projector products the table is stored as bf16 hi and lo planes of one
-  // (re, im) word per entry on half of the sphere, nproj32 columns of ldh words.
+  // (re, im) word per entry on half of the sphere, bcols columns of ldh words.
   bool beta_planes() const { return std::is_same<T, float>::value && flag(PW_FLAG_BF16_KB); }
   bool beta_otf() const { return flag(PW_FLAG_BETA_OTF); }
   BetaGen beta_gen() const {
@@ -265,7 +265,7 @@ struct Engine {
     return d;
   }
   unsigned int* beta_hi() const { return h->at<unsigned int>(P.lay.beta); }
-  unsigned int* beta_lo() const { return beta_hi() + (size_t)P.ldh * P.nproj32; }
+  unsigned int* beta_lo() const { return beta_hi() + (size_t)P.ldh * P.bcols; }
   // Work buffers of an H application: the arena's, or the static work array's during
   // pw_apply_h_noalloc.
   template <typename X>
@@ -274,7 +274,7 @@ struct Engine {
   }
   cplx<T>* sb_buf() const { return work<cplx<T>>(P.lay.sb, h->ws_sb); }
   cplx<T>* g1_buf() const { return work<cplx<T>>(P.lay.g1, h->ws_g1); }
-  double2* parts_buf() const { return work<double2>(P.lay.parts, h->ws_parts); }
+  double2* parts_buf() const { return work<double2>(P.lay.pparts, h->ws_parts); }
   int fft_batch() const { return h->ws ? h->ws_fft_batch : P.fft_batch; }
   // row pitch of the sized pencil form, 0 where it is not used
   int pencil_pitch() const { return !P.fl.pencil_n ? 0 : h->ws ? h->ws_pitch : P.fl.pitch; }
@@ -471,7 +471,7 @@ struct Engine {
     // phase timing on, everything stays on the caller's stream so that phase times are not
     // inflated by sharing the device.
     // Small blocks (serving-size cells) gain nothing from it and would only add streams.
-    const bool overlap = !P.rspace && !h->timing && (double)P.npw * nb >= (double)(1 << 26);
+    const bool overlap = !h->timing && P.overlaps(nb);
     if (P.rspace) {
       // the forward sticks write the updated block: nothing else to do
       drop_planes();
@@ -550,7 +550,7 @@ struct Engine {
           e.ldcl = P.ldw;
         }
         PW_TIMED(PW_PH_NL, launch_pairs_nl(beta_hi(), beta_lo(), P.ldh, pt_hi(), pt_lo(), ldpt(), P.npw, nb,
-                                           P.nproj32 / 32, out, ldo, e, h->stream));
+                                           P.bcols, out, ldo, e, h->stream));
         if (e.ph) set_pairs(out, nb);
         if (w_gram) h->wp_src = out;
         else if (e.ch) set_planes(out, nb);
@@ -1343,7 +1343,7 @@ struct Engine {
       PW_HIP(launch_beta_gen_tables(beta_gen(), h->at<double>(p.lay.frac), p.L, p.beta_sigma,
                                     h->at<double>(p.lay.brad), h->at<double2>(p.lay.bph), st));
     else if (p.nproj && beta_planes())
-      PW_HIP(launch_beta_planes(h->at<int>(p.lay.miller), p.nh, h->at<double>(p.lay.frac), p.natoms, p.nproj32, p.L,
+      PW_HIP(launch_beta_planes(h->at<int>(p.lay.miller), p.nh, h->at<double>(p.lay.frac), p.natoms, p.bcols, p.L,
                                 p.beta_sigma, p.proj_form, beta_hi(), beta_lo(), p.ldh, st));
     else if (p.nproj && !p.rspace)
       PW_HIP(launch_beta_table<T>(h->at<int>(p.lay.miller), p.nh, h->at<double>(p.lay.frac), p.natoms, p.L,
@@ -1430,6 +1430,20 @@ pw_status pw_plan(const pw_cell_desc* desc, pw_info* out) {
     pw_status s = make_plan(desc, device_max_lds(), &p, &err);
     if (s != PW_OK) return fail(nullptr, s, err);
     fill_info(p, out);
+    return PW_OK;
+  } catch (const std::bad_alloc&) {
+    return fail(nullptr, PW_ENOMEM, "host allocation failed");
+  }
+}
+
+pw_status pw_plan_arena(const pw_cell_desc* desc, size_t* useful_bytes) {
+  if (!useful_bytes) return fail(nullptr, PW_EINVAL, "null output");
+  try {
+    Plan p;
+    std::string err;
+    pw_status s = make_plan(desc, device_max_lds(), &p, &err);
+    if (s != PW_OK) return fail(nullptr, s, err);
+    *useful_bytes = plan_useful_bytes(p);
     return PW_OK;
   } catch (const std::bad_alloc&) {
     return fail(nullptr, PW_ENOMEM, "host allocation failed");
@@ -1531,6 +1545,7 @@ pw_status setup_handle(const pw_cell_desc* desc, void* arena_dev, size_t arena_b
     delete h;
     return fail(nullptr, PW_ENOMEM, m);
   }
+  widen_plan(&h->plan, arena_bytes);
   h->arena = static_cast<unsigned char*>(arena_dev);
   h->arena_bytes = arena_bytes;
   h->stream = static_cast<hipStream_t>(hip_stream);

@@ -180,16 +180,17 @@ struct PmTile {
   static constexpr int Q = 2 * LP / NW;
   static_assert(2 * LP % NW == 0, "the same number of loads for every wave");
   unsigned int off[Q];
-  __device__ __forceinline__ void offsets(long ld, int r0, int wave, int lane) {
+  // cols: the operand's columns where they are fewer than 32 (then k0 = 0), otherwise 32
+  __device__ __forceinline__ void offsets(long ld, int r0, int wave, int lane, int cols) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q) off[q] = pairs_moff_bytes(TH, ld, r0, (wave + NW * q) % LP, lane);
+    for (int q = 0; q < Q; ++q) off[q] = pairs_moff_bytes(TH, ld, r0, (wave + NW * q) % LP, lane, cols);
   }
   __device__ __forceinline__ void load(const unsigned int* __restrict__ H, const unsigned int* __restrict__ Lo, long ld,
-                                       int r0, int k0, unsigned char* dst, int wave) const {
+                                       int r0, int k0, unsigned char* dst, int wave, int cols) const {
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       const int j = wave + NW * q, pl = j / LP, i = j % LP;
-      dma16(at_off((pl ? Lo : H) + (long)(k0 + i * R) * ld + r0, off[q]), dst + j * 1024);
+      dma16(at_off((pl ? Lo : H) + (long)(k0 + pairs_mbase_col(TH, i, cols)) * ld + r0, off[q]), dst + j * 1024);
     }
   }
 };
@@ -348,14 +349,15 @@ struct PairEpi {
 };
 
 // Tile 16 HB WM half rows x 8 CB WN bands.  K tile of 32 projectors; B planes hold q as words of
-// two projectors (K-contiguous, zero past nproj).  Bound by the matrix cores, then by the update's
+// two projectors (K-contiguous, zero past nproj: the table holds whole K tiles, or the projectors alone where
+// they are fewer than 32).  Bound by the matrix cores, then by the update's
 // traffic (three blocks read, one block and its planes written): at the size above 9.1 ms, 14.4 ms
 // as complex products.
 template <int WM, int WN, int HB, int CB, int NS, int WPE>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void k_pairs_nl(
     const unsigned int* __restrict__ Ah, const unsigned int* __restrict__ Al, long lda,
     const unsigned int* __restrict__ Bh, const unsigned int* __restrict__ Bl, long ldb, int npw, int nh, int nb,
-    int ktiles, int tiles_n, float2* out, long ldo, EpiH e) {
+    int ktiles, int cols, int tiles_n, float2* out, long ldo, EpiH e) {
   constexpr int NW = WM * WN, TH = 16 * HB * WM, GB = WN * CB;
   constexpr int PA = 32 * TH * 4, PB = GB * 1024;  // bytes per plane
   constexpr int SB = 2 * (PA + PB);
@@ -371,11 +373,11 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(WP
   const int wm = wave % WM, wn = wave / WM;
   TA ta;
   TB tb;
-  ta.offsets(lda, r0, wave, lane);
+  ta.offsets(lda, r0, wave, lane, cols);
   tb.offsets(ldb, j0, nb, wave, lane);
   auto issue = [&](int kt) {
     unsigned char* st = smem + (kt % NS) * SB;
-    ta.load(Ah, Al, lda, r0, kt * 32, st, wave);
+    ta.load(Ah, Al, lda, r0, kt * 32, st, wave, cols);
     tb.load(Bh, Bl, ldb, j0, nb, kt * hBK, st + 2 * PA, wave);
   };
   // this lane's part of the transposing reads: row k = 8 (l / 16) + 4 u + (l % 16) / 4, chunk l % 4 of
@@ -582,10 +584,11 @@ hipError_t launch_pairs_proj(const unsigned int* Ah, const unsigned int* Al, lon
 }
 
 hipError_t launch_pairs_nl(const unsigned int* Ah, const unsigned int* Al, long lda, const unsigned int* Bh,
-                           const unsigned int* Bl, long ldb, int npw, int nb, int ktiles, float2* out, long ldo,
+                           const unsigned int* Bl, long ldb, int npw, int nb, int acols, float2* out, long ldo,
                            const EpiH& e0, hipStream_t s) {
   if (nb <= 0) return hipSuccess;
-  const int nh = (npw + 1) / 2;
+  const int nh = (npw + 1) / 2, ktiles = ceil_div(acols, 32), cols = std::min(acols, 32);
+  if (acols > 32 && acols % 32 != 0) return hipErrorInvalidValue;  // whole K tiles
   EpiH e = e0;
   auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   e.vec4 = al(out) && ldo % 2 == 0 && al(e.Zl) && e.ldz % 2 == 0 && al(e.kin) && al(e.Y) && e.ldy % 2 == 0 &&
@@ -594,7 +597,8 @@ hipError_t launch_pairs_nl(const unsigned int* Ah, const unsigned int* Al, long 
   do {                                                                                                              \
     const int tn = ceil_div(nb, 8 * CB * WN);                                                                       \
     hipLaunchKernelGGL((k_pairs_nl<WM, WN, HB, CB, NS, WPE>), dim3(ceil_div(nh, 16 * HB * WM) * tn),                \
-                       dim3(64 * WM * WN), 0, s, Ah, Al, lda, Bh, Bl, ldb, npw, nh, nb, ktiles, tn, out, ldo, e);   \
+                       dim3(64 * WM * WN), 0, s, Ah, Al, lda, Bh, Bl, ldb, npw, nh, nb, ktiles, cols, tn, out, ldo,  \
+                       e);                                                                                          \
   } while (0)
   // 128 half rows x 128 bands when that leaves several tiles per compute unit and pads the bands by at most a
   // tenth more than 64 would (1,088 bands: 8.64 ms, 9.45 in 64 x 64; 440 bands, 40,363 half rows: 616 us and 563);

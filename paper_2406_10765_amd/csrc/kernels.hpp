@@ -244,10 +244,10 @@ hipError_t launch_pairs_proj(const unsigned int* Ah, const unsigned int* Al, lon
 // projector index modulo 4.
 hipError_t launch_pair_reduce(const double2* part, int nsplit, int M, int nb, const double* dscale, unsigned int* H,
                               unsigned int* L, long ldp, hipStream_t s);
-// out = EpiH(mode 1) with V_NL psi from the projector planes (32 ktiles columns) and the planes of q
-// (16 ktiles words per column).
+// out = EpiH(mode 1) with V_NL psi from the projector planes (acols columns: a multiple of 32, or fewer than 32)
+// and the planes of q (16 words per column and 32 projectors, zero past the last one).
 hipError_t launch_pairs_nl(const unsigned int* Ah, const unsigned int* Al, long lda, const unsigned int* Bh,
-                           const unsigned int* Bl, long ldb, int npw, int nb, int ktiles, float2* out, long ldo,
+                           const unsigned int* Bl, long ldb, int npw, int nb, int acols, float2* out, long ldo,
                            const EpiH& e, hipStream_t s);
 
 // --------------------------------------------------------------- misc ------

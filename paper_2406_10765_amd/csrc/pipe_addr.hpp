@@ -36,12 +36,19 @@ __host__ __device__ inline unsigned int pipe_moff_bytes(long ld, int r0, int lan
 // words each, ld a multiple of 4), load i of 1 KB holding k rows i R .. i R + R - 1, R = 256 / th.  Lane l
 // fills 16-byte chunk l % (th / 4) of row k = i R + l / (th / 4) with the operand's chunk (that index) ^ f(k),
 // f(k) = 4 ((k ^ k / 8) % 4), clamped to the last group of four rows: byte offset from (k = i R, r0).
-__host__ __device__ inline unsigned int pairs_moff_bytes(int th, long ld, int r0, int i, int lane) {
+// An operand of fewer than 32 columns (cols) gives its last one for those past it: the load's base column is
+// pairs_mbase_col.
+__host__ __device__ inline int pairs_mbase_col(int th, int i, int cols) {
+  const int k = i * (256 / th);
+  return k < cols - 1 ? k : cols - 1;
+}
+__host__ __device__ inline unsigned int pairs_moff_bytes(int th, long ld, int r0, int i, int lane, int cols = 32) {
   const int per = th / 4, kk = lane / per, k = i * (256 / th) + kk;
   const int c = (lane % per) ^ (4 * ((k ^ (k >> 3)) & 3));
+  const int col = (k < cols - 1 ? k : cols - 1) - pairs_mbase_col(th, i, cols);
   long row = r0 + 4L * c;
   if (row > ld - 4) row = ld - 4;
-  return (unsigned int)((kk * ld + (row - r0)) * 4);
+  return (unsigned int)((col * ld + (row - r0)) * 4);
 }
 
 }  // namespace pw

@@ -130,6 +130,76 @@ static void build_rspace_tables(Plan& P) {
   P.rs_boff[per_band.size()] = (int)P.rs_bent.size();
 }
 
+// Work area of an H application: bands per FFT launch group, K splits of the projection, row pitch of the pencil
+// intermediate (0: without the sized pencil form), sizes and the offset of the projection's partials.
+struct Work {
+  int batch, nsplit, pitch;
+  size_t sb, g1, pparts, need;
+};
+
+static size_t stick_bytes(const Plan& P) { return (size_t)P.nst * P.g.n3 * 2 * P.real_bytes; }  // of one band
+static size_t pencil_bytes(const Plan& P, int pitch) {
+  const size_t rows = (size_t)P.g.n3 * P.g.n2 * 2 * P.real_bytes;
+  return pitch ? rows * pitch : P.fl.fused ? 0 : rows * P.g.n1a;
+}
+static int batch_of(const Plan& P, size_t per_band) {
+  return (int)std::max<size_t>(1, std::min<size_t>(P.nbb, P.fft_budget / per_band));
+}
+
+// The batch, the projection's splits (nsplit, or 0: to choose) and the form of the planes within `room` bytes.
+static Work choose_work(const Plan& P, long room, int nsplit) {
+  const bool bkb = (P.flags & PW_FLAG_BF16_KB) != 0, apart = P.overlaps(P.nbb);
+  const size_t sb1 = stick_bytes(P), per_split = 16 * (size_t)P.nproj * P.nbb;
+  Work w{};
+  auto fill = [&](int pitch) {
+    const size_t g11 = pencil_bytes(P, pitch);
+    w.pitch = pitch;
+    w.nsplit = nsplit;
+    if (!nsplit) {
+      // apart: the partials may take half of what one band's buffers leave
+      const long free1 = apart ? (room - (long)(align_up(sb1) + align_up(g11)) - (long)kArenaAlign) / 2 : room;
+      const long cap = P.nproj ? std::min(64L, std::max(1L, free1 / (long)per_split)) : 1;
+      w.nsplit = !P.nproj || P.rspace ? 1
+                 : bkb ? pairs_proj_splits(P.nproj, P.nbb, (int)(P.ldh / 16), cap)
+                       : pairs_cn_plan(P.nproj, P.nbb, P.nh, P.prec == PW_FP64, cap).splits;
+    }
+    const size_t parts = P.rspace ? 0 : align_up(w.nsplit * per_split);
+    const long left = room - (long)(apart ? parts : 0);
+    long fit = std::max(0L, left) / (long)(sb1 + g11);
+    while (fit > 0 && (long)(align_up(sb1 * fit) + align_up(g11 * fit)) > left) --fit;
+    const int want = batch_of(P, sb1 + g11);
+    w.batch = (int)std::max(1L, std::min<long>(want, fit));
+    w.batch = ceil_div(P.nbb, ceil_div(P.nbb, w.batch));  // equal batches
+    w.sb = align_up(sb1 * w.batch);
+    w.g1 = align_up(g11 * w.batch);
+    // of their own where the room has it: 101 bands on 32 x 64 x 96 in FP32 take 225 us, 233 on the sticks' memory
+    w.pparts = apart || (long)(w.sb + w.g1 + parts) <= room ? w.sb + w.g1 : 0;
+    w.need = std::max({w.sb + w.g1, w.pparts + parts, P.gram_bytes});
+    // A pass over few bands is bound by its latency: five launches of 5 us a batch.  32 x 64 x 96, 101 bands in
+    // FP32: 219 us in one batch, 260 in three, 315 in five, 509 in ten and 839 in twenty; with the planes inside
+    // LDS some 530.
+    return fit >= 1 && ceil_div(P.nbb, w.batch) <= std::max(6, 2 * ceil_div(P.nbb, want));
+  };
+  if (P.pencil_pitch) {
+    if (fill(P.pencil_pitch)) return w;
+    if (!P.fl.fused) {  // planes beyond LDS: the same form, rows without their padding if need be
+      if ((long)w.need > room) fill(P.g.n1a);
+      return w;
+    }
+  }
+  fill(0);
+  return w;
+}
+
+static void set_work(Plan& P, const Work& w) {
+  P.fft_batch = w.batch;
+  P.nsplit_proj = w.nsplit;
+  P.fl.pencil_n = w.pitch != 0;
+  if (w.pitch) P.fl.pitch = w.pitch;
+  P.lay.g1 = P.lay.sb + w.sb;
+  P.lay.pparts = P.lay.sb + w.pparts;
+}
+
 pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string* err) {
   if (!d) { *err = "null description"; return PW_EINVAL; }
   for (int i = 0; i < 3; ++i)
@@ -269,6 +339,7 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   P.ldh = (P.nh + 15) / 16 * 16;
   P.ldy = std::max(P.ldw, 2 * P.ldh);
   P.nproj32 = (P.nproj + 31) / 32 * 32;
+  P.bcols = P.nproj < 32 ? P.nproj : P.nproj32;
 
   // --- grid ----------------------------------------------------------------------
   const bool user_grid = d->fft_n[0] || d->fft_n[1] || d->fft_n[2];
@@ -339,20 +410,24 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
     }
   }
 
-  // --- batching ------------------------------------------------------------------
+  // --- batches, K splits and the work area ----------------------------------------
   const size_t cb = 2 * (size_t)P.real_bytes;
-  const size_t per_band_sb = (size_t)P.nst * g.n3 * cb;
-  const size_t per_band_g1 = P.fl.pencil_n ? (size_t)g.n3 * g.n2 * P.fl.pitch * cb
-                             : P.fl.fused ? 0 : (size_t)g.n3 * g.n2 * g.n1a * cb;
-  size_t budget = 192ull << 20;  // keep the stick/pencil intermediates of one batch cache-sized
-  if (const char* e = std::getenv("PW_FFT_BATCH_MB")) budget = (size_t)std::atol(e) << 20;
-  int fb = (int)(budget / (per_band_sb + per_band_g1));
-  if (fb < 1) fb = 1;
-  if (fb > P.nbb) fb = P.nbb;
-  P.fft_batch = fb;
-  // K splits: enough workgroups to fill the chip several times over (the pipelined split-bf16
+  const size_t nb = P.nbands, nproj = P.nproj;
+  const bool f64 = P.prec == PW_FP64;
+  const bool bkb = (P.flags & PW_FLAG_BF16_KB) != 0, bgr = (P.flags & PW_FLAG_BF16_GRAM) != 0;
+  const bool otf = (P.flags & PW_FLAG_BETA_OTF) != 0, lob = (P.flags & PW_FLAG_LOBPCG) != 0;
+  if (lob && P.nbb < P.nbands) {
+    *err = "PW_FLAG_LOBPCG needs every band in one block (the plan would filter in blocks)";
+    return PW_EINVAL;
+  }
+  // planes of Y and W for the Gram product: written by the nonlocal product's epilogue with
+  // split-precision projectors, split from Y and W before the Gram product with real-space ones
+  const bool gram_planes = (bkb || P.rspace) && bgr && P.nbb >= P.nbands;
+  P.yp_cols = bkb ? P.nbb * (gram_planes ? 2 : 1) : (gram_planes ? 2 * P.nbb : 0);
+  const size_t kb = lob ? 3 * nb : nb;  // largest dense problem
+  // K splits by tile count: enough workgroups to fill the chip several times over (the pipelined split-bf16
   // Gram product runs one workgroup per CU, and more, shorter chunks balance its tail: measured at
-  // Si512, 49 splits take 2 ms less than 25); the projection on pairs has its own rule
+  // Si512, 49 splits take 2 ms less than 25); the other products have rules of their own
   auto pick_split = [](int tiles, int K, int target = 2048) {
     int s = (target + tiles - 1) / tiles;
     int kmax = K / 512;
@@ -361,27 +436,49 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
     if (s < 1) s = 1;
     return s;
   };
-  const bool f64 = P.prec == PW_FP64;
-  const bool bkb = (P.flags & PW_FLAG_BF16_KB) != 0, bgr = (P.flags & PW_FLAG_BF16_GRAM) != 0;
-  P.nsplit_proj = P.nproj ? (bkb ? pairs_proj_splits(P.nproj, P.nbb, (int)(P.ldh / 16), 64)
-                                  : pairs_cn_plan(P.nproj, P.nbb, P.nh, f64, 64).splits)
-                          : 1;
-  // planes of Y and W for the Gram product: written by the nonlocal product's epilogue with
-  // split-precision projectors, split from Y and W before the Gram product with real-space ones
-  const bool gram_planes = (bkb || P.rspace) && bgr && P.nbb >= P.nbands;
-  P.yp_cols = bkb ? P.nbb * (gram_planes ? 2 : 1) : (gram_planes ? 2 * P.nbb : 0);
-  P.nsplit_gram = gram_planes ? pick_split(gemm_cn_bf16_planes_tiles(P.nbands, 2 * P.nbands), P.npw, 4096)
-                  : bgr       ? pick_split(gemm_cn_bf16_tiles(P.nbands, 2 * P.nbands), P.npw)
-                              : gemm_cn_splits(P.nbands, 2 * P.nbands, P.npw, f64, P.nbands);
-  const bool lob = (P.flags & PW_FLAG_LOBPCG) != 0;
-  if (lob && P.nbb < P.nbands) {
-    *err = "PW_FLAG_LOBPCG needs every band in one block (the plan would filter in blocks)";
-    return PW_EINVAL;
+  const int ns_gram16 = gram_planes ? pick_split(gemm_cn_bf16_planes_tiles(P.nbands, 2 * P.nbands), P.npw, 4096)
+                                    : pick_split(gemm_cn_bf16_tiles(P.nbands, 2 * P.nbands), P.npw);
+  const int ns_lob16 = pick_split(gemm_cn_bf16_tiles(3 * P.nbands, 6 * P.nbands), P.npw);
+  P.fft_budget = 192ull << 20;  // the stick/pencil intermediates of one batch stay cache-sized
+  if (const char* e = std::getenv("PW_FFT_BATCH_MB")) P.fft_budget = (size_t)std::atol(e) << 20;
+  P.pencil_pitch = P.fl.pencil_n ? P.fl.pitch : 0;
+  const size_t sb1 = stick_bytes(P), g1_lds = pencil_bytes(P, 0);
+
+  // Room: callers keep arenas sized by footprint_bytes and the request loop admits by it, so a plan asks for no
+  // more than this layout: the projector table over the whole sphere, the sticks of a batch (and its pencils where
+  // a plane does not fit LDS), and split partials by the counts of 64 x 64 (FP32: 128 x 64) tiles.  The buffers of
+  // an H application and the Gram partials are never in use together and share one area, and in it so do the
+  // sticks and pencils with the projection's partials, unless H applications put the two on streams of their own
+  // (overlaps); the half that a table no longer has adds to it.
+  auto al = [](size_t x) { return align_up(x); };
+  auto splits64 = [&](size_t M, size_t N) { return pick_split(ceil_div(M, f64 ? 64 : 128) * ceil_div(N, 64), P.npw); };
+  const size_t half = otf || P.rspace ? 0 : cb * P.ldh * (bkb ? (size_t)P.bcols : nproj);
+  const size_t whole = otf || P.rspace ? 0 : cb * P.ldw * nproj;
+  const size_t pt_bytes = cb * std::max<size_t>(1, bkb ? (size_t)P.nproj32 : nproj) * P.nbb;
+  const size_t yp_bytes = 8 * (size_t)P.ldy * P.yp_cols;
+  long room = 0;
+  {
+    const int ns_proj = !nproj ? 1
+                        : bkb  ? pick_split(gemm_cn_bf16_planes_tiles(P.nproj, P.nbb), P.npw, 4096)
+                               : splits64(nproj, P.nbb);
+    const size_t parts = std::max({(size_t)ns_proj * nproj * P.nbb,
+                                   (size_t)(gram_planes || bgr ? ns_gram16 : splits64(nb, 2 * nb)) * nb * 2 * nb,
+                                   lob ? (size_t)(bgr ? ns_lob16 : splits64(kb, 2 * kb)) * kb * 2 * kb : 0});
+    const size_t batch = batch_of(P, sb1 + g1_lds);
+    room = (long)(al(sb1 * batch) + al(g1_lds * batch) + al(16 * parts) + al(cb * std::max<size_t>(1, nproj) * P.nbb) +
+                  al(8 * (size_t)P.ldw * P.yp_cols)) -
+           (long)(al(pt_bytes) + al(yp_bytes));
   }
-  P.nsplit_lob = !lob  ? 0
-                 : bgr ? pick_split(gemm_cn_bf16_tiles(3 * P.nbands, 6 * P.nbands), P.npw)
-                       : gemm_cn_splits(3 * P.nbands, 6 * P.nbands, P.npw, f64, 0);
-  const size_t kb = lob ? 3 * (size_t)P.nbands : (size_t)P.nbands;  // largest dense problem
+  const long spare = (long)al(whole) - (long)al(half);
+  // Gram partials: no more splits than the room holds
+  auto gram_fit = [&](int splits, size_t n) {
+    return (int)std::max<long>(1, std::min<long>(splits, (room + std::min<long>(spare, 0)) / (long)(32 * n * n)));
+  };
+  P.nsplit_gram = gram_planes || bgr ? ns_gram16
+                                     : gram_fit(gemm_cn_splits(P.nbands, 2 * P.nbands, P.npw, f64, P.nbands), nb);
+  P.nsplit_lob = !lob ? 0 : bgr ? ns_lob16 : gram_fit(gemm_cn_splits(3 * P.nbands, 6 * P.nbands, P.npw, f64, 0), kb);
+  P.gram_bytes = align_up(16 * std::max((size_t)P.nsplit_gram * nb * 2 * nb, (size_t)P.nsplit_lob * kb * 2 * kb));
+  const Work base = choose_work(P, room, 0), work = spare ? choose_work(P, room + spare, 0) : base;
 
   // --- arena layout --------------------------------------------------------------
   ArenaLayout& L = P.lay;
@@ -392,7 +489,6 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
     return o;
   };
   const size_t rb = P.real_bytes;
-  const size_t nb = P.nbands;
   const size_t nr = (size_t)g.n1 * g.n2 * g.n3;
   L.miller = take(sizeof(int) * 3 * P.npw);
   L.sticks = take(sizeof(Stick) * P.nst);
@@ -408,17 +504,11 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   L.mpha = take(sizeof(double) * std::max<size_t>(1, P.mode_amp.size()));
   L.vg = take(sizeof(double) * 2 * P.npw);
   L.dscale = take(sizeof(double) * 4);
-  const bool otf = (P.flags & PW_FLAG_BETA_OTF) != 0;
   for (int i = 0; i < 3; ++i) P.hmax[i] = 0;
   for (int gi = 0; gi < P.npw; ++gi)
     for (int i = 0; i < 3; ++i) P.hmax[i] = std::max(P.hmax[i], std::abs(P.miller[3 * gi + i]));
   P.bwidth = (2 * P.hmax[0] + 1) + (2 * P.hmax[1] + 1) + (2 * P.hmax[2] + 1);
-  // The table over half the sphere takes the room a table over all of it would, less the pencil intermediate of
-  // planes that could also run inside LDS: plans keep the sizes that arenas were made for, and the forms without
-  // a table are smaller by a whole one.
-  const size_t half = cb * P.ldh * (bkb ? P.nproj32 : P.nproj), whole = cb * P.ldw * P.nproj;
-  const size_t shared = P.fl.pencil_n && P.fl.fused ? per_band_g1 * P.fft_batch : 0;
-  L.beta = take(otf || P.rspace ? 0 : std::max(half, whole - std::min(whole, shared)));
+  L.beta = take(half);
   L.brad = take(otf ? sizeof(double) * 4 * P.npw : 0);
   L.bph = take(otf ? 16 * (size_t)P.natoms * P.bwidth : 0);
   const bool blocked = P.nbb < P.nbands;
@@ -426,14 +516,9 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   L.u1 = take(cb * P.ldw * P.nbb);
   L.zb = take(cb * P.ldw * P.nbb);
   L.wf = take(blocked ? cb * P.ldw * nb : 0);
-  L.sb = take(per_band_sb * P.fft_batch);
-  L.g1 = take(per_band_g1 * P.fft_batch);
-  L.pt = take(cb * std::max(1, bkb ? P.nproj32 : P.nproj) * P.nbb);
+  L.pt = take(pt_bytes);
   // bf16 hi/lo planes of the block entering the projector product (split-precision projectors)
-  L.yp = take(8 * (size_t)P.ldy * P.yp_cols);
-  const size_t parts = std::max({(size_t)P.nsplit_proj * P.nproj * P.nbb, (size_t)P.nsplit_gram * nb * 2 * nb,
-                                  (size_t)P.nsplit_lob * kb * 2 * kb});
-  L.parts = take(16 * parts);
+  L.yp = take(yp_bytes);
   L.sh = take(16 * kb * 2 * kb);
   L.ct = take(cb * kb * kb);
   L.ct2 = take(blocked ? cb * nb * nb : 0);
@@ -454,9 +539,25 @@ pw_status make_plan(const pw_cell_desc* d, size_t max_lds, Plan* p, std::string*
   L.rsbe = take(sizeof(RsEnt) * P.rs_bent.size());
   L.rsao = take(sizeof(int) * P.rs_aoff.size());
   L.rsae = take(sizeof(int) * P.rs_aent.size());
-  L.rsp = take(32 * nent * (size_t)(P.rspace ? P.fft_batch : 0));  // 4 complex FP32 per band and entry
+  L.rsp = take(32 * nent * (size_t)(P.rspace ? work.batch : 0));  // 4 complex FP32 per band and entry
+  // Work area of an H application (sticks, pencils, projection partials) and of the Gram products (partials), last:
+  // a larger arena extends it.  With a table it keeps the room of the half that the table no longer has, so that
+  // footprints of the forms with and without a table differ by a whole one.
+  L.sb = L.parts = take(std::max(work.need, base.need + (size_t)std::max(0L, spare)));
   L.total = off;
+  set_work(P, work);
   return PW_OK;
+}
+
+size_t plan_useful_bytes(const Plan& P) {
+  if (P.rspace) return P.lay.total;
+  return std::max(P.lay.total, P.lay.sb + choose_work(P, 1L << 60, P.nsplit_proj).need);
+}
+
+void widen_plan(Plan* P, size_t arena_bytes) {
+  if (P->rspace || arena_bytes <= P->lay.total) return;
+  const Work w = choose_work(*P, (long)((arena_bytes - P->lay.sb) / kArenaAlign * kArenaAlign), P->nsplit_proj);
+  if (P->lay.sb + w.need <= arena_bytes && (w.batch > P->fft_batch || (w.pitch && !P->fl.pencil_n))) set_work(*P, w);
 }
 
 }  // namespace pw

@@ -133,6 +133,7 @@ def lib() -> ctypes.CDLL:
     vp = ctypes.c_void_p
     sig = {
         "pw_plan": ([P(CellDesc), P(Info)]),
+        "pw_plan_arena": ([P(CellDesc), P(ctypes.c_size_t)]),
         "pw_plan_gvectors": ([P(CellDesc), P(ctypes.c_int)]),
         "pw_setup": ([P(CellDesc), vp, ctypes.c_size_t, vp, P(vp)]),
         "pw_query": ([vp, P(Info)]),
@@ -254,9 +255,14 @@ class Handle:
         self.dtype = torch.complex128 if prec == PW_FP64 else torch.complex64
         d, self._keep = make_desc(cell, prec, nbands, fft_n, flags, filter_block, proj_form, rs_radius)
         self.info = Info()
-        _check(lib().pw_plan(ctypes.byref(d), ctypes.byref(self.info)))
+        useful = ctypes.c_size_t()
+        _check(lib().pw_plan_arena(ctypes.byref(d), ctypes.byref(useful)))
         self.device = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
-        self.arena = torch.empty(int(self.info.footprint_bytes), dtype=torch.uint8, device=self.device)
+        try:
+            self.arena = torch.empty(useful.value, dtype=torch.uint8, device=self.device)
+        except torch.OutOfMemoryError:  # the footprint alone, with smaller FFT batches
+            _check(lib().pw_plan(ctypes.byref(d), ctypes.byref(self.info)))
+            self.arena = torch.empty(int(self.info.footprint_bytes), dtype=torch.uint8, device=self.device)
         self.stream = torch.cuda.current_stream(self.device) if stream is None else stream
         h = ctypes.c_void_p()
         _check(lib().pw_setup(ctypes.byref(d), ctypes.c_void_p(self.arena.data_ptr()),
