@@ -169,7 +169,7 @@ static Work choose_work(const Plan& P, long room, int nsplit) {
     while (fit > 0 && (long)(align_up(sb1 * fit) + align_up(g11 * fit)) > left) --fit;
     const int want = batch_of(P, sb1 + g11);
     w.batch = (int)std::max(1L, std::min<long>(want, fit));
-    w.batch = ceil_div(P.nbb, ceil_div(P.nbb, w.batch));  // equal batches
+    if (fit < want) w.batch = ceil_div(P.nbb, ceil_div(P.nbb, w.batch));  // equal batches
     w.sb = align_up(sb1 * w.batch);
     w.g1 = align_up(g11 * w.batch);
     // of their own where the room has it: 101 bands on 32 x 64 x 96 in FP32 take 225 us, 233 on the sticks' memory
