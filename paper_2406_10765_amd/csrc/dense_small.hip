@@ -161,7 +161,23 @@ __global__ __launch_bounds__(64 * kWaves) void k_hetrd_small(const double2* __re
       if (lane + 64 * j > k + 1) s = fma(xv[j].x, xv[j].x, fma(xv[j].y, xv[j].y, s));
     }
     s = wave_sum(s);
-    const double2 al = x[k + 1];
+    double2 al = x[k + 1];
+    double down = 1.0;
+    if (const double t = fma(al.x, al.x, fma(al.y, al.y, s)); !(t > 1e-270 && t < 1e270)) {
+      // squares near or beyond the ends of the range (a zero column too): the same column times 2^600 or 2^-600
+      const double up = t < 1.0 ? 0x1p600 : 0x1p-600;
+      down = t < 1.0 ? 0x1p-600 : 0x1p600;
+      al.x *= up;
+      al.y *= up;
+      s = 0.0;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        xv[j].x *= up;
+        xv[j].y *= up;
+        if (lane + 64 * j > k + 1) s = fma(xv[j].x, xv[j].x, fma(xv[j].y, xv[j].y, s));
+      }
+      s = wave_sum(s);
+    }
     double beta = al.x;
     double2 tk = cz(), sc = cz();
     if (s != 0.0 || al.y != 0.0) {
@@ -181,7 +197,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_hetrd_small(const double2* __re
     }
     if (tid == 0) {
       tau[k] = tk;
-      E[k] = beta;
+      E[k] = beta * down;
     }
     wave_sync();
     // y = A v, rows below k
