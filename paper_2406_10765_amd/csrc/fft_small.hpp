@@ -6,6 +6,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "fft_trig.hpp"
 
 namespace pw {
 
@@ -18,26 +19,6 @@ template <int N, typename F>
 __device__ __forceinline__ void sfor(F&& f) {
   sfor_impl(f, std::make_integer_sequence<int, N>{});
 }
-
-// ---- compile-time trigonometry (twiddles of the small DFTs) ------------------------------
-constexpr double kPiC = 3.14159265358979323846264338327950288;
-// sin(x + q pi / 2) for |x| <= pi / 4 by the power series of sin or cos
-constexpr double csin_q(double x, int q) {
-  double term = q % 2 ? 1.0 : x, sum = term;
-  for (int n = 1; n < 14; ++n) {
-    const int k = q % 2 ? 2 * n - 1 : 2 * n;
-    term *= -x * x / (k * (k + 1));
-    sum += term;
-  }
-  return q >= 2 ? -sum : sum;
-}
-// x reduced to the nearest multiple of pi / 2, so that no series term exceeds the result's order
-constexpr double csin_from(double x, int q) {
-  const int k = (int)(x / (kPiC / 2) + (x < 0 ? -0.5 : 0.5));
-  return csin_q(x - k * (kPiC / 2), (((k + q) % 4) + 4) % 4);
-}
-constexpr double csin(double x) { return csin_from(x, 0); }
-constexpr double ccos(double x) { return csin_from(x, 1); }
 
 // In-register DFT of compile-time size S with sign SG (+1 inverse, -1 forward), natural order.
 template <typename T, int S, int SG>
@@ -82,9 +63,8 @@ struct SmallDft {
             constexpr int q = 4 * g * kf / S % 4;
             u[kf] = q == 2 ? mk<T>(-u[kf].x, -u[kf].y) : cmuli<T>(u[kf], q == 1 ? SG : -SG);
           } else if constexpr (g * kf != 0) {
-            constexpr int turn = 2 * g * kf > S ? g * kf - S : g * kf;  // angle within [-pi, pi]
-            constexpr double ang = SG * 2.0 * kPiC * (double)turn / (double)S;
-            constexpr T wc = (T)ccos(ang), ws = (T)csin(ang);
+            constexpr T wc = (T)turn_cos(g * kf, S), ws = (T)turn_sin(SG * g * kf, S);
+            static_assert(wc <= 1 && wc >= -1 && ws <= 1 && ws >= -1, "a constant for every angle");
             u[kf] = cmul<T>(u[kf], mk<T>(wc, ws));
           }
           t[g][kf] = u[kf];
