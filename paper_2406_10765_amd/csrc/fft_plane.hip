@@ -1134,7 +1134,8 @@ __device__ __forceinline__ int stick_index(int z, int h, int N) {
 }
 
 // sphere -> sticks, inverse FFT along z.  Grid (ceil(nst / SPW), nbatch).  SB layout [band][z][stick].
-template <typename T, int A, int B>
+// TOP: largest |n3| carried, stick_top for a cutoff on a z shell, otherwise plane_top (points_empty).
+template <typename T, int A, int B, int TOP>
 __global__ __launch_bounds__(256) void k_sticks_inv_n(const cplx<T>* __restrict__ X, long ldx,
                                                       cplx<T>* __restrict__ SB, const Stick* __restrict__ st,
                                                       GridDesc g, const cplx<T>* __restrict__ twg) {
@@ -1157,7 +1158,7 @@ __global__ __launch_bounds__(256) void k_sticks_inv_n(const cplx<T>* __restrict_
   for (int i = 0; i < I1; ++i)
 #pragma unroll
     for (int n1 = 0; n1 < A; ++n1) {
-      const int e = act && !stick_empty(N, B, n1) ? stick_index(B * n1 + t + TT * i, h, N) : -1;
+      const int e = act && !points_empty(N, B, n1, TOP) ? stick_index(B * n1 + t + TT * i, h, N) : -1;
       r1[i][n1] = e >= 0 ? xs[e] : mk<T>(0, 0);
     }
   __syncthreads();  // twiddles
@@ -1202,7 +1203,7 @@ __global__ __launch_bounds__(256) void k_sticks_inv_n(const cplx<T>* __restrict_
 
 // sticks -> sphere, forward FFT along z.  UPD (FP32): the Chebyshev update of StickUpd is applied to
 // each value as it is written (Z is then the updated block).
-template <typename T, int A, int B, bool UPD = false>
+template <typename T, int A, int B, int TOP, bool UPD = false>
 __global__ __launch_bounds__(256) void k_sticks_fwd_n(const cplx<T>* __restrict__ SB, cplx<T>* __restrict__ Z,
                                                       long ldz, const Stick* __restrict__ st, GridDesc g,
                                                       const cplx<T>* __restrict__ twg, StickUpd u) {
@@ -1253,7 +1254,7 @@ __global__ __launch_bounds__(256) void k_sticks_fwd_n(const cplx<T>* __restrict_
 #pragma unroll
     for (int k2 = 0; k2 < B; ++k2) {
       const int e = stick_index(k1 + A * k2, h, N);
-      if (!stick_empty(N, A, k2) && e >= 0) {
+      if (!points_empty(N, A, k2, TOP) && e >= 0) {
         if constexpr (UPD) {
           const long i = (long)sk.off + e;
           const float2 y = u.Y[(long)b * u.ldy + i];
@@ -1290,15 +1291,27 @@ bool sticks_n_supported(int n3) {
   }
 }
 
+// The kernels for one length: the plan's largest |n3| decides what they leave out (always stick_top: a block of grid
+// points more at some lengths, H X of 8 atoms on 24 points 36.6 us, 36.5 with plane_top).
+#define PW_STICK_LAUNCH(KERNEL, TT, AA, BB, ...)                                                             \
+  do {                                                                                                       \
+    constexpr int lo = plane_top(AA * BB), hi = stick_top(AA * BB);                                          \
+    const dim3 grid(ceil_div(g.nst, StickShape<TT, AA, BB>::SPW), nbatch), wg(StickShape<TT, AA, BB>::NT);   \
+    if (g.n3max <= lo) hipLaunchKernelGGL((KERNEL(TT, AA, BB, lo)), grid, wg, 0, s, __VA_ARGS__);            \
+    else if (g.n3max <= hi) hipLaunchKernelGGL((KERNEL(TT, AA, BB, hi)), grid, wg, 0, s, __VA_ARGS__);       \
+    else return hipErrorInvalidValue;                                                                        \
+  } while (0)
+#define PW_STICKS_INV(TT, AA, BB, TOP) k_sticks_inv_n<TT, AA, BB, TOP>
+#define PW_STICKS_FWD(TT, AA, BB, TOP) k_sticks_fwd_n<TT, AA, BB, TOP>
+#define PW_STICKS_UPD(TT, AA, BB, TOP) k_sticks_fwd_n<TT, AA, BB, TOP, true>
+
 template <typename T>
 hipError_t launch_sticks_inv_n(const cplx<T>* X, long ldx, cplx<T>* SB, int nbatch, const Stick* st,
                                const GridDesc& g, const cplx<T>* tw3, hipStream_t s) {
-  if (g.n3max > stick_top(g.n3)) return hipErrorInvalidValue;
   switch (g.n3) {
-#define PW_CASE(NN, AA, BB)                                                                                   \
-  case NN:                                                                                                    \
-    hipLaunchKernelGGL((k_sticks_inv_n<T, AA, BB>), dim3(ceil_div(g.nst, StickShape<T, AA, BB>::SPW), nbatch),  \
-                       dim3(StickShape<T, AA, BB>::NT), 0, s, X, ldx, SB, st, g, tw3);                         \
+#define PW_CASE(NN, AA, BB)                                       \
+  case NN:                                                        \
+    PW_STICK_LAUNCH(PW_STICKS_INV, T, AA, BB, X, ldx, SB, st, g, tw3); \
     return hipGetLastError();
     PW_STICK_SIZES(PW_CASE)
 #undef PW_CASE
@@ -1310,12 +1323,10 @@ hipError_t launch_sticks_inv_n(const cplx<T>* X, long ldx, cplx<T>* SB, int nbat
 template <typename T>
 hipError_t launch_sticks_fwd_n(const cplx<T>* SB, cplx<T>* Z, long ldz, int nbatch, const Stick* st,
                                const GridDesc& g, const cplx<T>* tw3, hipStream_t s) {
-  if (g.n3max > stick_top(g.n3)) return hipErrorInvalidValue;
   switch (g.n3) {
-#define PW_CASE(NN, AA, BB)                                                                                   \
-  case NN:                                                                                                    \
-    hipLaunchKernelGGL((k_sticks_fwd_n<T, AA, BB>), dim3(ceil_div(g.nst, StickShape<T, AA, BB>::SPW), nbatch),  \
-                       dim3(StickShape<T, AA, BB>::NT), 0, s, SB, Z, ldz, st, g, tw3, StickUpd{});             \
+#define PW_CASE(NN, AA, BB)                                       \
+  case NN:                                                        \
+    PW_STICK_LAUNCH(PW_STICKS_FWD, T, AA, BB, SB, Z, ldz, st, g, tw3, StickUpd{}); \
     return hipGetLastError();
     PW_STICK_SIZES(PW_CASE)
 #undef PW_CASE
@@ -1326,13 +1337,10 @@ hipError_t launch_sticks_fwd_n(const cplx<T>* SB, cplx<T>* Z, long ldz, int nbat
 
 hipError_t launch_sticks_fwd_upd(const float2* SB, float2* out, long ldo, int nbatch, const Stick* st,
                                  const GridDesc& g, const float2* tw3, const StickUpd& u, hipStream_t s) {
-  if (g.n3max > stick_top(g.n3)) return hipErrorInvalidValue;
   switch (g.n3) {
-#define PW_CASE(NN, AA, BB)                                                                                     \
-  case NN:                                                                                                      \
-    hipLaunchKernelGGL((k_sticks_fwd_n<float, AA, BB, true>),                                                   \
-                       dim3(ceil_div(g.nst, StickShape<float, AA, BB>::SPW), nbatch),                           \
-                       dim3(StickShape<float, AA, BB>::NT), 0, s, SB, out, ldo, st, g, tw3, u);                 \
+#define PW_CASE(NN, AA, BB)                                       \
+  case NN:                                                        \
+    PW_STICK_LAUNCH(PW_STICKS_UPD, float, AA, BB, SB, out, ldo, st, g, tw3, u); \
     return hipGetLastError();
     PW_STICK_SIZES(PW_CASE)
 #undef PW_CASE
@@ -1340,6 +1348,10 @@ hipError_t launch_sticks_fwd_upd(const float2* SB, float2* out, long ldo, int nb
       return hipErrorInvalidValue;
   }
 }
+#undef PW_STICK_LAUNCH
+#undef PW_STICKS_INV
+#undef PW_STICKS_FWD
+#undef PW_STICKS_UPD
 
 template hipError_t launch_sticks_inv_n<float>(const cplx<float>*, long, cplx<float>*, int, const Stick*,
                                                const GridDesc&, const cplx<float>*, hipStream_t);

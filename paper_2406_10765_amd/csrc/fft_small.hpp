@@ -97,9 +97,6 @@ __device__ __host__ __forceinline__ constexpr bool points_empty(int N, int S, in
 __device__ __host__ __forceinline__ constexpr bool grid_empty(int N, int S, int block) {  // across the planes
   return points_empty(N, S, block, plane_top(N));
 }
-__device__ __host__ __forceinline__ constexpr bool stick_empty(int N, int S, int block) {  // along z
-  return points_empty(N, S, block, stick_top(N));
-}
 
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
 
