@@ -21,11 +21,11 @@
 // of lane l holds C[4 (l / 16) + r][l % 16] for f32 but C[l / 16 + 4 r][l % 16]
 // for f64 (measured with one-hot operands on gfx950).
 //
-// The complex products read their operands from global memory straight into the lanes' MFMA layout,
-// a wave per tile, with no LDS and no barrier between waves (below); the products on pairs go
-// through two LDS buffers, so each K tile costs one barrier, with the next one's global loads in
-// registers meanwhile.  Tiles are handed out XCD by XCD: consecutive tiles, which share operand
-// panels, run on the same L2.
+// The complex products and the nonlocal product on pairs read their operands from global memory
+// straight into the lanes' MFMA layout, a wave per tile, with no LDS and no barrier between waves
+// (below); the projection on pairs goes through two LDS buffers, so each K tile costs one barrier,
+// with the next one's global loads in registers meanwhile.  Tiles are handed out XCD by XCD: consecutive
+// tiles, which share operand panels, run on the same L2.
 
 #include <algorithm>
 #include <type_traits>
@@ -68,7 +68,10 @@ __device__ __forceinline__ int xcd_tile(int w, int total) {
 // K value u of lane group q (0..3) among the eight of a step: whole 64-byte pieces of a column per load in
 // fp64, 16-byte loads in fp32
 template <typename T>
-__device__ __forceinline__ constexpr int koff(int q, int u) { return std::is_same<T, double>::value ? 4 * u + q : 2 * q + u; }
+__device__ __forceinline__ constexpr int koff(int q, int u) {
+  return std::is_same<T, double>::value ? 4 * u + q : 2 * q + u;
+}
+
 // ------------------------------------------------------------------------------------------
 // Complex products, one wave per tile of 16 WA x 16 WB: each lane loads its own operands of eight K values
 // (two of each column or row, so 128-byte lines in fp64) from global memory and the next eight are in flight
@@ -102,7 +105,7 @@ __device__ __forceinline__ void mma_step(const cplx<T> (&av)[WA][2], const cplx<
 
 // cn: part[s] = A^H B over K chunk s, a quarter of the chunk per wave, the four waves' tiles summed in LDS.
 // herm > 0: the first herm columns of B are A itself; tiles of that Gram block wholly below its diagonal are
-// left out.  [S | H_s] of 144 bands over 37,073 plane waves in fp64: 195 us; 64 x 64 tiles through LDS
+// left out.  [S | H_s] of 144 bands over 37,073 plane waves in fp64: 160 us; 64 x 64 tiles through LDS
 // took 377 us.
 template <typename T, int WA, int WB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_cn(
@@ -675,10 +678,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // Blocks of a wave's tile (cn: 16 wa x 16 wb) and K splits from smin to smax, by the time of the busiest
 // compute unit: its steps of eight K values at the matrix cores' rate or at that of the loads (72 cycles per
 // 64-lane load of fp64 measured, half of that per value pair in fp32), whichever is longer, no step shorter
-// than the latency of its loads (a quarter longer with one wave per SIMD), + start and end of a round + the partials' traffic.  In fp64, 480 bands x
-// 125,001: 3 x 2 blocks reach 84 TFLOP/s, 2 x 2 77 and 1 x 1 42; 144 x 37,073: 200, 180 and 274 us (2 x 2 fills
-// the last round best); 40 x 5,891: 10.2, 11.8 and 8.5 us, where 11 splits of 64 x 64 tiles took 92 us on 22
-// compute units.
+// than the latency of its loads (a quarter longer with one wave per SIMD), + start and end of a round + the
+// partials' traffic.  [S | H_s] in fp64 without the tiles left out, in 3 x 2, 2 x 2 and 1 x 1 blocks: 480 bands x
+// 124,289 6.6, 7.3 and 13.4 ms (52, 47 and 26 TFLOP/s of what is computed); 1,088 x 295,667 80, 95 and 171 ms;
+// 144 x 37,073 162, 159 and 265 us (2 x 2 fills the last round best); 40 x 5,891 14.6, 10.7 and 7.7 us, where 11
+// splits of 64 x 64 tiles took 92 us on 22 compute units.
 struct CnShape {
   int wa, wb, splits;
 };

@@ -369,7 +369,7 @@ struct CnBPlanes {
 };
 
 // nn B-operand adapters: the K-contiguous columns of B as Br = (br, -bi) words, either fp32 split on
-// the fly or planes already holding those words (launch_reduce_planes).
+// the fly or planes already holding those words (launch_coef_planes).
 template <int NC, int NTH = 256>
 struct NnBF32 {
   SplitK<NC, false, true, NTH> l;  // B rows are small, scalar loads

@@ -523,10 +523,14 @@ struct ProjShape {
 constexpr ProjShape kProj[4] = {
     {256, 128, 1, 1.7, 1.7}, {128, 64, 2, 0.55, 0.9}, {64, 32, 3, 0.3, 0.3}, {256, 16, 1, 2.0, 2.0}};
 
-// The largest tile that the product fills: 64 x 32 below 65,536 outputs (256 projectors x 144 bands, 18,537 half
-// rows: 38.5 us, 44.5 us in 128 x 64; 864 x 440: 882 and 534 us); up to 16 bands (a Lanczos vector) the table's one read is the
-// cost and the narrow tile keeps three stages of it in flight (one band, 2,048 projectors: 0.48 ms, 5.0 TB/s
-// of a 2.4 GB table; 1.65 ms as complex products in 256 x 128 tiles).
+// The largest tile that the product fills.  Below 65,536 outputs 64 x 32, from there 128 x 64, at 18,537 half rows
+// (us in the one and the other): 256 projectors x 144 bands 38.5 and 44.5, 256 x 256 54.2 and 60.2, 256 x 300 71.9
+// and 65.1, 512 x 240 103 and 89; at 40,363 they cross sooner: 256 x 160 76.7 and 76.9, 256 x 240 111 and 103, 256 x 300
+// 179 and 144.  From 2^17 outputs 256 x 128 (128 x 64 and 256 x 128): 18,537 half rows 512 x 256 90 and 117, 864 x 200
+// 128 and 148; 40,363: 512 x 160 151 and 157, 512 x 256 214 and 190, 864 x 200 294 and 266, 864 x 440 534 and 467: the
+// line lies between the two lengths' own.  Up to 16 bands (a Lanczos vector) the table's one read is the cost and the
+// narrow tile keeps three stages of it in flight (one band, 2,048 projectors: 0.48 ms, 5.0 TB/s of a 2.4 GB table;
+// 1.65 ms as complex products in 256 x 128 tiles).
 int proj_shape(int M, int nb) {
   if (nb <= 16 && M >= 256) return 3;
   if (M >= 256 && nb >= 96 && (long)M * nb >= (1L << 17)) return 0;
@@ -603,8 +607,8 @@ hipError_t launch_pairs_nl(const unsigned int* Ah, const unsigned int* Al, long 
   // 128 half rows x 128 bands when that leaves several tiles per compute unit and pads the bands by at most a
   // tenth more than 64 would (1,088 bands: 8.64 ms, 9.45 in 64 x 64; 440 bands, 40,363 half rows: 616 us and 563);
   // 64 x 64 (two workgroups per compute unit) below, 64 x 48 where it pads less (144 bands, 18,537 half rows:
-  // 43.6 us, 48.7 in 64 x 64; at equal padding they are equal); 128 x 16 for few bands, where the table's read is the cost (one band, 2,048
-  // projectors: 0.56 ms; 2.1 ms as complex products in 128 x 128 tiles)
+  // 43.6 us, 48.7 in 64 x 64; at equal padding they are equal); 128 x 16 for few bands, where the table's read is
+  // the cost (one band, 2,048 projectors: 0.56 ms; 2.1 ms as complex products in 128 x 128 tiles)
   if (nb <= 16 && ktiles >= 8) PW_NL(4, 1, 2, 2, 3, 1);
   else if (nb >= 96 && (long)ceil_div(nh, 128) * ceil_div(nb, 128) >= 512 && 20 * ceil_div(nb, 128) <= 11 * ceil_div(nb, 64))
     PW_NL(2, 4, 4, 4, 2, 2);

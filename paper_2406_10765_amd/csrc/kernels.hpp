@@ -14,9 +14,10 @@ struct FftLaunch {
   bool sized_sticks;  // z transforms with a compile-time size kernel
   // pencil form with compile-time line lengths: planes that do not fit in LDS, and the others without a
   // sized fused kernel (unequal sides).  A sized fused plane moves a quarter of the bytes and stays ahead
-  // (64^2, 144 bands, FP32: 109 against 236 us; 96^2, 128 bands, FP64: 1,093 against 1,341 us)
+  // (64^2, 144 bands, FP32: 112 against 230 us; 96^2, 128 bands, FP64: 991 against 1,276 us).  A plan without
+  // room for the intermediate in a few batches clears it again
   bool pencil_n;
-  int pitch;          // its row pitch of G1: n1a rounded up to whole 128-byte lines
+  int pitch;          // its row pitch of G1: n1a rounded up to whole 16 bytes
   int plane_thr;
   int cx, cy;     // columns / rows per workgroup in the pencil form
   int col_thr, row_thr;
@@ -319,6 +320,7 @@ hipError_t launch_scale_cols_lam(const double2* in, long ldi, cplx<T>* out, long
 // Hermitian part: A <- (A + A^H)/2, n x n complex double
 hipError_t launch_hermitize(double2* A, long lda, int n, hipStream_t s);
 // Hermitian matrix from its upper triangle: A(i, j) <- conj(A(j, i)) for i > j, Im A(i, i) <- 0
+hipError_t launch_mirror_upper(double2* A, long lda, int n, hipStream_t s);
 // Small dense problems (dense_small.hip), matrices n x n with leading dimension n.
 bool dense_small_supported(int n);
 // S = L L^H in S's lower triangle; *info = 0, or 1 + the first column with a pivot that is not positive.
@@ -330,7 +332,6 @@ hipError_t launch_hetrd_small(const double2* A, int n, double2* V, double2* tau,
 // C = L^{-H} Q Z (Z real).
 hipError_t launch_back_small(const double2* V, const double2* tau, const double2* L, const double* Z, int n, double2* C,
                              hipStream_t s);
-hipError_t launch_mirror_upper(double2* A, long lda, int n, hipStream_t s);
 // r_j = || W_j - lam_j X_j ||_2 with double accumulation; flag[0] |= non-finite seen
 template <typename T>
 hipError_t launch_resid(const cplx<T>* W, long ldw, const cplx<T>* X, long ldx, const double* lam, int rows,
